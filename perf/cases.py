@@ -696,8 +696,8 @@ def exact_samples(case, seed):
             n += (k * k * top <= N * N * sq).long()
         t = torch.repeat_interleave(torch.arange(len(n), device=DEV), n)
         k = torch.arange(len(t), device=DEV) - torch.repeat_interleave(torch.cumsum(n, 0) - n, n)
-        u1 = (k + 0.5) / n[t]
-        u2 = sum(((k >> b) & 1) * 2.0 ** -(b + 1) for b in range(8))
+        u1 = (k.to(F64) + 0.5) / n[t]
+        u2 = sum(((k >> b) & 1).to(F64) * 2.0 ** -(b + 1) for b in range(8))
         low = u2 > u1
         b0 = torch.where(low, 0.5 * u1, u1 - 0.5 * u2)
         b1 = torch.where(low, u2 - 0.5 * u1, 0.5 * u2)
