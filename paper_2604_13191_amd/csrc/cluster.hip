@@ -7,27 +7,45 @@
 // follows Ward's rule (least w_a w_b / (w_a + w_b) * D, ties to the first pair), then a few
 // weighted Lloyd passes refine the K clusters.  Merging is additive: (w_a + w_b, S_a + S_b).
 //
-// Mapping: a group of G lanes (G = 8 at level 1, 8K rounded up to a power of two above)
-// handles one parent voxel; lane m holds input lobe m; the cluster sums and the pairwise cost
-// matrix live in the group's LDS.  Every reduction has a fixed order (butterflies for the
-// argmin, member-order sums for the Lloyd centroids): the result is deterministic.
+// Mapping: a block takes a run of coarse voxels.  First one lane per voxel counts its input
+// lobes; voxels with at most K are finished there (their lobes, sorted).  The others are listed
+// in LDS by the number of lanes they need (8, 16, 32 or 64), and the waves serve each list with
+// full rounds of 64 / G voxels: lane m of a group holds input lobe m, the clusters and the
+// symmetric matrix of pairwise costs live in LDS.  Every reduction has a fixed order, so the
+// result is deterministic and depends neither on the group width nor on the grid.
+//
+// The clustering is bound by VALU issue and, on levels of a few thousand voxels, by the latency of
+// one round's chain of merges.  A merge step therefore keeps no cached minima: each lane rereads
+// its row (G / 4 16-byte loads) and takes its least cost with integer minima (costs are
+// non-negative: their bits order like the values), about 105 instructions against 250 with cached
+// minima, 64-bit keys and rescans.  Levels above the first, K = 4: the whole brushed surface (2.1 M
+// voxels at level 2) 3.31 -> 2.11 ms, 14 fabric patches 5.25 -> 1.47 ms, a sphere of 1.0 M leaf
+// voxels, where most voxels gather 17 to 32 lobes, 3.94 -> 0.47 ms (its levels had too few rounds
+// in flight).  First level (few voxels hold more than K lobes): 0.78 -> 0.50 ms.
 #include "vx_internal.hpp"
 
 namespace vx {
 
-// D between two normalised lobes a = S_a / w_a, b = S_b / w_b
+constexpr uint32_t kNoCost = 0x7f800000u;        // +inf: no pair (a NaN cost orders above it)
+
+// D between two normalised lobes a = S_a / w_a, b = S_b / w_b.  The operations and their fusions
+// are spelled out: near-equal costs must compare alike wherever they are computed.
 __device__ __forceinline__ float lobe_dist_n(const float* a, const float* b) {
+#pragma clang fp contract(off)
   float d[6];
 #pragma unroll
   for (int j = 0; j < 6; ++j) d[j] = a[j] - b[j];
-  const float tr = d[0] + d[1] + d[2];
-  const float t2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2] + 2.0f * (d[3] * d[3] + d[4] * d[4] + d[5] * d[5]);
-  return 2.0f * t2 + tr * tr;
+  const float tr = (d[0] + d[1]) + d[2];
+  const float diag = __builtin_fmaf(d[2], d[2], __builtin_fmaf(d[0], d[0], d[1] * d[1]));
+  const float off = __builtin_fmaf(d[5], d[5], __builtin_fmaf(d[3], d[3], d[4] * d[4]));
+  const float t2 = __builtin_fmaf(2.0f, off, diag);
+  return __builtin_fmaf(tr, tr, t2 + t2);
 }
 
-// Ward's merge cost w_a w_b / (w_a + w_b) D (reciprocals to 1 ulp)
+// Ward's merge cost w_a w_b / (w_a + w_b) D (reciprocals to 1 ulp); symmetric bit for bit
 __device__ __forceinline__ float ward_cost(float wa, float wb, const float* na, const float* nb) {
-  return wa * wb * __builtin_amdgcn_rcpf(wa + wb) * lobe_dist_n(na, nb);
+#pragma clang fp contract(off)
+  return (wa * wb * __builtin_amdgcn_rcpf(wa + wb)) * lobe_dist_n(na, nb);
 }
 
 template <int G>
@@ -36,579 +54,386 @@ __device__ __forceinline__ uint64_t group_bits(uint64_t ballot, int gi) {
   return (ballot >> (gi * G)) & ((uint64_t(1) << G) - 1);
 }
 
-// minimum of a 64-bit key over the G lanes of a group: DPP within rows of 16 (xor 1 and 2 by
-// quad permutes, then the half-row and row mirrors, each pairing every lane with a partner of
-// the other half), then cross-row exchanges for G = 32 and 64
-__device__ __forceinline__ uint64_t dpp_min_u64(uint64_t v, int ctrl_tag) {
-  const int lo = int(uint32_t(v)), hi = int(uint32_t(v >> 32));
-  int olo, ohi;
-  switch (ctrl_tag) {
-    case 0:
-      olo = __builtin_amdgcn_update_dpp(lo, lo, 0xB1, 0xF, 0xF, false);
-      ohi = __builtin_amdgcn_update_dpp(hi, hi, 0xB1, 0xF, 0xF, false);
-      break;
-    case 1:
-      olo = __builtin_amdgcn_update_dpp(lo, lo, 0x4E, 0xF, 0xF, false);
-      ohi = __builtin_amdgcn_update_dpp(hi, hi, 0x4E, 0xF, 0xF, false);
-      break;
-    case 2:
-      olo = __builtin_amdgcn_update_dpp(lo, lo, 0x141, 0xF, 0xF, false);
-      ohi = __builtin_amdgcn_update_dpp(hi, hi, 0x141, 0xF, 0xF, false);
-      break;
-    default:
-      olo = __builtin_amdgcn_update_dpp(lo, lo, 0x140, 0xF, 0xF, false);
-      ohi = __builtin_amdgcn_update_dpp(hi, hi, 0x140, 0xF, 0xF, false);
-      break;
-  }
-  const uint64_t o = (uint64_t(uint32_t(ohi)) << 32) | uint32_t(olo);
-  return o < v ? o : v;
-}
-
+// minimum over the G lanes of a group: DPP within rows of 16 (xor 1 and 2 by quad permutes, then
+// the half-row and row mirrors, each pairing every lane with a partner of the other half), then
+// row and half exchanges for G = 32 and 64
 template <int G>
-__device__ __forceinline__ uint64_t group_min_u64(uint64_t v) {
-  v = dpp_min_u64(v, 0);
-  v = dpp_min_u64(v, 1);
-  if (G > 4) v = dpp_min_u64(v, 2);
-  if (G > 8) v = dpp_min_u64(v, 3);
+__device__ __forceinline__ uint32_t group_min_u32(uint32_t v) {
+  auto least = [](uint32_t a, int b) { return uint32_t(b) < a ? uint32_t(b) : a; };
+  v = least(v, __builtin_amdgcn_update_dpp(0, int(v), 0xB1, 0xF, 0xF, true));
+  v = least(v, __builtin_amdgcn_update_dpp(0, int(v), 0x4E, 0xF, 0xF, true));
+  if (G > 4) v = least(v, __builtin_amdgcn_update_dpp(0, int(v), 0x141, 0xF, 0xF, true));
+  if (G > 8) v = least(v, __builtin_amdgcn_update_dpp(0, int(v), 0x140, 0xF, 0xF, true));
   if (G > 16) {
-    const uint64_t o = uint64_t(__shfl_xor((unsigned long long)v, 16, 64));
-    v = o < v ? o : v;
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = least(r[0], int(r[1]));
   }
   if (G > 32) {
-    const uint64_t o = uint64_t(__shfl_xor((unsigned long long)v, 32, 64));
-    v = o < v ? o : v;
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = least(r[0], int(r[1]));
   }
   return v;
 }
 
+// a lobe in LDS: (w, xx, yy, zz), (xy, xz, yz, -)
+struct LobeQ {
+  float4 a, b;
+};
+__device__ __forceinline__ void lobe_unpack(const LobeQ& q, float& w, float* S) {
+  w = q.a.x;
+  S[0] = q.a.y;
+  S[1] = q.a.z;
+  S[2] = q.a.w;
+  S[3] = q.b.x;
+  S[4] = q.b.y;
+  S[5] = q.b.z;
+}
+__device__ __forceinline__ LobeQ lobe_pack(float w, const float* S) {
+  return LobeQ{make_float4(w, S[0], S[1], S[2]), make_float4(S[3], S[4], S[5], 0.f)};
+}
+// the lobe's weight and normalised moments
+__device__ __forceinline__ void lobe_norm(const LobeQ& q, float& w, float* n) {
+  float S[6];
+  lobe_unpack(q, w, S);
+  const float iw = __builtin_amdgcn_rcpf(w);
+#pragma unroll
+  for (int t = 0; t < 6; ++t) n[t] = S[t] * iw;
+}
+
+// Rows of the cost matrix are padded by four words: the 16-byte row reads of 16 lanes then cover
+// all 64 banks once.  The input lobes wait in registers while the matrix is needed and take its
+// place for the Lloyd passes, so that three blocks of up to 32-lane groups fit a CU's 160 KB.
 template <int G>
 struct ClusterLds {
-  float lw[64 / G][G];
-  float lS[64 / G][6][G];
-  float cw[64 / G][G];
-  float cS[64 / G][6][G];
-  float nS[64 / G][6][G];     // cluster lobes normalised by their weight
-  float mat[64 / G][G][G + 1];   // [j][g]: row g's cost to column j (rows padded: no bank clashes)
-  int asg[64 / G][G];
+  LobeQ clu[64 / G][G];          // the clusters' sums
+  union {
+    uint32_t mat[64 / G][G][G + 4];
+    LobeQ lob[64 / G][G];        // the input lobes
+  };
+  uint32_t asg[64 / G][G / 4];   // Lloyd: each lobe's cluster, a byte each (255: no lobe)
 };
 
-// One round of one wave: group gi (gi < 64 / G) takes parent p (when live) of a level whose children
-// [pstart[p], pstart[p+1]) in the level below carry lobes cw[k * cap_c + c] and
-// cS[(j * Kc + k) * cap_c + c] (cnl == nullptr: one lobe per child, present when its weight is
-// positive).
-// BAND: parents that gather more than G lobes are left to a wider pass, and (LO > 0) those that
-// gather at most LO to an earlier, narrower one; with LO = 0 this pass also writes the parents
-// that gather no lobe.
-template <int G, bool BAND = false, int LO = 0, int SLOTS = 64>
-__device__ __forceinline__ void cluster_round(int64_t p, bool live, const int64_t* __restrict__ pstart,
-                                              const float* __restrict__ cw, const float* __restrict__ cS,
-                                              const uint8_t* __restrict__ cnl, int Kc, int64_t cap_c, int K,
-                                              int iters, const vx_lobes& out, ClusterLds<G>& L) {
+// the lobes of a level: one per voxel (nl == nullptr, present when its weight is positive) or up
+// to Kc per voxel, w[k * cap + c] and S[(j * Kc + k) * cap + c]
+struct ChildLobes {
+  const float* w;
+  const float* S;
+  const uint8_t* nl;
+  int Kc;
+  int64_t cap;
+};
+
+// lobe number m (child-major, then lobe order) of a voxel: nibble i of word counts child i's lobes
+__device__ __forceinline__ void nth_lobe(uint32_t word, int m, int& ch, int& k) {
+  ch = 0;
+#pragma unroll
+  for (int i = 0; i < 7; ++i) {
+    const int c = int((word >> (4 * i)) & 15u);
+    const bool past = ch == i && m >= c;
+    m = past ? m - c : m;
+    ch = past ? i + 1 : ch;
+  }
+  k = m;
+}
+
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// One round of one wave: group gi (gi < 64 / G) reduces the n input lobes (K < n <= G; 0 when not
+// live) of coarse voxel p, whose children start at cs.
+template <int G>
+__device__ __forceinline__ void cluster_round(int64_t p, bool live, int64_t cs, uint32_t word, int n,
+                                              const ChildLobes& C, int K, int iters, const vx_lobes& out,
+                                              ClusterLds<G>& L) {
   const int lane = lane_id();
   const int g = lane % G, gi = lane / G;
-  const int64_t cap = out.cap;
-  // ---- gather the children's lobes in canonical order (child, then lobe), compacted to lanes
-  // 0..n-1.  Lane g takes slots g, g + G, ... of the 8 Kc (child, lobe) slots; n <= G is the
-  // caller's guarantee (G >= 8 Kc, or a parent known to gather at most G lobes).
-  // All of this lane's slots are loaded first (the weight and moment together with the lobe
-  // count, all in bounds whatever the count), then compacted in slot order: one round of
-  // dependent loads after the parent's child range instead of one chain per slot.
-  const int slots = 8 * Kc;
-  constexpr int R = (SLOTS + G - 1) / G;           // slots per lane at most (8 Kc <= SLOTS)
-  int64_t cs = 0, ce = 0;
-  if (live) {
-    cs = pstart[p];
-    ce = pstart[p + 1];
-  }
-  float rw[R], rS[R][6];
-  bool rv[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int slot = r * G + g;
-    rw[r] = 0.f;
-    rv[r] = false;
-#pragma unroll
-    for (int j = 0; j < 6; ++j) rS[r][j] = 0.f;
-    if (live && slot < slots) {
-      const int ch = slot / Kc, k = slot % Kc;
-      const int64_t c = cs + ch;
-      if (c < ce) {
-        const int nl = cnl ? int(cnl[c]) : 1;
-        rw[r] = cw[int64_t(k) * cap_c + c];
-#pragma unroll
-        for (int j = 0; j < 6; ++j) rS[r][j] = cS[(int64_t(j) * Kc + k) * cap_c + c];
-        rv[r] = k < nl && rw[r] > 0.f;
-      }
-    }
-  }
-  int n = 0;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const uint64_t vm = group_bits<G>(__ballot(rv[r]), gi);
-    const int m = n + __popcll(vm & ((uint64_t(1) << g) - 1));
-    if (rv[r] && m < G) {
-      L.lw[gi][m] = rw[r];
-#pragma unroll
-      for (int j = 0; j < 6; ++j) L.lS[gi][j][m] = rS[r][j];
-    }
-    n += __popcll(vm);
-  }
-  if (BAND && (n > G || (LO > 0 && n <= LO))) {
-    live = false;                                  // another pass takes this parent
-    n = 0;
-  }
-  n = n < G ? n : G;
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   const bool mine = g < n;
-  float lw = 0.f, lS[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, ln[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  float w = 0.f, nrm[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // this lane's cluster
+  LobeQ own{};                                               // and its input lobe
   if (mine) {
-    lw = L.lw[gi][g];
-    const float il = __builtin_amdgcn_rcpf(lw);
+    int ch, k;
+    nth_lobe(word, g, ch, k);
+    const int64_t c = cs + ch;
+    float S[6];
+    w = C.w[int64_t(k) * C.cap + c];
 #pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      lS[j] = L.lS[gi][j][g];
-      ln[j] = lS[j] * il;
-    }
-    L.cw[gi][g] = lw;
+    for (int j = 0; j < 6; ++j) S[j] = C.S[(int64_t(j) * C.Kc + k) * C.cap + c];
+    own = lobe_pack(w, S);
+    L.clu[gi][g] = own;
+    lobe_norm(own, w, nrm);
+    uint4* row = reinterpret_cast<uint4*>(L.mat[gi][g]);
 #pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      L.cS[gi][j][g] = lS[j];
-      L.nS[gi][j][g] = ln[j];
+    for (int j = 0; j < G / 4; ++j) row[j] = make_uint4(kNoCost, kNoCost, kNoCost, kNoCost);
+  }
+  wave_lds_fence();
+  // the costs of all pairs, each computed once: lane g against the n / 2 lobes after it (cyclic)
+  if (mine) {
+    for (int d = 1; 2 * d <= n; ++d) {
+      const int j = g + d < n ? g + d : g + d - n;
+      float wj, nj[6];
+      lobe_norm(L.clu[gi][j], wj, nj);
+      const uint32_t c = __float_as_uint(ward_cost(w, wj, nrm, nj));
+      L.mat[gi][g][j] = c;
+      L.mat[gi][j][g] = c;
     }
   }
-  uint64_t act = n == 64 ? ~uint64_t(0) : ((uint64_t(1) << n) - 1);
+  wave_lds_fence();
+  bool alive = mine;
   int cl = g;                                      // the cluster that input lobe g belongs to
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  if (n > K) {
-    if constexpr (G <= 8) {
-      // ---- Ward agglomeration, few lobes per voxel (G <= 8): clusters and the upper triangle
-      // of the cost matrix in LDS, row g written by lane g
-      if (mine) {
-        for (int j = g + 1; j < n; ++j) {
-          float b[6];
+  for (int step = n; step > K; --step) {
+    // the least cost of the group, then the first pair (i, j), i < j, that has it: i is the first
+    // lane whose row holds it, j the first column of that row (the matrix is symmetric)
+    uint32_t best = kNoCost;
+    const uint4* row = reinterpret_cast<const uint4*>(L.mat[gi][g]);
 #pragma unroll
-          for (int t = 0; t < 6; ++t) b[t] = L.nS[gi][t][j];
-          L.mat[gi][g][j] = ward_cost(lw, L.cw[gi][j], ln, b);
-        }
-      }
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      // Each lane caches the minimum of its row (least cost, then least column); a merge of
-      // (bi, bj) only invalidates rows whose cached column was bi or bj, and row bi itself.
-      float best = INFINITY;
-      int bjr = G;
-      auto scan_row = [&]() {
-        best = INFINITY;
-        bjr = G;
-        if (mine && ((act >> g) & 1)) {
-          for (int j = g + 1; j < n; ++j) {
-            if (!((act >> j) & 1)) continue;
-            const float c = L.mat[gi][g][j];
-            if (c < best) { best = c; bjr = j; }
-          }
-        }
-      };
-      scan_row();
-      for (int step = n; step > K; --step) {
-        // group argmin of (cost, i); the row minimum already carries the smallest j.  Costs are
-        // non-negative, so their bits order like the values: one 64-bit key (cost, i, j).
-        const uint64_t key = (uint64_t(__float_as_uint(best)) << 32) | (uint64_t(bjr < G ? g : G) << 16) |
-                             uint64_t(bjr);
-        const uint64_t kmin = group_min_u64<G>(key);
-        const int bi = int((kmin >> 16) & 0xffff), bj = int(kmin & 0xffff);
-        if (bj < G && cl == bj) cl = bi;
-        // merge cluster bj into bi
-        if (g == bi && bj < G) {
-          const float nw = L.cw[gi][bi] + L.cw[gi][bj];
-          const float inw = __builtin_amdgcn_rcpf(nw);
-          L.cw[gi][bi] = nw;
-#pragma unroll
-          for (int t = 0; t < 6; ++t) {
-            const float v = L.cS[gi][t][bi] + L.cS[gi][t][bj];
-            L.cS[gi][t][bi] = v;
-            L.nS[gi][t][bi] = v * inw;
-          }
-        }
-        if (bj < G) act &= ~(uint64_t(1) << bj);
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        float cnew = INFINITY;
-        if (bj < G && mine && ((act >> g) & 1) && g != bi) {
-          float a[6], b[6];
-#pragma unroll
-          for (int t = 0; t < 6; ++t) { a[t] = L.nS[gi][t][bi]; b[t] = L.nS[gi][t][g]; }
-          cnew = ward_cost(L.cw[gi][bi], L.cw[gi][g], a, b);
-          if (g < bi) L.mat[gi][g][bi] = cnew; else L.mat[gi][bi][g] = cnew;
-        }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        // refresh the cached row minima
-        if (g == bj) {
-          best = INFINITY;
-          bjr = G;
-        } else if (g == bi || bjr == bi || bjr == bj) {
-          scan_row();
-        } else if (g < bi && mine && ((act >> g) & 1)) {
-          if (cnew < best || (cnew == best && bi < bjr)) { best = cnew; bjr = bi; }
-        }
-      }
-    } else {
-      // ---- Ward agglomeration.  Lane g holds cluster g (weight, sums, normalised sums) in
-      // registers and row g of the symmetric cost matrix in LDS; a dead cluster costs +inf.
-      float cw = lw, cS[6], nS[6];
-#pragma unroll
-      for (int t = 0; t < 6; ++t) {
-        cS[t] = lS[t];
-        nS[t] = ln[t];
-      }
-      // Each lane caches the minimum of its row (least cost, then least column).
-      float best = INFINITY;
-      int bjr = G;
-      if (mine) {
-        for (int j = 0; j < n; ++j) {
-          float c = INFINITY;
-          if (j != g) {
-            float b[6];
-#pragma unroll
-            for (int t = 0; t < 6; ++t) b[t] = L.nS[gi][t][j];
-            c = ward_cost(lw, L.cw[gi][j], ln, b);
-          }
-          L.mat[gi][j][g] = c;
-          if (c < best) {
-            best = c;
-            bjr = j;
-          }
-        }
-      }
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      const int base = lane - g;                  // the group's first lane
-      for (int step = n; step > K; --step) {
-        // group argmin of the cached row minima as one 64-bit key (cost, i, j), i < j: costs
-        // are non-negative, so their bits order like the values, and the least key is the
-        // first pair in (i, j) order among the least costs
-        const int lo = g < bjr ? g : bjr, hi = g < bjr ? bjr : g;
-        const uint64_t key = bjr < G ? (uint64_t(__float_as_uint(best)) << 32) | (uint64_t(lo) << 16) | uint64_t(hi)
-                                     : ~uint64_t(0);
-        const uint64_t kmin = group_min_u64<G>(key);
-        const int bi = int((kmin >> 16) & 0xffff), bj = int(kmin & 0xffff);
-        const bool merge = bj < G;
-        if (merge && cl == bj) cl = bi;
-        // the merged cluster (bi absorbs bj), computed by every lane from the two lanes' registers
-        const int si = base + (merge ? bi : 0), sj = base + (merge ? bj : 0);
-        const float mw = __shfl(cw, si, 64) + __shfl(cw, sj, 64);
-        const float inw = __builtin_amdgcn_rcpf(mw);
-        float mS[6], mn[6];
-#pragma unroll
-        for (int t = 0; t < 6; ++t) {
-          mS[t] = __shfl(cS[t], si, 64) + __shfl(cS[t], sj, 64);
-          mn[t] = mS[t] * inw;
-        }
-        if (merge) {
-          act &= ~(uint64_t(1) << bj);
-          if (g == bi) {
-            cw = mw;
-#pragma unroll
-            for (int t = 0; t < 6; ++t) {
-              cS[t] = mS[t];
-              nS[t] = mn[t];
-            }
-          }
-        }
-        const bool alive = mine && ((act >> g) & 1);
-        float cnew = INFINITY;
-        if (merge && alive && g != bi) {
-          cnew = ward_cost(mw, cw, mn, nS);
-          L.mat[gi][bi][g] = cnew;                // row g, column bi
-          L.mat[gi][g][bi] = cnew;                // row bi, column g
-        }
-        if (merge && mine) L.mat[gi][bj][g] = INFINITY;
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        // the merged row's minimum over the new costs (least cost, then least column)
-        const uint64_t k2 = (uint64_t(__float_as_uint(cnew)) << 32) | uint64_t(g);
-        const uint64_t m2 = group_min_u64<G>(k2);
-        // refresh the cached row minima: only column bi changed (to cnew) and column bj died.
-        // Row bj dies, row bi takes the merged row's minimum; a row whose minimum sat in column bi
-        // keeps it if the new cost is no larger, else (or if it sat in column bj) is rescanned;
-        // any other row compares the new cost with its minimum (ties to the lower column).  All
-        // decided with selects, no branch per case.
-        const bool isj = merge && g == bj;
-        const bool isi = merge && !isj && g == bi;
-        const bool oth = merge && !isj && !isi && alive;
-        const bool onbi = oth && bjr == bi, onbj = oth && !onbi && bjr == bj;
-        const bool keep_bi = onbi && cnew <= best;
-        const bool rescan = (onbi && !(cnew <= best)) || onbj;
-        const bool take_new = oth && !onbi && !onbj && (cnew < best || (cnew == best && bi < bjr));
-        const float mb = __uint_as_float(uint32_t(m2 >> 32));
-        const int mj = mb < INFINITY ? int(m2 & 0xffff) : G;
-        best = isj ? INFINITY : (isi ? mb : ((keep_bi || take_new) ? cnew : best));
-        bjr = isj ? G : (isi ? mj : (take_new ? bi : bjr));
-        if (rescan) {
-          best = INFINITY;
-          bjr = G;
-          if constexpr (G <= 16) {
-            // the whole row, its loads issued together (unrolled over the group width; every
-            // column is in bounds, those at or past n are replaced by +inf)
-            float c[G];
-#pragma unroll
-            for (int j = 0; j < G; ++j) c[j] = L.mat[gi][j][g];
-#pragma unroll
-            for (int j = 0; j < G; ++j) c[j] = j < n ? c[j] : INFINITY;
-#pragma unroll
-            for (int j = 0; j < G; ++j)
-              if (c[j] < best) {
-                best = c[j];
-                bjr = j;
-              }
-          } else {
-            for (int j = 0; j < n; ++j) {
-              const float c = L.mat[gi][j][g];
-              if (c < best) {
-                best = c;
-                bjr = j;
-              }
-            }
-          }
-        }
-      }
-      // the clusters back to LDS for the Lloyd passes and the output
-      if (mine) {
-        L.cw[gi][g] = cw;
-#pragma unroll
-        for (int t = 0; t < 6; ++t) {
-          L.cS[gi][t][g] = cS[t];
-          L.nS[gi][t][g] = nS[t];
-        }
-      }
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int q = 0; q < G / 4; ++q) {
+      const uint4 r = row[q];
+      best = min(best, min(min(r.x, r.y), min(r.z, r.w)));
     }
-    // ---- weighted Lloyd passes over the original lobes.  A pass that moves no lobe to another
-    // cluster leaves every cluster as it is, and so does every later one: the group stops there.
-    bool conv = false;                             // uniform over the group
+    best = alive ? best : kNoCost;
+    const uint32_t least = group_min_u32<G>(best);
+    if (least >= kNoCost) break;                   // no pair of finite cost
+    const int i = __ffsll((unsigned long long)group_bits<G>(__ballot(best == least), gi)) - 1;
+    const uint32_t col = L.mat[gi][i][g];
+    const int j = __ffsll((unsigned long long)group_bits<G>(__ballot(col == least), gi)) - 1;
+    // cluster i absorbs cluster j
+    float wi, wj, Si[6], Sj[6], mn[6];
+    lobe_unpack(L.clu[gi][i], wi, Si);
+    lobe_unpack(L.clu[gi][j], wj, Sj);
+    const float mw = wi + wj;
+    const float inw = __builtin_amdgcn_rcpf(mw);
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+#pragma clang fp contract(off)
+      Si[t] = Si[t] + Sj[t];
+      mn[t] = Si[t] * inw;
+    }
+    wave_lds_fence();
+    if (cl == j) cl = i;
+    if (g == j) alive = false;
+    if (g == i) {
+      w = mw;
+#pragma unroll
+      for (int t = 0; t < 6; ++t) nrm[t] = mn[t];
+      L.clu[gi][i] = lobe_pack(mw, Si);
+      L.mat[gi][i][j] = kNoCost;
+    } else if (alive) {
+      const uint32_t c = __float_as_uint(ward_cost(mw, w, mn, nrm));
+      L.mat[gi][i][g] = c;
+      L.mat[gi][g][i] = c;
+      L.mat[gi][g][j] = kNoCost;
+    }
+    wave_lds_fence();
+  }
+  uint64_t act = group_bits<G>(__ballot(alive), gi);
+  // ---- weighted Lloyd passes over the input lobes.  A pass that moves no lobe to another cluster
+  // leaves every cluster as it is, and so does every later one: the group stops there.
+  if (live) {
+    float lw, ln[6];
+    lobe_norm(own, lw, ln);
+    if (mine) L.lob[gi][g] = own;
     for (int it = 0; it < iters; ++it) {
       int assign = -1;
-      if (mine) {
-        // nearest active centroid (ties to the lowest index), walking the active set
-        float bestd = INFINITY;
-        for (uint64_t m = act; m; m &= m - 1) {
-          const int k = __ffsll((unsigned long long)m) - 1;
-          float b[6];
-#pragma unroll
-          for (int t = 0; t < 6; ++t) b[t] = L.nS[gi][t][k];
-          const float d = lobe_dist_n(ln, b);
-          if (d < bestd) { bestd = d; assign = k; }
-        }
-      }
-      conv = group_bits<G>(__ballot(mine && assign != cl), gi) == 0;
-      if (__ballot(!conv) == 0) break;             // every group of the wave has converged
-      if (conv) continue;
-      cl = assign;
-      if (mine) L.asg[gi][g] = assign;
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      // new cluster sums: one lane per (active cluster, component), adding the members in
-      // lobe order (sequential, so the sums are fixed)
-      const int na = __popcll(act);
-      for (int q = g; q < 7 * na; q += G) {
-        const int r = q / 7, t = q - 7 * r;
-        uint64_t m = act;
-        for (int i = 0; i < r; ++i) m &= m - 1;
-        const int k = __ffsll((unsigned long long)m) - 1;
-        // the members in lobe order (narrow groups: every member's load issued before the sum)
-        float sum = 0.f;
-        if constexpr (G <= 16) {
-          float v[G];
-          bool in[G];
-#pragma unroll
-          for (int mm = 0; mm < G; ++mm) {
-            in[mm] = mm < n && L.asg[gi][mm] == k;
-            v[mm] = in[mm] ? (t == 6 ? L.lw[gi][mm] : L.lS[gi][t][mm]) : 0.f;
-          }
-#pragma unroll
-          for (int mm = 0; mm < G; ++mm)
-            if (in[mm]) sum += v[mm];
-        } else {
-          for (int mm = 0; mm < n; ++mm)
-            if (L.asg[gi][mm] == k) sum += t == 6 ? L.lw[gi][mm] : L.lS[gi][t][mm];
-        }
-        if (t == 6) L.cw[gi][k] = sum;
-        else L.cS[gi][t][k] = sum;
-      }
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      uint64_t nact = 0;
+      // nearest active centroid (ties to the lowest index), walking the active set
+      float bestd = INFINITY;
       for (uint64_t m = act; m; m &= m - 1) {
         const int k = __ffsll((unsigned long long)m) - 1;
-        if (L.cw[gi][k] > 0.f) nact |= uint64_t(1) << k;
+        float wk, nk[6];
+        lobe_norm(L.clu[gi][k], wk, nk);
+        const float d = lobe_dist_n(ln, nk);
+        if (d < bestd) { bestd = d; assign = k; }
       }
-      act = nact;
-      // the new centroids, normalised
-      for (int q = g; q < 6 * na; q += G) {
-        const int r = q / 6, t = q - 6 * r;
-        uint64_t m = nact;
-        for (int i = 0; i < r && m; ++i) m &= m - 1;
-        if (!m) continue;
+      if (group_bits<G>(__ballot(mine && assign != cl), gi) == 0) break;
+      cl = assign;
+      reinterpret_cast<uint8_t*>(L.asg[gi])[g] = uint8_t(mine ? assign : 255);
+      wave_lds_fence();
+      // new cluster sums: one lane per (active cluster, component), adding the members in lobe
+      // order (sequential, so the sums are fixed)
+      const int na = __popcll(act);
+      for (int q = g; q < 7 * na; q += G) {
+        const int r = q / 7, t = q - 7 * r;        // component 0 is the weight
+        uint64_t m = act;
+        for (int x = 0; x < r; ++x) m &= m - 1;
         const int k = __ffsll((unsigned long long)m) - 1;
-        L.nS[gi][t][k] = L.cS[gi][t][k] * __builtin_amdgcn_rcpf(L.cw[gi][k]);
+        const float* v = reinterpret_cast<const float*>(&L.lob[gi][0]) + t;
+        float sum = 0.f;
+        for (int x = 0; x < n; x += 4) {
+          // (x + 3 < G: in bounds; a byte past the lobes matches no cluster)
+          const uint32_t of = L.asg[gi][x >> 2];
+          float u[4];
+#pragma unroll
+          for (int y = 0; y < 4; ++y) u[y] = v[8 * (x + y)];
+#pragma unroll
+          for (int y = 0; y < 4; ++y) sum += int((of >> (8 * y)) & 255u) == k ? u[y] : 0.f;
+        }
+        reinterpret_cast<float*>(&L.clu[gi][k])[t] = sum;
       }
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      wave_lds_fence();
+      uint64_t left = 0;
+      for (uint64_t m = act; m; m &= m - 1) {
+        const int k = __ffsll((unsigned long long)m) - 1;
+        if (L.clu[gi][k].a.x > 0.f) left |= uint64_t(1) << k;
+      }
+      act = left;
     }
-  }
-  // ---- output: active clusters sorted by descending weight (ties keep cluster order)
-  if (live) {
+    // ---- output: active clusters sorted by descending weight (ties keep cluster order)
     const int nl = __popcll(act);
-    if (g < G && ((act >> g) & 1)) {
-      const float wg = L.cw[gi][g];
+    if ((act >> g) & 1) {
+      const LobeQ q = L.clu[gi][g];
       int rank = 0;
-      for (int k = 0; k < n; ++k) {
-        if (!((act >> k) & 1) || k == g) continue;
-        const float wk = L.cw[gi][k];
-        rank += (wk > wg || (wk == wg && k < g)) ? 1 : 0;
+      for (uint64_t m = act; m; m &= m - 1) {
+        const int k = __ffsll((unsigned long long)m) - 1;
+        const float wk = L.clu[gi][k].a.x;
+        rank += (wk > q.a.x || (wk == q.a.x && k < g)) ? 1 : 0;
       }
       if (rank < K) {                             // at most K clusters remain; never write past them
-        out.w[int64_t(rank) * cap + p] = wg;
+        float ow, S[6];
+        lobe_unpack(q, ow, S);
+        out.w[int64_t(rank) * out.cap + p] = ow;
 #pragma unroll
-        for (int t = 0; t < 6; ++t) out.S[(int64_t(t) * K + rank) * cap + p] = L.cS[gi][t][g];
+        for (int t = 0; t < 6; ++t) out.S[(int64_t(t) * K + rank) * out.cap + p] = S[t];
       }
     }
     if (g >= nl && g < K) {
-      out.w[int64_t(g) * cap + p] = 0.f;
+      out.w[int64_t(g) * out.cap + p] = 0.f;
 #pragma unroll
-      for (int t = 0; t < 6; ++t) out.S[(int64_t(t) * K + g) * cap + p] = 0.f;
+      for (int t = 0; t < 6; ++t) out.S[(int64_t(t) * K + g) * out.cap + p] = 0.f;
     }
     if (g == 0) out.nl[p] = uint8_t(nl);
   }
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  wave_lds_fence();
 }
 
-// One level with a fixed group width G (G lanes per parent, 64 / G parents per wave).  With
-// BAND, only the parents that gather more than LO and at most G lobes are taken.
-template <int G, bool BAND, int LO = 0, int SLOTS = 64>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SLOTS <= 32 ? 4 : 3))) k_cluster(const int64_t* __restrict__ pstart, const int64_t* n_par_ptr,
-                                                    const float* __restrict__ cw, const float* __restrict__ cS,
-                                                    const uint8_t* __restrict__ cnl, int Kc, int64_t cap_c, int K,
-                                                    int iters, vx_lobes out) {
-  __shared__ ClusterLds<G> sm[kWaves];
-  ClusterLds<G>& L = sm[threadIdx.x >> 6];
-  const int64_t n_par = *n_par_ptr;
-  constexpr int per_wave = 64 / G;
-  const int64_t w0 = (int64_t(blockIdx.x) * kWaves + (threadIdx.x >> 6)) * per_wave;
-  const int64_t stride = int64_t(gridDim.x) * kWaves * per_wave;
-  for (int64_t base = w0; base < n_par; base += stride)
-    cluster_round<G, BAND, LO, SLOTS>(base + threadIdx.x % 64 / G, base + threadIdx.x % 64 / G < n_par, pstart, cw,
-                                      cS, cnl, Kc, cap_c, K, iters, out, L);
-}
-
-// Parents picked by a count, GB lanes each: a wave counts up to 64 parents' (child, lobe) slots
-// in use (one parent per lane), then serves those whose count lies in (QLO, QHI], 64 / GB at a
-// time.  A wave counts as many parents as spread the level over the grid, at least one round's
-// worth: a small level runs one round per wave, all in parallel.
-// Without BAND the count bounds the lobes (QHI <= GB); with BAND the round takes a parent only
-// when its positive lobes are more than LO and at most GB (the other picks take the rest).
-// When few parents are in the band this pass is mostly the count.  The group width changes no
-// result.
-constexpr int kAnyCount = 1 << 30;
-template <int GB, bool BAND, int LO, int QLO, int QHI, int SLOTS>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(GB <= 16 && SLOTS <= 32 ? 4 : 1))) k_cluster_pick(const int64_t* __restrict__ pstart,
-                                                         const int64_t* n_par_ptr, const float* __restrict__ cw,
-                                                         const float* __restrict__ cS,
-                                                         const uint8_t* __restrict__ cnl, int Kc, int64_t cap_c,
-                                                         int K, int iters, vx_lobes out) {
-  __shared__ ClusterLds<GB> sm[kWaves];
-  ClusterLds<GB>& L = sm[threadIdx.x >> 6];
-  const int lane = lane_id();
-  constexpr int per_r = 64 / GB;                  // parents served per round
-  const int gi = lane / GB;
-  const int64_t n_par = *n_par_ptr;
-  const int64_t waves = int64_t(gridDim.x) * kWaves;
-  int64_t per = (n_par + waves - 1) / waves;      // parents counted per wave (uniform)
-  per = per < per_r ? per_r : (per > 64 ? 64 : per);
-  const int64_t w0 = (int64_t(blockIdx.x) * kWaves + (threadIdx.x >> 6)) * per;
-  const int64_t stride = waves * per;
-  for (int64_t base = w0; base < n_par; base += stride) {
-    int nq = 0;
-    const int64_t p = base + lane;
-    const bool counted = lane < per && p < n_par;
-    if (counted) {
-      const int64_t cs = pstart[p], ce = pstart[p + 1];
-      for (int64_t c = cs; c < ce; ++c) nq += cnl ? (int(cnl[c]) < Kc ? int(cnl[c]) : Kc) : 1;
-    }
-    static_assert(BAND || QHI <= GB, "without the band check the count must bound the lobes");
-    uint64_t m = __ballot(counted && nq > QLO && nq <= QHI);
-    while (m) {
-      int64_t mine = -1;
+// A coarse voxel with at most K lobes keeps them, sorted by descending weight (ties in lobe
+// order): one lane each, so that the K sorted lobes of 64 neighbours leave in whole lines.
+template <int MAXK>
+__device__ __forceinline__ void keep_lobes(int64_t p, int64_t cs, uint32_t word, int n, const ChildLobes& C, int K,
+                                           const vx_lobes& out) {
+  float w[MAXK];
+  int at[MAXK];                                   // child * 16 + lobe
 #pragma unroll
-      for (int k = 0; k < per_r; ++k) {
-        if (m) {
-          if (k == gi) mine = base + (__ffsll((unsigned long long)m) - 1);
-          m &= m - 1;
+  for (int m = 0; m < MAXK; ++m) {
+    w[m] = -1.f;
+    at[m] = 0;
+    if (m < n) {
+      int ch, k;
+      nth_lobe(word, m, ch, k);
+      at[m] = ch * 16 + k;
+      w[m] = C.w[int64_t(k) * C.cap + cs + ch];
+    }
+  }
+  // odd-even transposition, neighbours exchanged only when strictly out of order: stable
+#pragma unroll
+  for (int r = 0; r < MAXK; ++r)
+#pragma unroll
+    for (int m = r & 1; m + 1 < MAXK; m += 2) {
+      const bool sw = w[m + 1] > w[m];
+      const float a = w[m], b = w[m + 1];
+      const int x = at[m], y = at[m + 1];
+      w[m] = sw ? b : a;
+      w[m + 1] = sw ? a : b;
+      at[m] = sw ? y : x;
+      at[m + 1] = sw ? x : y;
+    }
+#pragma unroll
+  for (int s = 0; s < MAXK; ++s) {
+    if (s >= K) break;
+    const bool has = s < n;
+    const int64_t c = cs + (at[s] >> 4);
+    const int k = at[s] & 15;
+    out.w[int64_t(s) * out.cap + p] = has ? w[s] : 0.f;
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+      out.S[(int64_t(t) * K + s) * out.cap + p] = has ? C.S[(int64_t(t) * C.Kc + k) * C.cap + c] : 0.f;
+  }
+  out.nl[p] = uint8_t(n);
+}
+
+// One level.  SLOTS: the most input lobes of a voxel (8: one per child; 32: up to four per child;
+// 64).  A block takes runs of `run` voxels: 256, or on small levels as few as spread the level
+// over three times the blocks that are resident, at least 8 (two rounds of 32 lanes per wave).
+template <int SLOTS>
+__global__ void __launch_bounds__(kBlock) k_cluster(const int64_t* __restrict__ pstart, const int64_t* n_par_ptr,
+                                                    ChildLobes C, int K, int iters, vx_lobes out) {
+  constexpr int kLists = SLOTS <= 8 ? 1 : (SLOTS <= 32 ? 3 : 4);
+  union WaveLds {
+    ClusterLds<8> g8;
+    ClusterLds<SLOTS <= 8 ? 8 : 16> g16;
+    ClusterLds<SLOTS <= 8 ? 8 : 32> g32;
+    ClusterLds<SLOTS <= 32 ? 8 : 64> g64;
+  };
+  __shared__ WaveLds lds[kWaves];
+  __shared__ int64_t first[kBlock];               // first child
+  __shared__ uint32_t words[kBlock];              // lobes per child, a nibble each
+  __shared__ uint8_t list[kLists][kBlock], count[kBlock];
+  __shared__ int32_t len[kLists];
+  const int tid = threadIdx.x, wave = tid >> 6;
+  const int64_t n_par = *n_par_ptr;
+  int64_t run = ((n_par + 3 * 768 - 1) / (3 * 768) + 7) & ~int64_t(7);
+  run = run < 8 ? 8 : (run > kBlock ? kBlock : run);
+  for (int64_t base = int64_t(blockIdx.x) * run; base < n_par; base += int64_t(gridDim.x) * run) {
+    if (tid < kLists) len[tid] = 0;
+    __syncthreads();
+    const int64_t p = base + tid;
+    if (tid < run && p < n_par) {
+      const int64_t cs = pstart[p], ce = pstart[p + 1];
+      uint32_t word = 0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if (cs + i < ce) {
+          int c;
+          if (SLOTS <= 8) c = C.w[cs + i] > 0.f ? 1 : 0;
+          else c = int(C.nl[cs + i]) < C.Kc ? int(C.nl[cs + i]) : C.Kc;
+          word |= uint32_t(c) << (4 * i);
         }
       }
-      // the count includes lobes of zero weight: the round takes a parent only when its positive
-      // lobes fall in the band (a narrower pass took fewer, a wider one takes more)
-      cluster_round<GB, BAND, LO, SLOTS>(mine < 0 ? 0 : mine, mine >= 0, pstart, cw, cS, cnl, Kc, cap_c, K, iters,
-                                         out, L);
+      const uint32_t pairs = (word & 0x0f0f0f0fu) + ((word >> 4) & 0x0f0f0f0fu);
+      const int n = int((pairs * 0x01010101u) >> 24);
+      if (n <= K) {
+        if (K <= 4) keep_lobes<4>(p, cs, word, n, C, K, out);
+        else keep_lobes<8>(p, cs, word, n, C, K, out);
+      } else {
+        first[tid] = cs;
+        words[tid] = word;
+        count[tid] = uint8_t(n);
+        const int l = SLOTS <= 8 ? 0 : (n <= 8 ? 0 : (n <= 16 ? 1 : (n <= 32 ? 2 : kLists - 1)));
+        list[l][atomicAdd(&len[l], 1)] = uint8_t(tid);
+      }
     }
+    __syncthreads();
+#define VX_ROUNDS(G, LIST, FIELD)                                                                        \
+  for (int r = wave * (64 / G); r < len[LIST]; r += kWaves * (64 / G)) {                                \
+    const int e = r + (tid & 63) / G;                                                                   \
+    const bool live = e < len[LIST];                                                                    \
+    const int q = live ? list[LIST][e] : 0;                                                             \
+    cluster_round<G>(base + q, live, live ? first[q] : 0, live ? words[q] : 0, live ? count[q] : 0, C, K, iters, out, \
+                     lds[wave].FIELD);                                                                  \
+  }
+    if constexpr (kLists > 3) { VX_ROUNDS(64, 3, g64) }
+    if constexpr (kLists > 1) {
+      VX_ROUNDS(32, 2, g32)
+      VX_ROUNDS(16, 1, g16)
+    }
+    VX_ROUNDS(8, 0, g8)
+#undef VX_ROUNDS
+    __syncthreads();
   }
 }
 
 void cluster_level(const int64_t* pstart, const int64_t* n_par, const float* cw, const float* cS, const uint8_t* cnl,
-                   int Kc, int64_t cap_c, int K, int iters, const vx_lobes& out, int grid, hipStream_t s,
-                   bool narrow_first) {
+                   int Kc, int64_t cap_c, int K, int iters, const vx_lobes& out, int grid, hipStream_t s) {
   const int need = 8 * Kc;
-  // no more blocks than the level's capacity of parents can use (the upper levels are small)
-  auto blocks = [&](int per_block) {
-    const int64_t b = (out.cap + per_block - 1) / per_block;
-    return int(b < grid ? (b < 1 ? 1 : b) : grid);
-  };
-  // timing names by group width: the first level (one lobe per child) and the levels above
+  // no more blocks than the level's capacity of voxels can use (the upper levels are small)
+  const int64_t most = (out.cap + 7) / 8;
+  const int blocks = int(most < grid ? (most < 1 ? 1 : most) : grid);
+  const ChildLobes C{cw, cS, cnl, Kc, cap_c};
+  // timing names: the first level (one lobe per child) and the levels above
   VX_TIMED(need <= 8 ? "lod_cluster" : "lod_cluster_up", s);
-  if (need <= 8)
-    hipLaunchKernelGGL((k_cluster<8, false, 0, 8>), dim3(blocks(kWaves * 8)), dim3(kBlock), 0, s, pstart, n_par, cw,
-                       cS, cnl, Kc, cap_c, K, iters, out);
-  else if (need <= 16)
-    hipLaunchKernelGGL((k_cluster<16, false, 0, 16>), dim3(blocks(kWaves * 4)), dim3(kBlock), 0, s, pstart, n_par, cw,
-                       cS, cnl, Kc, cap_c, K, iters, out);
-  else {
-    // parents by the lobes they gather: at most 16 positive lobes at four parents per wave (all
-    // parents gathered), 17 to 32 at two and the few above at one (picked after a count).  With
-    // narrow_first (the level above the first, whose children hold few lobes: many parents gather
-    // at most 8) those with at most 8 slots filled go first at eight per wave, then the others
-    // with at most 16 positive lobes at four, each picked after a count.
-    const int pgrid = blocks(kWaves * 64) < (grid / 4 > 64 ? grid / 4 : 64) ? blocks(kWaves * 64)
-                                                                            : (grid / 4 > 64 ? grid / 4 : 64);
-    const int mgrid = blocks(kWaves * 64 / 4);
-#define VX_PICK(GRID, GB, BAND, LO, QLO, QHI, SL)                                                                  \
-  hipLaunchKernelGGL((k_cluster_pick<GB, BAND, LO, QLO, QHI, SL>), dim3(GRID), dim3(kBlock), 0, s, pstart, n_par, cw, \
-                     cS, cnl, Kc, cap_c, K, iters, out)
-    if (need <= 32) {
-      if (narrow_first) {
-        VX_PICK(mgrid, 8, false, 0, -1, 8, 32);
-        VX_PICK(mgrid, 16, true, 0, 8, kAnyCount, 32);
-      } else {
-        hipLaunchKernelGGL((k_cluster<16, true, 0, 32>), dim3(blocks(kWaves * 4)), dim3(kBlock), 0, s, pstart, n_par,
-                           cw, cS, cnl, Kc, cap_c, K, iters, out);
-      }
-      VX_PICK(pgrid, 32, true, 16, 16, kAnyCount, 32);
-    } else {
-      if (narrow_first) {
-        VX_PICK(mgrid, 8, false, 0, -1, 8, 64);
-        VX_PICK(mgrid, 16, true, 0, 8, kAnyCount, 64);
-      } else {
-        hipLaunchKernelGGL((k_cluster<16, true, 0, 64>), dim3(blocks(kWaves * 4)), dim3(kBlock), 0, s, pstart, n_par,
-                           cw, cS, cnl, Kc, cap_c, K, iters, out);
-      }
-      VX_PICK(pgrid, 32, true, 16, 16, kAnyCount, 64);
-      VX_PICK(pgrid, 64, true, 32, 32, kAnyCount, 64);
-    }
-#undef VX_PICK
-  }
+  if (cnl == nullptr) hipLaunchKernelGGL(k_cluster<8>, dim3(blocks), dim3(kBlock), 0, s, pstart, n_par, C, K, iters, out);
+  else if (need <= 32) hipLaunchKernelGGL(k_cluster<32>, dim3(blocks), dim3(kBlock), 0, s, pstart, n_par, C, K, iters, out);
+  else hipLaunchKernelGGL(k_cluster<64>, dim3(blocks), dim3(kBlock), 0, s, pstart, n_par, C, K, iters, out);
 }
 
 }  // namespace vx

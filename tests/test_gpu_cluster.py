@@ -71,6 +71,30 @@ def test_cluster_on_given_leaf(vx, K, families):
         say(L, rep)
 
 
+@pytest.mark.parametrize("K", [2, 3, 5, 7, 8])
+def test_cluster_every_group_width(vx, K):
+    """A dense leaf (eight children everywhere), a tenth of its weights zero: voxels gather 0 to 8
+    lobes at level 1 and up to 8 K above, so that every group width is used, and kept, empty and
+    merged voxels stand side by side.  The same FP32 leaf goes to the oracle."""
+    log2_res = 4
+    keys, cnt, w, S = _random_leaf(400 + K, log2_res, 16 ** 3, 6)
+    gone = np.random.default_rng(K).random(len(w)) < 0.1
+    gone[:64] = True                               # whole empty voxels up to level 2
+    gone[64:72] = [True] * 7 + [False]             # a single lobe
+    w[gone] = 0.0
+    S[gone] = 0.0
+    say(f"case: dense leaf, 16^3, K={K}")
+    grid = synth.Grid((0.0, 0.0, 0.0), 16.0, log2_res)
+    leaf = _leaf_to_device(vx, keys, cnt, w, S, log2_res)
+    _, lobes = vx.build_lod(grid, leaf, log2_res + 1, K=K, iters=2, return_lobes=True)
+    ref = oracle.Voxels(keys, cnt, w.astype(np.float64), S.astype(np.float64), int(cnt.sum()))
+    lod = oracle.build_lod(ref, log2_res + 1)
+    olobes = oracle.cluster_pyramid(lod, K, 2)
+    for L in range(1, log2_res + 1):
+        rep = compare_lobes(lobes[L - 1].numpy(), olobes[L], lod[L].w, lod[L].S, K, what=f"dense K{K} L{L}")
+        say(L, rep)
+
+
 def test_cluster_brushed_metal_window(vx):
     wl = synth.brushed_metal(window=128)
     say("case: brushed metal 128x128 window, 4096^3, 13 levels, K=4")
