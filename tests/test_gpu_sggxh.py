@@ -108,6 +108,39 @@ def test_given_leaf_extreme_caps(vx, K):
     _stepwise(vx, grid, leaf, lodp, K, 300, f"given K{K}")
 
 
+@pytest.mark.parametrize("K,N", [(2, 1), (3, 65), (4, 700), (5, 65536)])
+def test_given_leaf_lobe_shapes(vx, K, N):
+    """Every shape a lobe can take (flat, needle, round, not positive, huge and tiny) at sample
+    counts from one to the largest: the decisions near a bin's edge or the acceptance bound are
+    those of the FP64 definition."""
+    import torch
+    rng = np.random.default_rng(70 + K)
+    log2_res, n = 3, 512 if N < 10000 else 72
+    keys = np.arange(n, dtype=np.uint64)
+    w = rng.uniform(0.1, 2.0, n).astype(np.float32)
+    t = rng.normal(size=(n, 3))
+    t /= np.linalg.norm(t, axis=1, keepdims=True)
+    t[::5] = np.eye(3)[rng.integers(0, 3, len(t[::5]))]
+    nn = np.stack([t[:, 0] ** 2, t[:, 1] ** 2, t[:, 2] ** 2, t[:, 0] * t[:, 1], t[:, 0] * t[:, 2], t[:, 1] * t[:, 2]], 1)
+    eye = np.array([1.0, 1.0, 1.0, 0.0, 0.0, 0.0])
+    kind = rng.integers(0, 4, n)[:, None]
+    M = np.where(kind == 0, nn, np.where(kind == 1, eye - nn, np.where(kind == 2, eye / 3 + 0.01 * nn, eye - 1.1 * nn)))
+    w[::7] *= np.float32(1e12)
+    w[3::7] *= np.float32(1e-12)
+    S = (w[:, None] * M).astype(np.float32)
+    leaf = vx.alloc_voxels(n, log2_res, "cuda", False)
+    leaf.keys.copy_(torch.as_tensor(keys.astype(np.uint32).view(np.int32)))
+    leaf.count.copy_(torch.ones(n, dtype=torch.int32))
+    leaf.w.copy_(torch.as_tensor(w))
+    leaf.S.copy_(torch.as_tensor(np.ascontiguousarray(S.T)))
+    leaf.n = n
+    grid = synth.Grid((0.0, 0.0, 0.0), 8.0, log2_res)
+    lodp = vx.LodPlan(grid, leaf, torch.tensor([n], dtype=torch.int64, device="cuda"), 3).run()
+    lodp.check()
+    say(f"case: SGGX-H, lobe shapes, {n} voxels, 8^3, K = {K}, {N} samples")
+    _stepwise(vx, grid, leaf, lodp, K, N, f"shapes K{K} N{N}")
+
+
 def test_errors(vx):
     import torch
     wl = synth.icosphere(subdiv=2)
