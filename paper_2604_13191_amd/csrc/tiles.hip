@@ -343,25 +343,27 @@ struct UnitTotal {
 // the unit kernel: test, weigh, group by voxel and sum in LDS
 // ---------------------------------------------------------------------------------------------
 struct UnitLds {
-  uint32_t* start;    // [budget]   after the batches: the voxels' keys and range ends (2 x u16)
   uint16_t* key;      // [budget]   unit-local Morton code of each pair
-  uint16_t* idx;      // [budget]   grouped order -> pair
-  float* w;           // [budget]   (before the weights: the queue of undecided candidates)
-  uint32_t* prim;     // [budget]  
+  float* w;           // [budget]
+  uint32_t* prim;     // [budget]
   uint16_t* ckey;     // [budget]   per candidate of the batch: kTouch | its unit-local key,
-                      // kUndecided, or 0 for a miss (after the batches: each pair's arrival
-                      // slot among its voxel's pairs)
+                      // kUndecided, or 0 for a miss
+  uint16_t* queue;    // [budget]   the batch's undecided candidates (fibers: in the space of w, whose
+                      // weights come after the batches; triangles: of idx)
+  uint16_t* idx;      // [budget]   triangles: the slots of a batch's new pairs; after the batches:
+                      // grouped order -> pair (fibers: in the space of ckey)
   uint64_t* sbm;      // [64] batch: bit c set where a slot's first candidate is c
   uint32_t* spre;     // [64] slot starts below each word
-  int32_t* bprim;     // [kBlock] the current record batch
-  int32_t* blo;       // [3][kBlock]
-  int32_t* bn;        // [3][kBlock]
-  int32_t* boff;      // [kBlock] candidate offsets within the batch
   int32_t* brec;      // [kBlock][9] the slot's primitive vertices (record words 0..8; after
                       // the batches: the per-key counters, then starts)
-  int32_t* bpatch;    // [kBlock] the slot's patch (batched)
+  // the current record batch; after the batches its space holds the voxels' keys
   double* binv;       // [kBlock] fibers: the slot's 1 / |B - A|^2 (lattice units); triangles:
-                      // twice the slot's area (voxel^2)
+                      // tri_area_under's factor from projected to true area
+  int32_t* bprim;     // [kBlock]
+  uint32_t* bbox;     // [kBlock] the slot's candidate box in the unit (pack_slot_box)
+  int32_t* boff;      // [kBlock] candidate offsets within the batch
+  int32_t* bpatch;    // [kBlock] the slot's patch (batched fibers); triangles: tri_area_under's `how`
+  uint16_t* vkey;     // [budget]
   int32_t* tmp32;     // [kWaves + 1]
   int32_t* misc;      // [8]
 };
@@ -380,19 +382,29 @@ static_assert(kBlock * 16 == kUnitKeys, "each thread owns 16 keys in the scan of
 constexpr uint16_t kTouch = 0x8000, kUndecided = 0x4000;
 static_assert(kUnitKeys <= kUndecided, "keys fit below the flags");
 
-// LDS of a unit with a budget of CAND candidates; the budgets and the unit kernel's waves per
-// SIMD that the LDS then allows (160 KB per CU: 2 blocks at 3072 and 2048, 3 at 1536, 4 at 1024)
-template <int CAND>
+// LDS of a unit with a budget of CAND candidates, and the unit kernel's waves per SIMD that the LDS
+// then allows (160 KB per CU: 4 blocks at 1024 and 1536; above, 3, but 2 for triangles at 3072).
+// Much of a unit's time is latency (dependent loads, barriers, LDS), so another block per CU is worth
+// more than the registers it takes.  With packed boxes, shared space and the arrival slots in registers
+// the brushed surface's units (1536) went from 49 to 38 KB and 6.43 to 5.75 ms, a fabric's (3072) from
+// 77 to 53 KB and 0.68 to 0.50 ms.
+template <int KIND, int CAND>
 constexpr size_t unit_lds_bytes() {
-  return size_t(CAND) * (4 + 2 + 2 + 4 + 4 + 2) + 64 * 8 + 64 * 4 + kBlock * 4 * (8 + 9 + 1) + kBlock * 8 +
-         (kWaves + 1) * 4 + 8 * 4 + 256;
+  constexpr size_t batch = kBlock * (8 + 4 * 4) > CAND * 2 ? kBlock * (8 + 4 * 4) : CAND * 2;
+  return size_t(CAND) * (2 + 4 + 4 + 2 + (KIND == 0 ? 2 : 0)) + 64 * 8 + 64 * 4 + kBlock * 9 * 4 + batch +
+         (kWaves + 2) * 4 + 8 * 4;
 }
-constexpr int unit_waves(int cand) { return cand <= 1024 ? 4 : (cand <= 1536 ? 3 : 2); }
-static_assert(2 * unit_lds_bytes<3072>() <= 160 * 1024, "two units per CU at the largest budget");
-static_assert(3 * unit_lds_bytes<1536>() <= 160 * 1024, "three units per CU at 1536");
-static_assert(4 * unit_lds_bytes<1024>() <= 160 * 1024, "four units per CU at 1024");
+template <int KIND>
+constexpr int unit_waves(int cand) {
+  return cand <= 1536 ? 4 : (KIND == 1 || cand <= 2048 ? 3 : 2);
+}
+static_assert(2 * unit_lds_bytes<0, 3072>() <= 160 * 1024, "two units per CU");
+static_assert(3 * unit_lds_bytes<0, 2048>() <= 160 * 1024, "three units per CU");
+static_assert(4 * unit_lds_bytes<0, 1536>() <= 160 * 1024, "four units per CU");
+static_assert(3 * unit_lds_bytes<1, 3072>() <= 160 * 1024, "three units per CU");
+static_assert(4 * unit_lds_bytes<1, 1536>() <= 160 * 1024, "four units per CU");
 
-template <int CAND>
+template <int KIND, int CAND>
 __device__ __forceinline__ UnitLds carve_unit_lds(char* base) {
   UnitLds L;
   size_t off = 0;
@@ -402,23 +414,31 @@ __device__ __forceinline__ UnitLds carve_unit_lds(char* base) {
     return p;
   };
   L.sbm = reinterpret_cast<uint64_t*>(take(64 * 8));
-  L.start = reinterpret_cast<uint32_t*>(take(CAND * 4));
+  char* batch = take(kBlock * (8 + 4 * 4) > CAND * 2 ? kBlock * (8 + 4 * 4) : CAND * 2);
+  L.binv = reinterpret_cast<double*>(batch);
+  L.bprim = reinterpret_cast<int32_t*>(batch + kBlock * 8);
+  L.bbox = reinterpret_cast<uint32_t*>(batch + kBlock * 12);
+  L.boff = reinterpret_cast<int32_t*>(batch + kBlock * 16);
+  L.bpatch = reinterpret_cast<int32_t*>(batch + kBlock * 20);
+  L.vkey = reinterpret_cast<uint16_t*>(batch);
   L.w = reinterpret_cast<float*>(take(CAND * 4));
   L.prim = reinterpret_cast<uint32_t*>(take(CAND * 4));
   L.key = reinterpret_cast<uint16_t*>(take(CAND * 2));
-  L.idx = reinterpret_cast<uint16_t*>(take(CAND * 2));
   L.ckey = reinterpret_cast<uint16_t*>(take(CAND * 2));
+  L.idx = KIND == 0 ? reinterpret_cast<uint16_t*>(take(CAND * 2)) : L.ckey;
+  L.queue = KIND == 0 ? L.idx : reinterpret_cast<uint16_t*>(L.w);
   L.spre = reinterpret_cast<uint32_t*>(take(64 * 4));
-  L.bprim = reinterpret_cast<int32_t*>(take(kBlock * 4));
-  L.blo = reinterpret_cast<int32_t*>(take(3 * kBlock * 4));
-  L.bn = reinterpret_cast<int32_t*>(take(3 * kBlock * 4));
-  L.boff = reinterpret_cast<int32_t*>(take(kBlock * 4));
   L.brec = reinterpret_cast<int32_t*>(take(kBlock * 9 * 4));
-  L.bpatch = reinterpret_cast<int32_t*>(take(kBlock * 4));
-  L.binv = reinterpret_cast<double*>(take(kBlock * 8));
   L.tmp32 = reinterpret_cast<int32_t*>(take((kWaves + 1) * 4));
   L.misc = reinterpret_cast<int32_t*>(take(8 * 4));
   return L;
+}
+
+// A slot's candidate box in the unit: first voxel from the unit's (4 bits per axis), extents less
+// one along x and y (units span at most 16 voxels per axis)
+__device__ __forceinline__ uint32_t pack_slot_box(const int32_t o[3], const int32_t lo[3], const int32_t n[3]) {
+  return uint32_t(lo[0] - o[0]) | (uint32_t(lo[1] - o[1]) << 4) | (uint32_t(lo[2] - o[2]) << 8) |
+         (uint32_t(n[0] - 1) << 12) | (uint32_t(n[1] - 1) << 16);
 }
 
 // Load records [j0, j0 + kBlock) of the tile clipped to the unit box, keeping those with
@@ -427,15 +447,15 @@ __device__ __forceinline__ UnitLds carve_unit_lds(char* base) {
 template <int KIND>
 __device__ __forceinline__ int32_t load_batch(const UnitLds& S, const int32_t* __restrict__ rec,
                                               const uint32_t* __restrict__ rprim, const float4* __restrict__ dirs,
-                                              int64_t j0, int64_t e,
+                                              int64_t j0, int64_t e, int Sb,
                                               const int32_t o[3], const int32_t sz[3], int& nslot) {
   const int64_t j = j0 + threadIdx.x;
   int32_t c = 0, lo[3], n[3];
   uint32_t p = 0;
-  // the whole record (and the triangle's doubled area) in registers at once: one round of loads
-  // after the primitive id, none after the scan below
+  // the whole record (and the triangle's normal and doubled area) in registers at once: one round
+  // of loads after the primitive id, none after the scan below
   int32_t r[kRec];
-  float a2 = 0.f;
+  float4 dir = make_float4(0.f, 0.f, 0.f, 0.f);
   if (threadIdx.x < 64) S.sbm[threadIdx.x] = 0;
   if (j < e) {
     p = rprim[j];
@@ -448,7 +468,7 @@ __device__ __forceinline__ int32_t load_batch(const UnitLds& S, const int32_t* _
       r[4 * k + 2] = v.z;
       r[4 * k + 3] = v.w;
     }
-    if (KIND == 0) a2 = dirs[p].w;
+    if (KIND == 0) dir = dirs[p];
     c = int32_t(clip_box(r, o, sz, lo, n));
   }
   // candidates (below 2^21 per batch) and kept slots (bits 21 and up) in one scan
@@ -459,16 +479,19 @@ __device__ __forceinline__ int32_t load_batch(const UnitLds& S, const int32_t* _
     const int32_t off = ex & ((1 << 21) - 1);
     S.bprim[q] = int32_t(p);
     S.boff[q] = off;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      S.blo[a * kBlock + q] = lo[a];
-      S.bn[a * kBlock + q] = n[a];
-    }
+    S.bbox[q] = pack_slot_box(o, lo, n);
 #pragma unroll
     for (int k = 0; k < 9; ++k) S.brec[q * 9 + k] = r[k];
-    S.bpatch[q] = r[15];
-    if (KIND == 1) S.binv[q] = cap_inv_len2(r);
-    else S.binv[q] = double(a2);
+    if (KIND == 1) {
+      S.bpatch[q] = r[15];
+      S.binv[q] = cap_inv_len2(r);
+    } else {
+      uint32_t how;
+      double scale;
+      tri_area_setup(r, dir, Sb, how, scale);
+      S.bpatch[q] = int32_t(how);
+      S.binv[q] = scale;
+    }
     atomicOr(reinterpret_cast<unsigned long long*>(&S.sbm[off >> 6]), 1ull << (off & 63));
   }
   nslot = tot >> 21;
@@ -485,13 +508,14 @@ __device__ __forceinline__ int32_t load_batch(const UnitLds& S, const int32_t* _
 // voxel of candidate li (x fastest) of the record in batch slot `slot`.  li < 16^3 and extents
 // <= 16: the quotients by float reciprocal are exact (the rounding error, below 1e-3, stays
 // under the 1/32 margin of (li + 1/2) / n to the next integer)
-__device__ __forceinline__ void slot_voxel(const UnitLds& S, int slot, int32_t li, int64_t v[3]) {
-  const int32_t nx = S.bn[slot], ny = S.bn[kBlock + slot];
+__device__ __forceinline__ void slot_voxel(const UnitLds& S, const int32_t o[3], int slot, int32_t li, int32_t v[3]) {
+  const uint32_t box = S.bbox[slot];
+  const int32_t nx = int32_t((box >> 12) & 15u) + 1, ny = int32_t((box >> 16) & 15u) + 1;
   const int32_t t = int32_t((float(li) + 0.5f) * __builtin_amdgcn_rcpf(float(nx)));
   const int32_t iz = int32_t((float(t) + 0.5f) * __builtin_amdgcn_rcpf(float(ny)));
-  v[0] = S.blo[slot] + (li - t * nx);
-  v[1] = S.blo[kBlock + slot] + (t - iz * ny);
-  v[2] = S.blo[2 * kBlock + slot] + iz;
+  v[0] = o[0] + int32_t(box & 15u) + (li - t * nx);
+  v[1] = o[1] + int32_t((box >> 4) & 15u) + (t - iz * ny);
+  v[2] = o[2] + int32_t((box >> 8) & 15u) + iz;
 }
 
 // candidate c (< 4096) of the batch -> its record slot: the slot starts at or below c, less one
@@ -500,24 +524,54 @@ __device__ __forceinline__ int find_slot(const UnitLds& S, int32_t c) {
   return int(S.spre[wd] + uint32_t(__popcll(S.sbm[wd] & ((2ull << (c & 63)) - 1)))) - 1;
 }
 
-template <int KIND>
-__device__ __forceinline__ bool unit_test(const int32_t* r, const int64_t v[3], const LatQ& Lp) {
-  if (KIND == 0) return tri_touch(r, v, Lp.s, Lp.Sb);
-  return cap_touch(r, v, Lp.s, Lp.Sb, Lp.rho);
+// A voxel's Morton code within its aligned 16^3 cell (12 bits) and back: units and tiles lie in one
+// such cell, so differences of these codes are differences of the whole keys.
+__device__ __forceinline__ uint32_t spread4(uint32_t x) {
+  x = (x | (x << 4)) & 0x0c3u;
+  return (x | (x << 2)) & 0x249u;
+}
+__device__ __forceinline__ uint32_t cell_code(const int32_t v[3]) {
+  return spread4(uint32_t(v[0]) & 15u) | (spread4(uint32_t(v[1]) & 15u) << 1) | (spread4(uint32_t(v[2]) & 15u) << 2);
+}
+__device__ __forceinline__ int32_t compact4(uint32_t x) {
+  x &= 0x249u;
+  x = (x | (x >> 2)) & 0x0c3u;
+  return int32_t((x | (x >> 4)) & 15u);
+}
+__device__ __forceinline__ void cell_voxel(const int32_t o[3], uint32_t code, int32_t v[3]) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) v[a] = (o[a] & ~15) | compact4(code >> a);
 }
 
-template <int KIND>
-__device__ __forceinline__ float unit_weight(const int32_t* r, const int64_t v[3], const LatQ& Lp, float len) {
-  if (KIND == 0) return tri_area(r, v, Lp.Sb, len);
-  return seg_length(r, v, Lp.Sb, len);
+__device__ __forceinline__ float fib_weight(const int32_t* r, const int32_t v[3], int Sb, float len) {
+  const int64_t w[3] = {v[0], v[1], v[2]};
+  return seg_length(r, w, Sb, len);
 }
-// the same, out of line: the rare streaming path keeps no second copy of the weight code
-template <int KIND>
-__device__ __attribute__((noinline)) float unit_weight_call(const int32_t* r, int64_t v0, int64_t v1, int64_t v2,
-                                                            int Sb, float len) {
-  const int64_t v[3] = {v0, v1, v2};
-  if (KIND == 0) return tri_area(r, v, Sb, len);
-  return seg_length(r, v, Sb, len);
+// out of line: the rare streaming path keeps no second copy of the weight code
+__device__ __attribute__((noinline)) float fib_weight_call(const int32_t* r, int32_t v0, int32_t v1, int32_t v2,
+                                                           int Sb, float len) {
+  const int32_t v[3] = {v0, v1, v2};
+  return fib_weight(r, v, Sb, len);
+}
+__device__ __attribute__((noinline)) float tri_weight_call(const int32_t* r, int32_t v0, int32_t v1, int32_t v2,
+                                                           int Sb, uint32_t how, double scale) {
+  const int32_t v[3] = {v0, v1, v2};
+  return tri_area_under(r, v, Sb, how, scale);
+}
+
+// does a vertex of the triangle lie in the closed box?  Decides about half the candidates of
+// voxel-sized triangles (a box that holds a vertex is touched) with integer compares
+__device__ __forceinline__ bool tri_vertex_in(const int32_t* r, const int32_t v[3], int Sb) {
+  const uint32_t s = 1u << Sb;
+  bool any = false;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    bool in = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) in = in & (uint32_t(r[3 * i + a] - (v[a] << Sb)) <= s);
+    any = any | in;
+  }
+  return any;
 }
 
 // Staging of a unit's voxels (SoA, capacity cap); units claim contiguous ranges in any order.
@@ -544,8 +598,11 @@ __device__ __forceinline__ void write_voxel(const Stage& st, int64_t i, uint64_t
   st.S[5 * st.cap + i] = m.yz;
 }
 
+// Bound by VALU issue (three quarters of the cycles) and the latencies above.  The whole brushed
+// surface (149 M pairs): 7.95 -> 5.75 ms with the area by integration (2.2 ms of it; 3.7 before), unit
+// codes spread over 4 bits instead of 21, and half the candidates decided by a vertex in the box.
 template <int KIND, int CAND>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(unit_waves(CAND)))) k_unit(const int32_t* __restrict__ rec, const float4* __restrict__ dirs,
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(unit_waves<KIND>(CAND)))) k_unit(const int32_t* __restrict__ rec, const float4* __restrict__ dirs,
                                                  const uint32_t* __restrict__ rprim,
                                                  const int64_t* __restrict__ tstart, const Unit* __restrict__ units,
                                                  const int64_t* __restrict__ ctl, Lat L, const Lat* __restrict__ lats,
@@ -555,7 +612,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
   extern __shared__ double lds_dyn[];
   static_assert(CAND <= 0xffff, "pair positions are 16-bit");
   static_assert(CAND % (kWaves * 64) == 0, "each wave's queue holds all of its candidates");
-  const UnitLds S = carve_unit_lds<CAND>(reinterpret_cast<char*>(lds_dyn));
+  const UnitLds S = carve_unit_lds<KIND, CAND>(reinterpret_cast<char*>(lds_dyn));
   const int64_t n_units = ctl[CTL_N_UNITS];
   const int tid = threadIdx.x;
   for (int64_t u = blockIdx.x; u < n_units; u += gridDim.x) {
@@ -564,29 +621,36 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
     int32_t usz[3];
     unit_box(U.lev, U.ncell, usz);
     const uint64_t m0 = morton3(uint32_t(U.o[0]), uint32_t(U.o[1]), uint32_t(U.o[2]));   // the unit's first key
+    const uint32_t c0 = uint32_t(m0) & 4095u;                                              // its code in the cell
     const bool stream = U.cand > CAND;          // a single voxel holding too many candidates
     int32_t np = 0;                                   // pairs so far (uniform)
     Moment acc{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // streaming sums (thread 0)
     uint32_t acc_n = 0;
     for (int64_t j0 = s; j0 < e; j0 += kBlock) {
       int nb;
-      const int32_t cb = load_batch<KIND>(S, rec, rprim, dirs, j0, e, U.o, usz, nb);
+      const int32_t cb = load_batch<KIND>(S, rec, rprim, dirs, j0, e, L.Sb, U.o, usz, nb);
       (void)nb;
       if (stream) {
-        for (int32_t c0 = 0; c0 < cb; c0 += kBlock) {
-          const int32_t c = c0 + tid;
+        for (int32_t b0 = 0; b0 < cb; b0 += kBlock) {
+          const int32_t c = b0 + tid;
           bool hit = false;
           float wgt = 0.f;
           uint32_t p = 0;
           if (c < cb) {
             const int slot = find_slot(S, c);
-            int64_t v[3];
-            slot_voxel(S, slot, c - S.boff[slot], v);
+            int32_t v[3];
+            slot_voxel(S, U.o, slot, c - S.boff[slot], v);
+            const int64_t vl[3] = {v[0], v[1], v[2]};
             p = uint32_t(S.bprim[slot]);
             const int32_t* r = S.brec + slot * 9;
-            const LatQ Lp = lat_q(lats, S.bpatch[slot], L);
-            hit = unit_test<KIND>(r, v, Lp);
-            if (hit) wgt = unit_weight_call<KIND>(r, v[0], v[1], v[2], Lp.Sb, dirs[p].w);
+            if (KIND == 0) {
+              hit = tri_touch(r, vl, L.s, L.Sb);
+              if (hit) wgt = tri_weight_call(r, v[0], v[1], v[2], L.Sb, uint32_t(S.bpatch[slot]), S.binv[slot]);
+            } else {
+              const LatQ Lp = lat_q(lats, S.bpatch[slot], L);
+              hit = cap_touch(r, vl, Lp.s, Lp.Sb, Lp.rho);
+              if (hit) wgt = fib_weight_call(r, v[0], v[1], v[2], Lp.Sb, dirs[p].w);
+            }
           }
           int32_t tot;
           const int32_t pos = block_exclusive_scan(int32_t(hit), S.tmp32, tot);
@@ -606,48 +670,55 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
         continue;
       }
       // Test in two rounds so that lanes stay busy: a cheap filter decides most candidates and
-      // queues the rest (fibers: the centre-ball filter), then the queue gets the full test.
+      // queues the rest (fibers: the centre-ball filter; triangles: a vertex in the box), then the
+      // queue gets the full test.
       // Each wave works on its own candidates and drains its own queue (a quarter of the queue
       // space: a wave holds at most a quarter of a unit's candidates); every candidate records
       // its outcome in place, and the touching ones are then compacted in candidate order,
       // which is primitive order.
       const int wv = tid >> 6, lane = tid & 63;
       const uint64_t lt = (uint64_t(1) << lane) - 1;
-      uint32_t* wq = reinterpret_cast<uint32_t*>(S.w) + wv * (CAND / kWaves);
+      uint16_t* wq = S.queue + wv * (CAND / kWaves);
       int32_t nq = 0;                                  // this wave's queue (uniform)
-      for (int32_t c0 = wv * 64; c0 < cb; c0 += kBlock) {
-        const int32_t c = c0 + lane;
+      for (int32_t b0 = wv * 64; b0 < cb; b0 += kBlock) {
+        const int32_t c = b0 + lane;
         int res = 0;                                   // 0 miss, 1 touch, 2 undecided
         if (c < cb) {
           const int slot = find_slot(S, c);
-          int64_t v[3];
-          slot_voxel(S, slot, c - S.boff[slot], v);
+          int32_t v[3];
+          slot_voxel(S, U.o, slot, c - S.boff[slot], v);
           const int32_t* r = S.brec + slot * 9;
-          const LatQ Lp = lat_q(lats, S.bpatch[slot], L);
           if (KIND == 0) {
-            res = tri_touch(r, v, Lp.s, Lp.Sb) ? 1 : 0;
+            res = tri_vertex_in(r, v, L.Sb) ? 1 : 2;
           } else {
-            const int b = cap_ball(r, v, Lp.s, Lp.Sb, Lp.rho, S.binv[slot]);
+            const LatQ Lp = lat_q(lats, S.bpatch[slot], L);
+            const int64_t vl[3] = {v[0], v[1], v[2]};
+            const int b = cap_ball(r, vl, Lp.s, Lp.Sb, Lp.rho, S.binv[slot]);
             res = b < 0 ? 2 : b;
           }
-          S.ckey[c] = res == 1 ? uint16_t(kTouch | (morton3(uint32_t(v[0]), uint32_t(v[1]), uint32_t(v[2])) - m0))
-                               : (res == 2 ? kUndecided : uint16_t(0));
+          S.ckey[c] = res == 1 ? uint16_t(kTouch | (cell_code(v) - c0)) : (res == 2 ? kUndecided : uint16_t(0));
         }
         const uint64_t mb = __ballot(res == 2);
-        if (res == 2) wq[nq + int32_t(__popcll(mb & lt))] = uint32_t(c);
+        if (res == 2) wq[nq + int32_t(__popcll(mb & lt))] = uint16_t(c);
         nq += int32_t(__popcll(mb));
       }
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      for (int32_t q = lane; KIND == 1 && q < nq; q += 64) {
+      for (int32_t q = lane; q < nq; q += 64) {
         const int32_t c = int32_t(wq[q]);
         const int slot = find_slot(S, c);
-        int64_t v[3];
-        slot_voxel(S, slot, c - S.boff[slot], v);
+        int32_t v[3];
+        slot_voxel(S, U.o, slot, c - S.boff[slot], v);
+        const int64_t vl[3] = {v[0], v[1], v[2]};
         const int32_t* r = S.brec + slot * 9;
-        const LatQ Lp = lat_q(lats, S.bpatch[slot], L);
-        const bool hit = cap_bracket(r, v, Lp.s, Lp.Sb, Lp.rho);
-        S.ckey[c] = hit ? uint16_t(kTouch | (morton3(uint32_t(v[0]), uint32_t(v[1]), uint32_t(v[2])) - m0)) : uint16_t(0);
+        bool hit;
+        if (KIND == 0) {
+          hit = tri_touch(r, vl, L.s, L.Sb);
+        } else {
+          const LatQ Lp = lat_q(lats, S.bpatch[slot], L);
+          hit = cap_bracket(r, vl, Lp.s, Lp.Sb, Lp.rho);
+        }
+        S.ckey[c] = hit ? uint16_t(kTouch | (cell_code(v) - c0)) : uint16_t(0);
       }
       __syncthreads();
       // ordered compaction: wave w takes candidates [w span, (w + 1) span)
@@ -655,8 +726,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
         const int32_t span = ((cb + kWaves * 64 - 1) / (kWaves * 64)) * 64;
         const int32_t w0 = wv * span, w1 = w0 + span < cb ? w0 + span : cb;
         int32_t cnt = 0;
-        for (int32_t c0 = w0; c0 < w1; c0 += 64) {
-          const int32_t c = c0 + lane;
+        for (int32_t b0 = w0; b0 < w1; b0 += 64) {
+          const int32_t c = b0 + lane;
           cnt += int32_t(__popcll(__ballot(c < w1 && (S.ckey[c] & kTouch) != 0)));
         }
         if (lane == 0) S.tmp32[wv] = cnt;
@@ -666,8 +737,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
           if (i < wv) base += S.tmp32[i];
           tot += S.tmp32[i];
         }
-        for (int32_t c0 = w0; c0 < w1; c0 += 64) {
-          const int32_t c = c0 + lane;
+        for (int32_t b0 = w0; b0 < w1; b0 += 64) {
+          const int32_t c = b0 + lane;
           const bool hit = c < w1 && (S.ckey[c] & kTouch) != 0;
           const uint64_t mh = __ballot(hit);
           if (hit) {
@@ -689,10 +760,9 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
           const int32_t q1 = np + tot < CAND ? np + tot : CAND;
           for (int32_t q = np + tid; q < q1; q += kBlock) {
             const int sl = S.idx[q];
-            const uint64_t m = m0 + S.key[q];
-            const int64_t v[3] = {int64_t(compact3(m)), int64_t(compact3(m >> 1)), int64_t(compact3(m >> 2))};
-            const LatQ Lp = lat_q(lats, S.bpatch[sl], L);
-            S.w[q] = unit_weight<KIND>(S.brec + sl * 9, v, Lp, float(S.binv[sl]));
+            int32_t v[3];
+            cell_voxel(U.o, c0 + S.key[q], v);
+            S.w[q] = tri_area_under(S.brec + sl * 9, v, L.Sb, uint32_t(S.bpatch[sl]), S.binv[sl]);
           }
         }
         np += tot;
@@ -719,26 +789,31 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
     }
     const int32_t npairs = np < CAND ? np : CAND;
     // Group the pairs by voxel with one counter per key of the unit's range (at most 4096 keys;
-    // 16-bit counts packed two to a word, in the record batch's space, dead now); the fibers'
-    // weights are computed in the same pass.  Each pair keeps its arrival slot among its voxel's
-    // pairs.
+    // 16-bit counts packed two to a word, in the record batch's space, dead now).  Each pair's
+    // arrival slot among its voxel's pairs stays in its thread's registers until it is placed.
     uint32_t* kcw = reinterpret_cast<uint32_t*>(S.brec);                 // [2048] packed counts
     uint16_t* kst = reinterpret_cast<uint16_t*>(S.brec);                 // [4096] then starts
-    uint16_t* slot = S.ckey;                                              // [npairs]
-    uint16_t* vkey = reinterpret_cast<uint16_t*>(S.start);               // [nv] key of voxel v
-    uint16_t* vend = reinterpret_cast<uint16_t*>(S.start) + CAND;   // [nv] end of its pairs
+    uint16_t* vkey = S.vkey;                                             // [nv] key of voxel v
     for (int32_t j = tid; j < kUnitKeys / 2; j += kBlock) kcw[j] = 0u;
-    __syncthreads();
-    for (int32_t i = tid; i < npairs; i += kBlock) {
-      const uint32_t p = S.prim[i], k = S.key[i];
-      const uint32_t sh = 16u * (k & 1u);
-      slot[i] = uint16_t(atomicAdd(&kcw[k >> 1], 1u << sh) >> sh);
-      if (KIND == 1) {                            // (triangles were weighed batch by batch)
+    if (KIND == 1) {                              // (triangles were weighed batch by batch)
+      for (int32_t i = tid; i < npairs; i += kBlock) {
+        const uint32_t p = S.prim[i];
         const int32_t* r = rec + int64_t(p) * kRec;
         const LatQ Lp = lat_q(lats, r[15], L);
-        const uint64_t m = m0 + k;
-        const int64_t v[3] = {int64_t(compact3(m)), int64_t(compact3(m >> 1)), int64_t(compact3(m >> 2))};
-        S.w[i] = unit_weight<KIND>(r, v, Lp, dirs[p].w);
+        int32_t v[3];
+        cell_voxel(U.o, c0 + S.key[i], v);
+        S.w[i] = fib_weight(r, v, Lp.Sb, dirs[p].w);
+      }
+    }
+    __syncthreads();
+    uint32_t slot[CAND / kBlock];
+#pragma unroll
+    for (int q = 0; q < CAND / kBlock; ++q) {
+      const int32_t i = tid + q * kBlock;
+      slot[q] = 0;
+      if (i < npairs) {
+        const uint32_t k = S.key[i], sh = 16u * (k & 1u);
+        slot[q] = (atomicAdd(&kcw[k >> 1], 1u << sh) >> sh) & 0xffffu;
       }
     }
     __syncthreads();
@@ -767,11 +842,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
       for (int k = 0; k < 16; ++k) {
         const uint32_t key = uint32_t(tid) * 16u + uint32_t(k);
         kst[key] = uint16_t(rp);
-        if (c[k] != 0u) {
-          vkey[rv] = uint16_t(key);
-          vend[rv] = uint16_t(rp + c[k]);
-          ++rv;
-        }
+        if (c[k] != 0u) vkey[rv++] = uint16_t(key);
         rp += c[k];
       }
     }
@@ -794,7 +865,11 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
     // ballots over the 12 key bits.
     const bool stable = npairs > stable_mean<KIND>() * nv;
     if (!stable) {
-      for (int32_t i = tid; i < npairs; i += kBlock) S.idx[kst[S.key[i]] + slot[i]] = uint16_t(i);
+#pragma unroll
+      for (int q = 0; q < CAND / kBlock; ++q) {
+        const int32_t i = tid + q * kBlock;
+        if (i < npairs) S.idx[kst[S.key[i]] + slot[q]] = uint16_t(i);
+      }
     } else if (tid < 64) {
       const uint64_t lt = (uint64_t(1) << tid) - 1;
       for (int32_t i0 = 0; i0 < npairs; i0 += 64) {
@@ -824,7 +899,16 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
     const uint64_t hi = lats ? uint64_t(uint32_t(rec[int64_t(rprim[s]) * kRec + 15])) << kPatchShift : 0ull;
     if (b + nv <= st.cap) {
       for (int32_t v = tid; v < nv; v += kBlock) {
-        const uint32_t a = v ? uint32_t(vend[v - 1]) : 0u, z = vend[v];
+        // its pairs: [start, next start), or (stably placed: the starts have run to the ends) [last
+        // end, end)
+        uint32_t a, z;
+        if (!stable) {
+          a = kst[vkey[v]];
+          z = v + 1 < nv ? uint32_t(kst[vkey[v + 1]]) : uint32_t(npairs);
+        } else {
+          a = v ? uint32_t(kst[vkey[v - 1]]) : 0u;
+          z = kst[vkey[v]];
+        }
         // the voxel's pairs in list order, which is primitive order (insertion sort)
         for (uint32_t i = a + 1; !stable && i < z; ++i) {
           const uint16_t x = S.idx[i];
@@ -1139,14 +1223,15 @@ vx_status tile_voxelize(int kind, const vx_grid* g, const float* data, int64_t n
     const int ugrid = tu.grids[kTuneUnit];
 #define VX_UNIT(KD, C)                                                                                           \
   do {                                                                                                          \
+    constexpr size_t bytes_ = unit_lds_bytes<KD, C>();                                                          \
     static bool attr_ = false;                                                                                  \
     if (!attr_) {                                                                                               \
       (void)hipFuncSetAttribute((const void*)k_unit<KD, C>, hipFuncAttributeMaxDynamicSharedMemorySize,        \
-                                int(unit_lds_bytes<C>()));                                                      \
+                                int(bytes_));                                                                   \
       attr_ = true;                                                                                             \
     }                                                                                                           \
-    hipLaunchKernelGGL((k_unit<KD, C>), dim3(ugrid), dim3(kBlock), unit_lds_bytes<C>(), s, w.rec, w.dirs, R.prim, \
-                       w.tstart, w.units, w.ctl, L, lats, w.unv, w.unp, w.usoff, w.st, w.stage_ctr, stats);    \
+    hipLaunchKernelGGL((k_unit<KD, C>), dim3(ugrid), dim3(kBlock), bytes_, s, w.rec, w.dirs, R.prim, w.tstart,  \
+                       w.units, w.ctl, L, lats, w.unv, w.unp, w.usoff, w.st, w.stage_ctr, stats);              \
   } while (0)
 #define VX_UNIT_KIND(KD)                                        \
   switch (tu.unit_budget) {                                     \
