@@ -66,6 +66,27 @@ def test_random_triangles_and_fibers(vx, seed):
     compare(lod, occ, occupancy_fibers(fw.grid, fw.pts, fw.offsets, 0.7, 5), "random fibers")
 
 
+@pytest.mark.parametrize("thin", [0, 1, 2])
+def test_thin_and_aligned_triangles(vx, thin):
+    """Triangles thin along each axis, with vertices on sub-cell corners and half-cells (their planes
+    and edges meet sub-cells in faces, edges and corners), planes parallel to an axis, needles and
+    points: all at once, so that every row and column ends exactly on a boundary somewhere."""
+    rng = np.random.default_rng(80 + thin)
+    grid = synth.Grid((0.0, 0.0, 0.0), 8.0, 3)
+    n = 72
+    t = rng.integers(4, 60, size=(n, 1, 3)) + rng.integers(-12, 13, size=(n, 3, 3))
+    t[:, :, thin] = t[:, :1, thin] + rng.integers(-2, 3, size=(n, 3))
+    t = t * 1.0
+    t[::3] += 0.5                                        # half sub-cells
+    t[::5, :, thin] = np.round(t[::5, :1, thin])         # flat on a sub-cell boundary
+    t[1::7, 2, (thin + 1) % 3] = t[1::7, 1, (thin + 1) % 3]
+    t[2::11, 2] = t[2::11, 1]                            # needles and, by chance, points
+    tris = (t / 8.0).astype(np.float32)
+    say(f"case: occupancy, {n} triangles thin along axis {thin}, 8^3, 3 levels")
+    lod, occ, _ = _pyramid(vx, 0, grid, _dev(tris), 3)
+    compare(lod, occ, occupancy_triangles(grid, tris, 3), f"thin {thin}")
+
+
 def test_lattice_aligned_cases(vx):
     """Flat triangles on a sub-cell boundary and on a voxel face, and a fiber along a sub-cell
     edge with a radius of whole sub-cells: every closed-box tie at once."""
