@@ -563,17 +563,6 @@ __global__ void __launch_bounds__(kBlock) k_fit_up64(const int64_t* __restrict__
   }
 }
 
-__global__ void __launch_bounds__(kBlock) k_copy_pairs(const uint8_t* __restrict__ ksrc, const uint32_t* __restrict__ psrc,
-                                                       const int64_t* __restrict__ ctl, int kb,
-                                                       uint8_t* __restrict__ kdst, uint32_t* __restrict__ pdst) {
-  const int64_t n = ctl[CTL_N_PAIRS];
-  for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += int64_t(gridDim.x) * kBlock) {
-    if (kb == 8) reinterpret_cast<uint64_t*>(kdst)[i] = reinterpret_cast<const uint64_t*>(ksrc)[i];
-    else reinterpret_cast<uint32_t*>(kdst)[i] = reinterpret_cast<const uint32_t*>(ksrc)[i];
-    pdst[i] = psrc[i];
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // orchestration
 // ---------------------------------------------------------------------------------------------
@@ -590,7 +579,7 @@ struct FitWs {
   FrontWs f;
   double* s64[21];         // [7][cap_L] per level 0..hi-1: FP64 sums (S, then w)
   int64_t* sstart;         // [cap_0 + 2] first sorted pair of every leaf voxel, end, key count
-  PairBufs pb, pc;         // sort buffers of the re-emitted pairs (a copy, then ping-pong)
+  PairBufs pb, pc;         // sort buffers of the re-emitted pairs, ping-pong
   int32_t* hist;           // radix digit histograms
 };
 
@@ -620,7 +609,7 @@ static size_t fit_ws_layout(int64_t n_pts, int64_t max_cand, int64_t max_pairs, 
   const int kb = key64 ? 8 : 4;
   for (PairBufs* pbuf : {&x.pb, &x.pc}) {
     pbuf->keys = cv.take<uint8_t>(max_pairs * kb);
-    pbuf->w = cv.take<float>(max_pairs);
+    pbuf->w = nullptr;
     pbuf->prim = cv.take<uint32_t>(max_pairs);
   }
   x.hist = cv.take<int32_t>(max_pairs > 0 ? int64_t(kRadixBuckets) * kGrid : 0);
@@ -704,14 +693,11 @@ vx_status fit_forward_run(const vx_grid* g, const vx_voxels* levels, const int64
 // FP64 sums of levels 0..hi-1 from the re-emitted pairs (f.pa, emission order, left intact)
 template <class Key>
 static void level_sums64(const vx_grid* g, const vx_voxels* levels, const int64_t* n_levels, int hi,
-                         const FitWs& w, const int64_t* caps, int64_t* stats, hipStream_t s) {
+                         const FitWs& w, const int64_t* caps, int64_t max_pairs, int64_t* stats, hipStream_t s) {
   VX_TIMED("fit_sums64", s);
-  const int kb = int(sizeof(Key));
-  hipLaunchKernelGGL(k_copy_pairs, dim3(kGrid), dim3(kBlock), 0, s, (const uint8_t*)w.f.pa.keys, w.f.pa.prim,
-                     w.f.ctl, kb, (uint8_t*)w.pc.keys, w.pc.prim);
-  const int res = radix_sort_pairs(kb == 8, 3 * g->log2_res, w.pc, w.pb, w.f.ctl + CTL_N_PAIRS, 0, w.hist,
-                                   w.partial, s);
-  const PairBufs P = res ? w.pb : w.pc;
+  // (the emission order stays in w.f.pa)
+  const PairBufs P = radix_sort_pairs(sizeof(Key) == 8, 3 * g->log2_res, w.f.pa, w.pb, w.pc, w.f.ctl + CTL_N_PAIRS,
+                                      max_pairs, w.hist, w.partial, s);
   device_scan(HeadIn<Key, 0>{(const Key*)P.keys}, LeafSegOut{w.sstart, caps[0]},
               LeafSegTotal{w.sstart, caps[0], n_levels, stats}, w.f.ctl + CTL_N_PAIRS, 0, w.partial, s);
   const Lat lat = make_lat(g, 1, 0.0f);
@@ -740,8 +726,8 @@ vx_status fit_backward_run(const vx_grid* g, const float* pts, int64_t n_pts, co
   child_starts(key64, levels, n_levels, hi, w, s);
   // (no points: every level is empty and the FP64 sums, sized by the points, are not read)
   if (n_pts > 0) {
-    if (key64) level_sums64<uint64_t>(g, levels, n_levels, hi, w, caps, stats, s);
-    else level_sums64<uint32_t>(g, levels, n_levels, hi, w, caps, stats, s);
+    if (key64) level_sums64<uint64_t>(g, levels, n_levels, hi, w, caps, max_pairs, stats, s);
+    else level_sums64<uint32_t>(g, levels, n_levels, hi, w, caps, max_pairs, stats, s);
   }
   // lobe gradients and the children's (S, w) gradients, level by level
   for (int L = lo; L <= hi; ++L) {

@@ -16,57 +16,72 @@ __device__ __forceinline__ void flag_or_s(int64_t* p, int64_t bit) {
 // ---------------------------------------------------------------------------------------------
 // radix sort
 // ---------------------------------------------------------------------------------------------
-constexpr int kDigitBits = 9;                 // 18-bit tile keys (1024^3 grids) sort in two passes
+constexpr int kDigitBits = kRadixBits;        // 18-bit tile keys (1024^3 grids) sort in two passes
 constexpr int kBuckets = 1 << kDigitBits;
 static_assert(kBuckets == kRadixBuckets, "histogram workspace");
-// blocks of the sort kernels: four per CU, all resident at once with the scatter's LDS (the digit
-// histograms, kBuckets per block, and their scan stay small)
-constexpr int kSortGrid = 1024;
+constexpr int kSortBlock = 512;               // one thread per digit, 8 waves
+constexpr int kSortWaves = kSortBlock / 64;
+constexpr int kSortE = 8;                     // elements per thread of a scatter tile
+constexpr int kSortTile = kSortBlock * kSortE;
+static_assert(kBuckets == kSortBlock, "thread d serves digit d");
+// Blocks of the sort kernels.  Large inputs: two per CU, all resident with the scatter's LDS, at least
+// two tiles each.  Small ones (up to 32 blocks): the scatter adds up the digit counts of the blocks
+// before it by itself (32 x 512 counts from L2) instead of leaving that to a scan's two launches
+// (28,000 records, one pass: 16 us; with the scan, whose part was 11 us, 31 us).
+constexpr int kSortFused = 32;
+constexpr int kSortGrid = kGrid;
 static_assert(kSortGrid <= kGrid, "histogram workspace");
-
-__device__ __forceinline__ int64_t sort_chunk(int64_t n) {
-  const int64_t c = (n + kSortGrid - 1) / kSortGrid;
-  return (c + kBlock - 1) / kBlock * kBlock;
+inline int sort_blocks(int64_t cap) {
+  const int64_t half = (cap + kSortTile / 2 - 1) / (kSortTile / 2), two = (cap + 2 * kSortTile - 1) / (2 * kSortTile);
+  if (two <= kSortFused) return int(half < 1 ? 1 : (half < kSortFused ? half : kSortFused));
+  return int(two < kSortGrid ? two : kSortGrid);
 }
 
-template <class Key>
-__global__ void __launch_bounds__(kBlock) k_radix_hist(const Key* __restrict__ keys, const int64_t* n_ptr, int shift,
-                                                       int32_t* __restrict__ hist) {
-  __shared__ int32_t h[kBuckets];
-  for (int d = threadIdx.x; d < kBuckets; d += kBlock) h[d] = 0;
+__device__ __forceinline__ int64_t sort_chunk(int64_t n) {
+  const int64_t c = (n + gridDim.x - 1) / gridDim.x;
+  return (c + kSortBlock - 1) / kSortBlock * kSortBlock;
+}
+
+// Digit counts of every block's chunk: hist[d][block], or hist[block][d] for the fused scatter.
+// Eight rows of 512 keys are loaded together; runs of one digit in a row (common: records of one tile)
+// are added once each, by their first lanes.  Bound by the read with keys spread widely (41.7 M 64-bit
+// samples: 0.089 ms = 3.7 TB/s, with four rows of 256 per block 0.16 ms), by LDS adds to the same few
+// counters otherwise (47.6 M records: 0.16 ms; every lane adding by itself 0.22 ms).
+template <class Key, bool FUSED>
+__global__ void __launch_bounds__(kSortBlock) k_radix_hist(const Key* __restrict__ keys, const int64_t* n_ptr, int shift,
+                                                           int32_t* __restrict__ hist, const int64_t* only_if) {
+  __shared__ int32_t h[kSortWaves][kBuckets];
+  if (only_if && *only_if == 0) return;
+  const int t = threadIdx.x, w = t >> 6, lane = lane_id();
+#pragma unroll
+  for (int q = 0; q < kSortWaves; ++q) h[q][t] = 0;
   __syncthreads();
   const int64_t n = *n_ptr;
   const int64_t chunk = sort_chunk(n);
   const int64_t b0 = int64_t(blockIdx.x) * chunk;
   const int64_t b1 = b0 + chunk < n ? b0 + chunk : n;
-  // Four rows of 256 keys per step, loaded together.  Lanes of a wave holding the same digit find
-  // each other by ballots over its bits and the first of them adds the group's count: one LDS
-  // atomic per distinct digit and wave (runs of equal digits are common in the record lists).
-  constexpr int kRows = 4;
-  const int lane = lane_id();
-  const uint64_t lt = (uint64_t(1) << lane) - 1;
-  for (int64_t t0 = b0; t0 < b1; t0 += int64_t(kRows) * kBlock) {
-    int dg[kRows];
-    bool ok[kRows];
+  for (int64_t t0 = b0; t0 < b1; t0 += kSortTile) {
+    int dg[kSortE];
 #pragma unroll
-    for (int j = 0; j < kRows; ++j) {
-      const int64_t i = t0 + j * kBlock + threadIdx.x;
-      ok[j] = i < b1;
-      dg[j] = ok[j] ? int((keys[i] >> shift) & (kBuckets - 1)) : 0;
+    for (int j = 0; j < kSortE; ++j) {
+      const int64_t i = t0 + j * kSortBlock + t;
+      dg[j] = i < b1 ? int((keys[i] >> shift) & (kBuckets - 1)) : -1;
     }
 #pragma unroll
-    for (int j = 0; j < kRows; ++j) {
-      uint64_t peers = __ballot(ok[j]);
-#pragma unroll
-      for (int b = 0; b < kDigitBits; ++b) {
-        const uint64_t m = __ballot((dg[j] >> b) & 1);
-        peers &= ((dg[j] >> b) & 1) ? m : ~m;
-      }
-      if (ok[j] && (peers & lt) == 0) atomicAdd(&h[dg[j]], int32_t(__popcll(peers)));
+    for (int j = 0; j < kSortE; ++j) {
+      const int prev = __builtin_amdgcn_update_dpp(-1, dg[j], 0x138, 0xf, 0xf, false);   // of the lane before
+      const bool head = lane == 0 || dg[j] != prev;
+      const uint64_t heads = __builtin_amdgcn_ballot_w64(head);
+      const uint64_t after = heads >> lane >> 1;
+      const int len = after ? __ffsll((unsigned long long)after) : 64 - lane;
+      if (head && dg[j] >= 0) atomicAdd(&h[w][dg[j]], len);
     }
   }
   __syncthreads();
-  for (int d = threadIdx.x; d < kBuckets; d += kBlock) hist[int64_t(d) * kSortGrid + blockIdx.x] = h[d];
+  int32_t sum = 0;
+#pragma unroll
+  for (int q = 0; q < kSortWaves; ++q) sum += h[q][t];
+  hist[FUSED ? int64_t(blockIdx.x) * kBuckets + t : int64_t(t) * gridDim.x + blockIdx.x] = sum;
 }
 
 struct I32In {
@@ -81,151 +96,173 @@ struct NoTotal {
   __device__ void operator()(int64_t, int64_t) const {}
 };
 
-// One pass of the stable scatter.  A block takes its chunk in tiles of kTileN elements; a tile
-// is ranked by digit (wave ballots within each row of 256, counts per row and wave, one scan over
-// the digits), placed digit by digit in LDS, and written out in that order, so each digit's run
-// of the tile lands contiguously (coalesced) at the digit's next position.  Order within a digit
-// is row, wave, lane = input order: the sort is stable.  w may be null (not carried).
-constexpr int kTileE = 4;                      // rows of 256 elements per tile (38 KB of LDS per block)
-constexpr int kTileN = kBlock * kTileE;
-static_assert(kBuckets == 2 * kBlock, "the digit scan takes two digits per thread");
-static_assert(kTileN <= 32767, "16-bit tile positions");
-
-template <class Key>
-__global__ void __launch_bounds__(kBlock) k_radix_scatter(const Key* __restrict__ kin, const float* __restrict__ win,
-                                                          const uint32_t* __restrict__ pin, Key* __restrict__ kout,
-                                                          float* __restrict__ wout, uint32_t* __restrict__ pout,
-                                                          const int64_t* n_ptr, int shift,
-                                                          const int32_t* __restrict__ hist_off) {
-  __shared__ int32_t run[kBuckets];                    // next output position of each digit
-  __shared__ int16_t cnt[kTileE][kWaves][kBuckets];    // per row and wave; then their prefixes (< kTileN)
-  __shared__ int32_t toff[kBuckets];                   // each digit's first slot in the sorted tile
-  __shared__ int32_t ttot[kBuckets];
-  __shared__ Key sk[kTileN];
-  __shared__ float sw[kTileN];
-  __shared__ uint32_t sp[kTileN];
-  __shared__ int32_t stmp[kWaves + 1];
+// One pass of the stable scatter.  A block takes its chunk in tiles of kSortTile elements, each wave a
+// contiguous eighth of the tile, row by row: lanes holding the same digit find each other by
+// ballots over its bits, and the wave's running count of the digit gives their ranks.  One scan over
+// the digits places the tile digit by digit in LDS, and it is written out in that order: each
+// digit's run (8 elements on average) lands contiguously at the digit's next position.  Order within
+// a digit is wave, row, lane = input order: the sort is stable.
+// Bound by HBM and, close behind, by the ballots: 41.7 M samples in 64-bit words, per pass 0.166 ms
+// (4.0 TB/s); in tiles of 1,024, with counts per row and wave and the weights carried along, 0.39 ms.
+template <class Key, bool PRIM, bool FUSED>
+__global__ void __launch_bounds__(kSortBlock) k_radix_scatter(const Key* __restrict__ kin,
+                                                              const uint32_t* __restrict__ pin, Key* __restrict__ kout,
+                                                              uint32_t* __restrict__ pout, const int64_t* n_ptr,
+                                                              int shift, const int32_t* __restrict__ hist,
+                                                              const int64_t* only_if) {
+  __shared__ uint16_t cnt[kSortWaves][kBuckets];       // per wave: counts, then first slots in the tile
+  __shared__ int32_t place[kBuckets];                  // output position less tile slot, per digit
+  __shared__ Key sk[kSortTile];
+  __shared__ uint32_t sp[PRIM ? kSortTile : 1];
+  __shared__ int32_t stmp[kSortWaves + 1];
+  if (only_if && *only_if == 0) return;
   const int t = threadIdx.x, w = t >> 6, lane = lane_id();
-  const bool has_w = win != nullptr;
-  for (int d = t; d < kBuckets; d += kBlock) run[d] = hist_off[int64_t(d) * kSortGrid + blockIdx.x];
+  int32_t run;                                         // next output position of digit t
+  if (FUSED) {
+    int32_t before = 0, all = 0, total;
+    constexpr int kAtOnce = 8;
+    for (int g0 = 0; g0 < int(gridDim.x); g0 += kAtOnce) {
+      int32_t c[kAtOnce];
+#pragma unroll
+      for (int j = 0; j < kAtOnce; ++j) {
+        const int g = g0 + j < int(gridDim.x) ? g0 + j : 0;
+        c[j] = hist[int64_t(g) * kBuckets + t];
+      }
+#pragma unroll
+      for (int j = 0; j < kAtOnce; ++j) {
+        const int g = g0 + j;
+        before += g < int(blockIdx.x) ? c[j] : 0;
+        all += g < int(gridDim.x) ? c[j] : 0;
+      }
+    }
+    run = block_exclusive_scan_n<kSortWaves>(all, stmp, total) + before;
+  } else {
+    run = hist[int64_t(t) * gridDim.x + blockIdx.x];
+  }
   const int64_t n = *n_ptr;
   const int64_t chunk = sort_chunk(n);
   const int64_t b0 = int64_t(blockIdx.x) * chunk;
   const int64_t b1 = b0 + chunk < n ? b0 + chunk : n;
-  const uint64_t lt = (uint64_t(1) << lane) - 1;
-  for (int64_t t0 = b0; t0 < b1; t0 += kTileN) {
-    const int ntile = int(b1 - t0 < kTileN ? b1 - t0 : kTileN);
-    for (int q = t; q < kTileE * kWaves * kBuckets; q += kBlock) (&cnt[0][0][0])[q] = 0;
-    Key k[kTileE];
-    float wv[kTileE];
-    uint32_t pv[kTileE];
-    int dg[kTileE], rk[kTileE];
+  for (int64_t t0 = b0; t0 < b1; t0 += kSortTile) {
+    const int ntile = int(b1 - t0 < kSortTile ? b1 - t0 : kSortTile);
+    Key k[kSortE];
+    uint32_t pv[kSortE];
+    int rk[kSortE];
 #pragma unroll
-    for (int j = 0; j < kTileE; ++j) {
-      const int64_t i = t0 + j * kBlock + t;
-      const bool valid = i < b1;
-      k[j] = valid ? kin[i] : Key(0);
-      wv[j] = valid && has_w ? win[i] : 0.f;
-      pv[j] = valid ? pin[i] : 0u;
-      dg[j] = int((k[j] >> shift) & (kBuckets - 1));
+    for (int j = 0; j < kSortE; ++j) {
+      const int e = w * (64 * kSortE) + j * 64 + lane;
+      k[j] = e < ntile ? kin[t0 + e] : Key(0);
+      if (PRIM) pv[j] = e < ntile ? pin[t0 + e] : 0u;
     }
+#pragma unroll
+    for (int q = 0; q < kSortWaves; ++q) cnt[q][t] = 0;
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kTileE; ++j) {
-      const bool valid = t0 + j * kBlock + t < b1;
-      uint64_t peers = __ballot(valid);
+    for (int j = 0; j < kSortE; ++j) {
+      const bool valid = w * (64 * kSortE) + j * 64 + lane < ntile;
+      const int dg = int((k[j] >> shift) & (kBuckets - 1));
+      const uint64_t valids = __builtin_amdgcn_ballot_w64(valid);
+      uint32_t plo = uint32_t(valids), phi = uint32_t(valids >> 32);
 #pragma unroll
-      for (int b = 0; b < kDigitBits; ++b) {
-        const uint64_t m = __ballot((dg[j] >> b) & 1);
-        peers &= ((dg[j] >> b) & 1) ? m : ~m;
+      for (int b = 0; b < kDigitBits; ++b) {            // keep the lanes whose bit is this lane's
+        const int mine = __builtin_amdgcn_sbfe(dg, b, 1);
+        const uint64_t m = __builtin_amdgcn_ballot_w64(mine != 0);
+        plo &= ~(uint32_t(m) ^ uint32_t(mine));
+        phi &= ~(uint32_t(m >> 32) ^ uint32_t(mine));
       }
-      rk[j] = valid ? __popcll(peers & lt) : -1;
-      if (valid && rk[j] == 0) cnt[j][w][dg[j]] = int16_t(__popcll(peers));
+      const int r = int(__builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0)));
+      const int have = valid ? int(cnt[w][dg]) : 0;
+      rk[j] = have + r;
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (valid && r == 0) cnt[w][dg] = uint16_t(have + __popc(plo) + __popc(phi));
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
     __syncthreads();
-    // per digit: prefixes over (row, wave) in input order, and the tile's count
-    int32_t dsum = 0;
-    for (int d = t; d < kBuckets; d += kBlock) {
-      int32_t acc = 0;
+    // digit t: its counts over the waves in input order, and its first slot in the sorted tile
+    int32_t c[kSortWaves], sum = 0, total;
 #pragma unroll
-      for (int j = 0; j < kTileE; ++j)
-#pragma unroll
-        for (int ww = 0; ww < kWaves; ++ww) {
-          const int32_t c = cnt[j][ww][d];
-          cnt[j][ww][d] = int16_t(acc);
-          acc += c;
-        }
-      ttot[d] = acc;
+    for (int q = 0; q < kSortWaves; ++q) {
+      c[q] = cnt[q][t];
+      sum += c[q];
     }
-    __syncthreads();
-    // tile offsets of the digits: thread t scans digits 2t and 2t + 1
-    {
-      const int32_t a = ttot[2 * t], b = ttot[2 * t + 1];
-      int32_t total;
-      const int32_t ex = block_exclusive_scan<int32_t>(a + b, stmp, total);
-      toff[2 * t] = ex;
-      toff[2 * t + 1] = ex + a;
-      (void)dsum;
+    int32_t slot0 = block_exclusive_scan_n<kSortWaves>(sum, stmp, total);
+    place[t] = run - slot0;
+    run += sum;
+#pragma unroll
+    for (int q = 0; q < kSortWaves; ++q) {
+      cnt[q][t] = uint16_t(slot0);
+      slot0 += c[q];
     }
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kTileE; ++j) {
-      if (rk[j] >= 0) {
-        const int slot = toff[dg[j]] + cnt[j][w][dg[j]] + rk[j];
+    for (int j = 0; j < kSortE; ++j) {
+      if (w * (64 * kSortE) + j * 64 + lane < ntile) {
+        const int slot = int(cnt[w][int((k[j] >> shift) & (kBuckets - 1))]) + rk[j];
         sk[slot] = k[j];
-        sw[slot] = wv[j];
-        sp[slot] = pv[j];
+        if (PRIM) sp[slot] = pv[j];
       }
     }
     __syncthreads();
-    for (int q = t; q < ntile; q += kBlock) {
+    for (int q = t; q < ntile; q += kSortBlock) {
       const Key kk = sk[q];
-      const int d = int((kk >> shift) & (kBuckets - 1));
-      const int32_t pos = run[d] + (q - toff[d]);
+      const int32_t pos = place[int((kk >> shift) & (kBuckets - 1))] + q;
       kout[pos] = kk;
-      if (has_w) wout[pos] = sw[q];
-      pout[pos] = sp[q];
+      if (PRIM) pout[pos] = sp[q];
     }
-    __syncthreads();
-    for (int d = t; d < kBuckets; d += kBlock) run[d] += ttot[d];
     __syncthreads();
   }
 }
 
-int radix_sort_pairs(bool key64, int key_bits, PairBufs a, PairBufs b, const int64_t* n_dev, int64_t cap,
-                     int32_t* hist, int64_t* partial, hipStream_t s) {
-  (void)cap;
-  const int passes = (key_bits + kDigitBits - 1) / kDigitBits;
-  PairBufs src = a, dst = b;
-  for (int p = 0; p < passes; ++p) {
-    const int shift = kDigitBits * p;
-    {
-      VX_TIMED("radix_hist", s);
-      if (key64)
-        hipLaunchKernelGGL(k_radix_hist<uint64_t>, dim3(kSortGrid), dim3(kBlock), 0, s, (const uint64_t*)src.keys, n_dev,
-                           shift, hist);
-      else
-        hipLaunchKernelGGL(k_radix_hist<uint32_t>, dim3(kSortGrid), dim3(kBlock), 0, s, (const uint32_t*)src.keys, n_dev,
-                           shift, hist);
-    }
-    {
-      VX_TIMED("radix_scan", s);
-      device_scan(I32In{hist}, I32Out{hist}, NoTotal{}, nullptr, int64_t(kBuckets) * kSortGrid, partial, s);
-    }
-    {
-      VX_TIMED("radix_scatter", s);
-      if (key64)
-        hipLaunchKernelGGL(k_radix_scatter<uint64_t>, dim3(kSortGrid), dim3(kBlock), 0, s, (const uint64_t*)src.keys,
-                           src.w, src.prim, (uint64_t*)dst.keys, dst.w, dst.prim, n_dev, shift, hist);
-      else
-        hipLaunchKernelGGL(k_radix_scatter<uint32_t>, dim3(kSortGrid), dim3(kBlock), 0, s, (const uint32_t*)src.keys,
-                           src.w, src.prim, (uint32_t*)dst.keys, dst.w, dst.prim, n_dev, shift, hist);
-    }
-    PairBufs tmp = src;
-    src = dst;
-    dst = tmp;
+template <class Key>
+static void radix_pass(const PairBufs& src, const PairBufs& dst, const int64_t* n_dev, int64_t cap, int shift,
+                       int32_t* hist, int64_t* partial, const int64_t* only_if, hipStream_t s) {
+  const int blocks = sort_blocks(cap);
+  const bool fused = blocks <= kSortFused;
+  {
+    VX_TIMED("radix_hist", s);
+    if (fused)
+      hipLaunchKernelGGL((k_radix_hist<Key, true>), dim3(blocks), dim3(kSortBlock), 0, s, (const Key*)src.keys, n_dev,
+                         shift, hist, only_if);
+    else
+      hipLaunchKernelGGL((k_radix_hist<Key, false>), dim3(blocks), dim3(kSortBlock), 0, s, (const Key*)src.keys, n_dev,
+                         shift, hist, only_if);
   }
-  return passes & 1;
+  if (!fused) {
+    VX_TIMED("radix_scan", s);
+    device_scan(I32In{hist}, I32Out{hist}, NoTotal{}, nullptr, int64_t(kBuckets) * blocks, partial, s);
+  }
+  VX_TIMED("radix_scatter", s);
+  const auto scatter = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kSortBlock), 0, s, (const Key*)src.keys, src.prim, (Key*)dst.keys,
+                       dst.prim, n_dev, shift, hist, only_if);
+  };
+  if constexpr (sizeof(Key) == 8) {
+    if (!src.prim)
+      return fused ? scatter(k_radix_scatter<Key, false, true>) : scatter(k_radix_scatter<Key, false, false>);
+  }
+  fused ? scatter(k_radix_scatter<Key, true, true>) : scatter(k_radix_scatter<Key, true, false>);
+}
+
+void radix_sort_pass(bool key64, const PairBufs& src, const PairBufs& dst, const int64_t* n_dev, int64_t cap,
+                     int shift, int32_t* hist, int64_t* partial, const int64_t* only_if, hipStream_t s) {
+  if (key64) radix_pass<uint64_t>(src, dst, n_dev, cap, shift, hist, partial, only_if, s);
+  else radix_pass<uint32_t>(src, dst, n_dev, cap, shift, hist, partial, only_if, s);
+}
+
+PairBufs radix_sort_pairs(bool key64, int key_bits, const PairBufs& in, const PairBufs& t0, const PairBufs& t1,
+                          const int64_t* n_dev, int64_t cap, int32_t* hist, int64_t* partial, hipStream_t s,
+                          int first_bit) {
+  PairBufs src = in, dst = t0, spare = t1;
+  for (int shift = first_bit; shift < first_bit + key_bits; shift += kDigitBits) {
+    radix_sort_pass(key64, src, dst, n_dev, cap, shift, hist, partial, nullptr, s);
+    src = dst;
+    const PairBufs x = dst;
+    dst = spare;
+    spare = x;
+  }
+  return src;
 }
 
 // ---------------------------------------------------------------------------------------------

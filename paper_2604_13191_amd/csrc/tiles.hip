@@ -1191,9 +1191,7 @@ vx_status tile_voxelize(int kind, const vx_grid* g, const float* data, int64_t n
     while ((1 << pb) < batch->n_patches) ++pb;
     key_bits = kPatchShift - 3 * tb + pb;
   }
-  // the records carry no weight: the sort moves keys and primitive ids only
-  const int res = radix_sort_pairs(key64, key_bits, w.ra, w.rb, w.ctl + CTL_N_REC, max_rec, w.hist, w.partial, s);
-  const PairBufs R = res ? w.rb : w.ra;
+  const PairBufs R = radix_sort_pairs(key64, key_bits, w.ra, w.rb, w.ra, w.ctl + CTL_N_REC, max_rec, w.hist, w.partial, s);
   {
     VX_TIMED("tile_heads", s);
     if (key64)

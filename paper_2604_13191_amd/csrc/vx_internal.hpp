@@ -284,10 +284,17 @@ struct PairBufs {
 
 void launch_fill_i64(int64_t* p, int64_t n, int64_t v, hipStream_t s);
 
-// sort pairs by key (stable LSD radix); returns the buffer index (0 = a, 1 = b) holding the result
+// sort (key, prim) pairs by key (stable LSD radix) from `in`, which stays as it is unless it is t1,
+// through t0 and t1 in turn; returns the buffers holding the result.  cap bounds *n_dev.  Without prims
+// (prim == nullptr, 64-bit keys only) the keys alone are sorted, by the key_bits bits from first_bit.
 constexpr int kRadixBuckets = 512;          // digit values of the record sort (hist is kRadixBuckets x kGrid)
-int radix_sort_pairs(bool key64, int key_bits, PairBufs a, PairBufs b, const int64_t* n_dev, int64_t cap,
-                     int32_t* hist, int64_t* partial, hipStream_t s);
+constexpr int kRadixBits = 9;
+PairBufs radix_sort_pairs(bool key64, int key_bits, const PairBufs& in, const PairBufs& t0, const PairBufs& t1,
+                          const int64_t* n_dev, int64_t cap, int32_t* hist, int64_t* partial, hipStream_t s,
+                          int first_bit = 0);
+// one pass by the digit at `shift`; with only_if, nothing is done where *only_if is 0
+void radix_sort_pass(bool key64, const PairBufs& src, const PairBufs& dst, const int64_t* n_dev, int64_t cap,
+                     int shift, int32_t* hist, int64_t* partial, const int64_t* only_if, hipStream_t s);
 
 // head flags of sorted keys (SHIFT 0: the key, 3: the parent key) and segment starts
 template <class Key, bool BATCH>

@@ -172,3 +172,21 @@ def test_errors(vx):
         vx.SamplePlan(1, grid, _dev(pts), offsets=torch.tensor([0, 2, 1, 3]), chords=2, per_chord=2)
     with pytest.raises(vx.VxError):                                   # N out of range (host check)
         vx.SamplePlan(0, grid, _dev(tris), N=0)
+
+
+@pytest.mark.parametrize("log2_res,n,N,inside", [
+    (9, 1, 1, True), (9, 511, 1, True), (9, 4096, 1, False), (9, 8193, 1, True),     # 27 key bits fill three passes
+    (9, 3000, 2000, False), (10, 3000, 2000, True),                                    # sorts of more than 32 blocks
+    (11, 4097, 2, False), (12, 700, 16, True), (12, 700, 16, False),                 # key and id in one word
+    (12, 3000, 2000, False), (20, 8, 64, True), (20, 8, 64, False), (20, 300, 16, False)])
+def test_sort_paths(vx, log2_res, n, N, inside):
+    """Samples around the sort's tile sizes, in one block and in many, with and without samples outside
+    the grid where those take a pass of their own, and ids that fit beside the key and that do not."""
+    R = 1 << log2_res
+    wl = synth.random_triangles(n, log2_res, seed=n + N, scale=R / 40, margin=R / 20)
+    tris = np.clip(wl.tris, np.float32(0.25 / R), np.float32(1 - 0.5 / R)) if inside else wl.tris
+    say(f"case: sampled random triangles {n}, R = {R}, N = {N}, {'all inside' if inside else 'some outside'}")
+    p, g = _tris(vx, wl.grid, tris, N)
+    ref = oracle.sample_triangles(wl.grid, tris, N)
+    assert p.n_inside == ref.n_pairs and (p.n_inside == p.n_samples) == inside
+    say(compare_samples(g, ref, f"{n} triangles, R = {R}, N = {N}"))
