@@ -13,6 +13,8 @@
 // points.  Intermediates are recomputed instead of stored: the per-direction profiles are
 // re-evaluated in the backward kernel, and the (segment, voxel) pairs are re-emitted in
 // primitive order by the voxelize front half.
+#include <type_traits>
+
 #include "geom.hpp"
 #include "vx_internal.hpp"
 
@@ -28,33 +30,45 @@ __device__ __forceinline__ int64_t key_lower_bound(const Key* __restrict__ keys,
   return lo;
 }
 
-__device__ __forceinline__ float quadf(const float* S, float x, float y, float z) {
-  return S[0] * x * x + S[1] * y * y + S[2] * z * z + 2.0f * (S[3] * x * y + S[4] * x * z + S[5] * y * z);
-}
-
 constexpr int kMaxChild = 8;
 
-// children of voxel u in the level below: [cstart[u], cstart[u + 1]), at most 8
-__device__ __forceinline__ int child_range(const int64_t* __restrict__ cstart, int64_t u, int64_t& first) {
-  first = cstart[u];
-  const int64_t n = cstart[u + 1] - first;
-  return int(n < kMaxChild ? n : kMaxChild);
-}
-
 // ---------------------------------------------------------------------------------------------
-// Layout of both passes: 16 lanes per voxel (four voxels per wave), each lane taking every 16th
-// direction; a voxel's children (w, S) are staged in LDS by its group, the directions of the set
-// once per block.  Sums over a group's lanes are butterfly reductions over 16 lanes.
+// Layout of both passes: one wave per voxel, the voxels of all fitted levels in one launch (sixteen
+// lanes per voxel ran as long as the largest of a wave's four, and the upper levels' launches stood
+// nearly empty).  Each lane keeps ndir / 64 directions as their products
+// x^2 .. 2yz, so that w^T S w is six fused multiply-adds; a child's sums are the same for all lanes
+// and come from LDS.
 // ---------------------------------------------------------------------------------------------
-constexpr int kGroup = 16;                      // lanes per voxel
-constexpr int kGroups = kBlock / kGroup;        // voxels in flight per block
-constexpr int kMaxDir = 256;
+constexpr int kMaxFit = 20;
+constexpr int kFitGrid = 2 * kGrid;
+struct FitLevel {
+  const int64_t* n;        // voxels
+  int64_t rows;            // parameter rows: voxels past them are not fitted
+  const float* w;
+  const int64_t* cstart;   // children of voxel u in the level below: [cstart[u], cstart[u + 1]), at most 8
+  const float* Lp;
+  const float* chw;        // forward: the children's sums, and the loss per voxel
+  const float* chS;
+  int64_t chcap;
+  float* loss;
+  const double* c64;       // backward: the children's FP64 sums [7][gcap] (S, then w), their gradients
+  double* gch;             // [7][gcap] likewise, and the parameters'
+  int64_t gcap;
+  float* dLp;
+};
+struct FitLevels {
+  FitLevel l[kMaxFit];
+  int count;
+};
 
-template <class T>
-__device__ __forceinline__ T group_sum(T v) {
-#pragma unroll
-  for (int off = kGroup / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kGroup);
-  return v;
+// the i-th voxel of all levels: its level, and i reduced to its index there; false past the last
+__device__ __forceinline__ bool fit_level(const FitLevels& lv, int64_t& i, int& L) {
+  for (L = 0; L < lv.count; ++L) {
+    const int64_t n = *lv.l[L].n;
+    if (i < n) return true;
+    i -= n;
+  }
+  return false;
 }
 
 __device__ __forceinline__ void wave_sync_lds() {
@@ -62,76 +76,99 @@ __device__ __forceinline__ void wave_sync_lds() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
-// the children of voxel u staged by the group: cw[c], cS[c][6]; returns their number
+// the products of direction k (zeros past the set: its terms vanish)
 template <class T>
-__device__ __forceinline__ int stage_children(const vx_voxels& ch, const int64_t* cstart, int64_t u, bool active,
-                                              int gl, T* cw, T (*cS)[6], int64_t& first) {
-  int nc = 0;
-  first = 0;
-  if (active) nc = child_range(cstart, u, first);
-  if (active && gl < nc) {
-    const int64_t cc = first + gl;
-    cw[gl] = T(ch.w[cc]);
+__device__ __forceinline__ void dir_products(const float* __restrict__ dirs, int ndir, int k, T x[3], T m[6]) {
 #pragma unroll
-    for (int t = 0; t < 6; ++t) cS[gl][t] = T(ch.S[int64_t(t) * ch.cap + cc]);
-  }
-  wave_sync_lds();
-  return nc;
+  for (int a = 0; a < 3; ++a) x[a] = k < ndir ? T(dirs[3 * k + a]) : T(0);
+  m[0] = x[0] * x[0];
+  m[1] = x[1] * x[1];
+  m[2] = x[2] * x[2];
+  m[3] = T(2) * x[0] * x[1];
+  m[4] = T(2) * x[0] * x[2];
+  m[5] = T(2) * x[1] * x[2];
+}
+template <class T>
+__device__ __forceinline__ T quad(const T* S, const T m[6]) {
+  T q = S[0] * m[0];
+#pragma unroll
+  for (int t = 1; t < 6; ++t) q = fma(S[t], m[t], q);
+  return q;
 }
 
 // ---------------------------------------------------------------------------------------------
-// forward
+// forward.  Bound by FP32 arithmetic (0.69 M voxels, 2.7 M children, 128 directions: 0.25 ms;
+// with sixteen lanes per voxel, the sums read from LDS for every direction, 0.58 ms).
 // ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(kBlock) k_fit_fwd(vx_voxels par, const int64_t* n_par_p, int64_t rows, vx_voxels ch,
-                                                    const int64_t* __restrict__ cstart, const float* __restrict__ Lp,
-                                                    const float* __restrict__ dirs, int ndir,
-                                                    float* __restrict__ loss_vox) {
-  __shared__ float sdir[kMaxDir][3];
-  __shared__ float scw[kGroups][kMaxChild];
-  __shared__ float scS[kGroups][kMaxChild][6];
-  for (int k = threadIdx.x; k < ndir; k += kBlock)
-    for (int a = 0; a < 3; ++a) sdir[k][a] = dirs[3 * k + a];
-  __syncthreads();
-  const int grp = threadIdx.x / kGroup, gl = threadIdx.x % kGroup;
-  const int64_t n_par = *n_par_p < rows ? *n_par_p : rows;   // never past the parameter rows
-  // the four groups of a wave advance together (uniform trip count per wave)
-  const int wgrp0 = (threadIdx.x >> 6) * (64 / kGroup);
-  for (int64_t u0 = int64_t(blockIdx.x) * kGroups + wgrp0; u0 < n_par; u0 += int64_t(gridDim.x) * kGroups) {
-    const int64_t u = u0 + (grp - wgrp0);
-    const bool in = u < n_par;
-    const float W = in ? par.w[u] : 0.f;
-    const bool active = in && W > 0.f;
-    int64_t first;
-    const int nc = stage_children(ch, cstart, u, active, gl, scw[grp], scS[grp], first);
-    float acc = 0.f;
-    if (active) {
-      float l[12];
-      for (int t = 0; t < 12; ++t) l[t] = Lp[u * 12 + t];
-      const float invW = 1.0f / W;
-      for (int k = gl; k < ndir; k += kGroup) {
-        const float x = sdir[k][0], y = sdir[k][1], z = sdir[k][2];
-        float tau = 0.f;
-        for (int c = 0; c < nc; ++c)
-          if (scw[grp][c] > 0.f) tau += sqrtf(fmaxf(scw[grp][c] * quadf(scS[grp][c], x, y, z), 0.f));
-        tau *= invW;
-        float f = 0.f;
-        for (int j = 0; j < 2; ++j) {
-          const float* lj = l + 6 * j;
-          const float y0 = lj[0] * x + lj[1] * y + lj[3] * z, y1 = lj[2] * y + lj[4] * z, y2 = lj[5] * z;
-          f += sqrtf(y0 * y0 + y1 * y1 + y2 * y2);
-        }
-        const float r = f - tau;
-        acc = fmaf(r, r, acc);
-      }
+// sqrt(x): the reciprocal root's estimate, refined on the residual x - s^2; zeros and numbers so
+// small that the residual underflows take the library's function
+__device__ __forceinline__ float sqrt_nrf(float x) {
+  if (__builtin_amdgcn_ballot_w64(!(x >= 0x1p-96f))) return sqrtf(x);
+  const float r = __builtin_amdgcn_rsqf(x), s = x * r;
+  return fmaf(fmaf(-s, s, x), 0.5f * r, s);
+}
+
+template <int DPL>
+__global__ void __launch_bounds__(kBlock) k_fit_fwd(FitLevels lv, const float* __restrict__ dirs, int ndir) {
+  __shared__ float stage[kWaves][kMaxChild][8];      // per child: S, then w
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float x[DPL][3], m[DPL][6];
+#pragma unroll
+  for (int i = 0; i < DPL; ++i) dir_products(dirs, ndir, lane + 64 * i, x[i], m[i]);
+  const float rdir = float(ndir);
+  for (int64_t i0 = int64_t(blockIdx.x) * kWaves + wv;; i0 += int64_t(gridDim.x) * kWaves) {
+    int64_t u = i0;
+    int L;
+    if (!fit_level(lv, u, L)) return;
+    const FitLevel& F = lv.l[L];
+    if (u >= F.rows) continue;                       // never past the parameter rows
+    const float W = F.w[u];
+    if (!(W > 0.f)) {
+      if (lane == 0) F.loss[u] = 0.f;
+      continue;
     }
-    acc = group_sum(acc);
-    if (in && gl == 0) loss_vox[u] = active ? acc / float(ndir) : 0.f;
-    wave_sync_lds();                                  // the group's LDS slots are reused next
+    const int64_t first = F.cstart[u], nch = F.cstart[u + 1] - first;
+    const int nc = int(nch < kMaxChild ? nch : kMaxChild);
+    const int lt = lane >> 3, lc = lane & 7;
+    if (lc < nc && lt < 7) stage[wv][lc][lt] = lt < 6 ? F.chS[int64_t(lt) * F.chcap + first + lc] : F.chw[first + lc];
+    wave_sync_lds();
+    float tau[DPL];
+#pragma unroll
+    for (int i = 0; i < DPL; ++i) tau[i] = 0.f;
+    for (int c = 0; c < nc; ++c) {
+      float S[6];
+#pragma unroll
+      for (int t = 0; t < 6; ++t) S[t] = stage[wv][c][t];
+      const float wc = stage[wv][c][6];
+      if (!(wc > 0.f)) continue;
+#pragma unroll
+      for (int i = 0; i < DPL; ++i) tau[i] += sqrt_nrf(fmaxf(wc * quad(S, m[i]), 0.f));
+    }
+    float l[12], acc = 0.f;
+#pragma unroll
+    for (int t = 0; t < 12; ++t) l[t] = F.Lp[u * 12 + t];
+    const float invW = 1.0f / W;
+#pragma unroll
+    for (int i = 0; i < DPL; ++i) {
+      float f = 0.f;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const float* lj = l + 6 * j;
+        const float y0 = lj[0] * x[i][0] + lj[1] * x[i][1] + lj[3] * x[i][2];
+        const float y1 = lj[2] * x[i][1] + lj[4] * x[i][2], y2 = lj[5] * x[i][2];
+        f += sqrt_nrf(y0 * y0 + y1 * y1 + y2 * y2);
+      }
+      const float r = f - tau[i] * invW;
+      acc = fmaf(r, r, acc);
+    }
+    acc = wave_sum(acc);
+    if (lane == 0) F.loss[u] = acc / rdir;
+    wave_sync_lds();                                  // the wave's LDS slots are reused next
   }
 }
 
-// deterministic sum of the per-voxel losses of all levels into loss[0]: fixed per-block chunks
-// of every level, then one block adds the block sums in order
+// deterministic sum, in FP64, of the per-voxel losses of all levels into loss[0]: fixed per-block
+// chunks of every level, then one block adds the block sums in order
 struct LossLevels {
   const float* p[24];
   const int64_t* n[24];
@@ -139,43 +176,44 @@ struct LossLevels {
   int count;
 };
 
-__global__ void __launch_bounds__(kBlock) k_fit_partial(LossLevels lv, float* __restrict__ part) {
-  __shared__ float red[kWaves];
-  float acc = 0.f;
+__global__ void __launch_bounds__(kBlock) k_fit_partial(LossLevels lv, double* __restrict__ part) {
+  __shared__ double red[kWaves];
+  double acc = 0.0;
   for (int i = 0; i < lv.count; ++i) {
     const int64_t n = *lv.n[i] < lv.rows[i] ? *lv.n[i] : lv.rows[i];
     const int64_t chunk = (n + kGrid - 1) / kGrid;
     const int64_t b0 = int64_t(blockIdx.x) * chunk, b1 = b0 + chunk < n ? b0 + chunk : n;
-    for (int64_t j = b0 + threadIdx.x; j < b1; j += kBlock) acc += lv.p[i][j];
+    for (int64_t j = b0 + threadIdx.x; j < b1; j += kBlock) acc += double(lv.p[i][j]);
   }
   acc = wave_sum(acc);
   if (lane_id() == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
   if (threadIdx.x == 0) {
-    float t = 0.f;
+    double t = 0.0;
     for (int w = 0; w < kWaves; ++w) t += red[w];
     part[blockIdx.x] = t;
   }
 }
 
-__global__ void __launch_bounds__(1024) k_fit_total(const float* __restrict__ part, float* loss) {
-  __shared__ float red[16];
-  float acc = threadIdx.x < kGrid ? part[threadIdx.x] : 0.f;
+__global__ void __launch_bounds__(1024) k_fit_total(const double* __restrict__ part, float* loss) {
+  __shared__ double red[16];
+  double acc = threadIdx.x < kGrid ? part[threadIdx.x] : 0.0;
   acc = wave_sum(acc);
   if (lane_id() == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
   if (threadIdx.x == 0) {
-    float t = 0.f;
+    double t = 0.0;
     for (int w = 0; w < 16; ++w) t += red[w];
-    loss[0] = t;
+    loss[0] = float(t);
   }
 }
 
 // ---------------------------------------------------------------------------------------------
 // backward per voxel: lobe gradients and the gradient of the target w.r.t. the children's sums.
 // FP64: the derivative of the target along a child's own (w, S) direction nearly cancels (the
-// target is invariant when all children scale alike), so the parts must be accurate.
-// gch: [7][gcap] (S components, then w) for the level below.  DPL: directions per lane.
+// target is invariant when all children scale alike), so the parts must be accurate.  Bound by
+// FP64 arithmetic (the workload of the forward: 0.97 ms; with sixteen lanes per voxel, whose children
+// were evaluated again for their gradients and summed over the lanes by LDS permutes, 2.46 ms).
 // ---------------------------------------------------------------------------------------------
 // 1 / sqrt(x), x > 0: the hardware estimate refined by one Newton step,
 // r' = r (3/2 - x r^2 / 2), which squares the estimate's relative error
@@ -184,154 +222,192 @@ __device__ __forceinline__ double rsqrt_nr(double x) {
   const double h = 0.5 * x * r;
   return fma(r, fma(-h, r, 0.5), r);
 }
-// sqrt(x) for x >= 0 as x / sqrt(x)
-__device__ __forceinline__ double sqrt_nr(double x) { return x > 0.0 ? x * rsqrt_nr(x) : 0.0; }
 
-__device__ __forceinline__ double quadd(const double* S, double x, double y, double z) {
-  return S[0] * x * x + S[1] * y * y + S[2] * z * z + 2.0 * (S[3] * x * y + S[4] * x * z + S[5] * y * z);
+// cross-lane moves of a double: a DPP pattern; v_permlane{16,32}_swap of a and b, added
+template <int CTRL>
+__device__ __forceinline__ double dpp64(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e, kDppHalfMirror = 0x141, kDppRor8 = 0x128;
+__device__ __forceinline__ double swap_add32(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ double swap_add16(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// sum over eight lanes / a row of sixteen, in every lane of them
+__device__ __forceinline__ double sum8(double v) {
+  v += dpp64<kDppXor1>(v);
+  v += dpp64<kDppXor2>(v);
+  return v + dpp64<kDppHalfMirror>(v);
+}
+__device__ __forceinline__ double sum16(double v) { return sum8(v + dpp64<kDppRor8>(v)); }
+// sums of eight values over the wave: lane l gets that of value 4 * bit 5 + 2 * bit 4 + bit 3 of l.
+// Each step halves the values a lane still carries, where a butterfly per value would add all.
+__device__ __forceinline__ double wave_sum8(const double v[8], int lane) {
+  double a[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a[i] = swap_add32(v[i], v[i + 4]);
+  const double b0 = swap_add16(a[0], a[2]), b1 = swap_add16(a[1], a[3]);
+  const bool up = lane & 8;
+  const double mine = up ? b1 : b0, other = up ? b0 : b1;
+  return sum8(mine + dpp64<kDppRor8>(other));
+}
+// sums of four values: lane l gets that of value 2 * bit 5 + bit 4 of l
+__device__ __forceinline__ double wave_sum4(const double v[4]) {
+  return sum16(swap_add16(swap_add32(v[0], v[2]), swap_add32(v[1], v[3])));
 }
 
 template <int DPL>
-__global__ void __launch_bounds__(kBlock) k_fit_bwd(vx_voxels par, const int64_t* n_par_p, int64_t rows,
-                                                    const double* __restrict__ c64, int64_t ccap,
-                                                    const int64_t* __restrict__ cstart, const float* __restrict__ Lp,
-                                                    const float* __restrict__ dirs, int ndir,
-                                                    const float* __restrict__ dloss, float* __restrict__ dLp,
-                                                    double* __restrict__ gch, int64_t gcap) {
-  // directions and the children's FP64 sums staged once, not converted in the inner loops
-  __shared__ double sdir[kMaxDir][3];
-  __shared__ double scw[kGroups][kMaxChild];
-  __shared__ double scS[kGroups][kMaxChild][6];
-  for (int k = threadIdx.x; k < ndir; k += kBlock)
-    for (int a = 0; a < 3; ++a) sdir[k][a] = dirs[3 * k + a];
-  __syncthreads();
-  const int grp = threadIdx.x / kGroup, gl = threadIdx.x % kGroup;
-  const int64_t n_par = *n_par_p < rows ? *n_par_p : rows;
-  const double g0 = double(dloss[0]);
-  const double g2 = 2.0 / double(ndir) * g0;
-  const int wgrp0 = (threadIdx.x >> 6) * (64 / kGroup);
-  for (int64_t u0 = int64_t(blockIdx.x) * kGroups + wgrp0; u0 < n_par; u0 += int64_t(gridDim.x) * kGroups) {
-    const int64_t u = u0 + (grp - wgrp0);
-    const bool in = u < n_par;
-    const float Wf = in ? par.w[u] : 0.f;
-    const bool active = in && Wf > 0.f && c64 != nullptr;   // no FP64 sums: no points, nothing to fit
-    int64_t first = 0;
-    int nc = 0;
-    if (active) nc = child_range(cstart, u, first);
-    if (active && gl < nc) {
-      const int64_t cc = first + gl;
-      scw[grp][gl] = c64[6 * ccap + cc];
+__global__ void __launch_bounds__(kBlock, DPL <= 2 ? 3 : 1) k_fit_bwd(FitLevels lv, const float* __restrict__ dirs, int ndir,
+                                                    const float* __restrict__ dloss) {
+  // per child: S and w; later sqrt(w) and 1 / (2 sqrt(w)) in the last two, the gradients in the first seven
+  __shared__ double stage[kWaves][kMaxChild][8];
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double(*st)[8] = stage[wv];
+  double x[DPL][3], m[DPL][6];
 #pragma unroll
-      for (int t = 0; t < 6; ++t) scS[grp][gl][t] = c64[int64_t(t) * ccap + cc];
+  for (int i = 0; i < DPL; ++i) dir_products(dirs, ndir, lane + 64 * i, x[i], m[i]);
+  const double g2 = 2.0 / double(ndir) * double(dloss[0]);
+  const int lt = lane >> 3, lc = lane & 7;
+  for (int64_t i0 = int64_t(blockIdx.x) * kWaves + wv;; i0 += int64_t(gridDim.x) * kWaves) {
+    int64_t u = i0;
+    int L;
+    if (!fit_level(lv, u, L)) return;
+    const FitLevel& F = lv.l[L];
+    const bool fitted = u < F.rows;
+    const bool active = fitted && F.w[u] > 0.f && F.c64 != nullptr;   // no FP64 sums: no points, nothing to fit
+    const int64_t first = F.cstart[u], nch = F.cstart[u + 1] - first;
+    const int nc = int(nch < kMaxChild ? nch : kMaxChild);
+    if (!active) {
+      if (fitted && lane < 12) F.dLp[u * 12 + lane] = 0.f;
+      if (lc < nc && lt < 7) F.gch[int64_t(lt) * F.gcap + first + lc] = 0.0;
+      continue;
     }
-    wave_sync_lds();
-    const double* cw = scw[grp];
-    double l[12], gl12[12], dg[DPL], dt[DPL];
-#pragma unroll
-    for (int t = 0; t < 12; ++t) {
-      l[t] = active ? double(Lp[u * 12 + t]) : 0.0;
-      gl12[t] = 0.0;
+    // lane 8 t + c: component t of child c (w in the last two rows, as its root and half its reciprocal)
+    double wc = 0.0;
+    if (lc < nc) {
+      const double v = F.c64[int64_t(lt < 6 ? lt : 6) * F.gcap + first + lc];
+      wc = v;
+      const double r = v > 0.0 ? rsqrt_nr(v) : 0.0;
+      st[lc][lt] = lt < 6 ? v : lt == 6 ? v * r : 0.5 * r;
     }
     // the parent's weight as the FP64 sum of its children's
-    double Wd = 0.0;
-    for (int c = 0; c < nc; ++c) Wd += cw[c];
-    const double invW = active && Wd > 0.0 ? 1.0 / Wd : 0.0;
-    // pass 1 (this lane's directions): target, fit, residual; lobe gradients
+    const double Ws = sum8(wc);
+    const double Wd = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(Ws), 48),
+                                       __builtin_amdgcn_readlane(__double2loint(Ws), 48));
+    const double invW = Wd > 0.0 ? 1.0 / Wd : 0.0;
+    wave_sync_lds();
+    // pass 1: the target, with every child's root s and 1 / s kept
+    double s[kMaxChild][DPL], r[kMaxChild][DPL], tau[DPL], g[DPL];
+#pragma unroll
+    for (int i = 0; i < DPL; ++i) tau[i] = 0.0;
+#pragma unroll
+    for (int c = 0; c < kMaxChild; ++c) {
+      if (c >= nc) continue;
+      double S[6];
+#pragma unroll
+      for (int t = 0; t < 6; ++t) S[t] = st[c][t];
+      const double sw = st[c][6];
+#pragma unroll
+      for (int i = 0; i < DPL; ++i) {
+        const double q = quad(S, m[i]);
+        r[c][i] = q > 0.0 ? rsqrt_nr(q) : 0.0;
+        s[c][i] = q * r[c][i];
+        tau[i] = fma(sw, s[c][i], tau[i]);
+      }
+    }
+    // fit, residual and lobe gradients
+    double gl[12];
+#pragma unroll
+    for (int t = 0; t < 12; ++t) gl[t] = 0.0;
 #pragma unroll
     for (int i = 0; i < DPL; ++i) {
-      const int k = gl + kGroup * i;
-      dg[i] = 0.0;
-      dt[i] = 0.0;
-      if (!active || k >= ndir) continue;
-      const double x = sdir[k][0], y = sdir[k][1], z = sdir[k][2];
-      double tau = 0.0;
-      for (int c = 0; c < nc; ++c) {
-        const double wc = double(cw[c]);
-        if (!(wc > 0.0)) continue;
-        tau += sqrt_nr(fmax(wc * quadd(scS[grp][c], x, y, z), 0.0));
-      }
-      tau *= invW;
-      double f = 0.0, yv[2][3], ry[2];
+      tau[i] *= invW;
+      double f = 0.0, y[2][3], ry[2];
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const double* lj = l + 6 * j;
-        yv[j][0] = lj[0] * x + lj[1] * y + lj[3] * z;
-        yv[j][1] = lj[2] * y + lj[4] * z;
-        yv[j][2] = lj[5] * z;
-        const double n2 = yv[j][0] * yv[j][0] + yv[j][1] * yv[j][1] + yv[j][2] * yv[j][2];
+        const float* lj = F.Lp + u * 12 + 6 * j;
+        y[j][0] = double(lj[0]) * x[i][0] + double(lj[1]) * x[i][1] + double(lj[3]) * x[i][2];
+        y[j][1] = double(lj[2]) * x[i][1] + double(lj[4]) * x[i][2];
+        y[j][2] = double(lj[5]) * x[i][2];
+        const double n2 = y[j][0] * y[j][0] + y[j][1] * y[j][1] + y[j][2] * y[j][2];
         ry[j] = n2 > 0.0 ? rsqrt_nr(n2) : 0.0;                 // 1 / |L_j^T w|
         f += n2 * ry[j];
       }
-      const double g = (f - tau) * g2;                          // d loss / d f;  d loss / d tau = -g
-      dg[i] = g;
-      dt[i] = tau;
+      g[i] = (f - tau[i]) * g2;                                 // d loss / d f;  d loss / d tau = -g
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        if (!(ry[j] > 0.0)) continue;
-        const double sj = g * ry[j];
-        double* gj = gl12 + 6 * j;
-        gj[0] += sj * yv[j][0] * x;
-        gj[1] += sj * yv[j][0] * y;
-        gj[2] += sj * yv[j][1] * y;
-        gj[3] += sj * yv[j][0] * z;
-        gj[4] += sj * yv[j][1] * z;
-        gj[5] += sj * yv[j][2] * z;
+        const double sj = g[i] * ry[j];
+        const double a0 = sj * y[j][0], a1 = sj * y[j][1], a2 = sj * y[j][2];
+        double* gj = gl + 6 * j;
+        gj[0] = fma(a0, x[i][0], gj[0]);
+        gj[1] = fma(a0, x[i][1], gj[1]);
+        gj[2] = fma(a1, x[i][1], gj[2]);
+        gj[3] = fma(a0, x[i][2], gj[3]);
+        gj[4] = fma(a1, x[i][2], gj[4]);
+        gj[5] = fma(a2, x[i][2], gj[5]);
       }
     }
-#pragma unroll
-    for (int t = 0; t < 12; ++t) {
-      const double v = group_sum(gl12[t]);
-      if (active && gl == t) dLp[u * 12 + t] = float(v);
+    {
+      const double v8 = wave_sum8(gl, lane), v4 = wave_sum4(gl + 8);
+      if (lc == 0) F.dLp[u * 12 + lt] = float(v8);
+      if ((lane & 15) == 0) F.dLp[u * 12 + 8 + (lane >> 4)] = float(v4);
     }
-    if (in && !active && gl < 12) dLp[u * 12 + gl] = 0.f;
-    // pass 2 (one child at a time): d loss / d (S_c, w_c)
+    // pass 2: d loss / d (S_c, w_c).  d tau / d (w^T S_c w) = sqrt(w_c) / (2 s) / W and
+    // d tau / d w_c = (s / (2 sqrt(w_c)) - tau) / W
+#pragma unroll
     for (int c = 0; c < kMaxChild; ++c) {
-      if (!__any(active && c < nc)) break;                 // uniform over the wave
-      double acc[7] = {0, 0, 0, 0, 0, 0, 0};
-      const bool on = active && c < nc;
-      const double wc = on ? double(cw[c]) : 0.0;
-      if (on && wc > 0.0) {
+      if (c >= nc) continue;
+      const double sw = st[c][6], hs = st[c][7];
+      double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-        for (int i = 0; i < DPL; ++i) {
-          const int k = gl + kGroup * i;
-          if (k >= ndir) continue;
-          const double x = sdir[k][0], y = sdir[k][1], z = sdir[k][2], g = dg[i];
-          const double qs = quadd(scS[grp][c], x, y, z);
-          const double q2 = wc * qs;
-          double dw = -dt[i] * invW;
-          if (q2 > 0.0) {
-            const double h = 0.5 * rsqrt_nr(q2) * invW;         // 1 / (2 sqrt(w_c w^T S_c w)) / W
-            const double k2 = -g * wc * h;                      // d loss / d (w^T S_c w)
-            acc[0] += k2 * x * x;
-            acc[1] += k2 * y * y;
-            acc[2] += k2 * z * z;
-            acc[3] += k2 * 2.0 * x * y;
-            acc[4] += k2 * 2.0 * x * z;
-            acc[5] += k2 * 2.0 * y * z;
-            dw += qs * h;
-          }
-          acc[6] += -g * dw;
-        }
-      }
+      for (int i = 0; i < DPL; ++i) {
+        const double gr = g[i] * r[c][i];
 #pragma unroll
-      for (int t = 0; t < 7; ++t) {
-        const double v = group_sum(acc[t]);
-        if (on && gl == t) gch[int64_t(t) * gcap + first + c] = v;
+        for (int t = 0; t < 6; ++t) acc[t] = fma(gr, m[i][t], acc[t]);
+        acc[6] = fma(g[i], fma(hs, s[c][i], -tau[i]), acc[6]);
       }
+      const double v = wave_sum8(acc, lane) * -invW * (lt < 6 ? 0.5 * sw : sw > 0.0 ? 1.0 : 0.0);
+      wave_sync_lds();
+      if (lc == 0) st[c][lt] = v;                               // (the eighth is not read)
     }
-    wave_sync_lds();                                  // the group's LDS slots are reused next
+    wave_sync_lds();
+    if (lc < nc && lt < 7) F.gch[int64_t(lt) * F.gcap + first + lc] = st[lc][lt];
+    wave_sync_lds();                                  // the wave's LDS slots are reused next
   }
 }
 
-// top-down: every voxel of level L adds its parent's accumulated gradient (level L+1)
-__global__ void __launch_bounds__(kBlock) k_fit_down(const int32_t* __restrict__ pidx, const int64_t* n_p,
-                                                     double* __restrict__ g, int64_t gcap,
-                                                     const double* __restrict__ gup, int64_t gupcap) {
+// the leaf's gradients: its own and those of all its ancestors, added from the top down (levels
+// below the first fitted one hold none).  One pass over the leaf instead of one per level.
+struct FitDown {
+  const int32_t* pidx[kMaxFit];    // index of every voxel's parent
+  double* g[kMaxFit];              // [7][gcap]
+  int64_t gcap[kMaxFit];
+  int lo, hi;                      // levels lo .. hi - 1 hold gradients
+};
+__global__ void __launch_bounds__(kBlock) k_fit_down(FitDown d, const int64_t* n_p) {
   const int64_t n = *n_p;
   for (int64_t c = int64_t(blockIdx.x) * kBlock + threadIdx.x; c < n; c += int64_t(gridDim.x) * kBlock) {
-    const int64_t p = pidx[c];
+    int32_t at[kMaxFit];
+    at[0] = int32_t(c);
 #pragma unroll
-    for (int t = 0; t < 7; ++t) g[int64_t(t) * gcap + c] += gup[int64_t(t) * gupcap + p];
+    for (int L = 1; L < kMaxFit; ++L)
+      if (L < d.hi) at[L] = d.pidx[L - 1][at[L - 1]];
+    double acc[7] = {0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int L = kMaxFit - 1; L >= 0; --L)
+      if (L < d.hi && L >= d.lo)
+#pragma unroll
+        for (int t = 0; t < 7; ++t) acc[t] = d.g[L][int64_t(t) * d.gcap[L] + at[L]] + acc[t];
+#pragma unroll
+    for (int t = 0; t < 7; ++t) d.g[0][int64_t(t) * d.gcap[0] + c] = acc[t];
   }
 }
 
@@ -348,7 +424,9 @@ __global__ void __launch_bounds__(kBlock) k_tile_index(const Key* __restrict__ k
 }
 
 // per segment: chain rule over its (segment, voxel) pairs, which the front half emitted
-// contiguously in primitive order; seg_grad[p] = (d/dA, d/dB) in world units
+// contiguously in primitive order; seg_grad[p] = (d/dA, d/dB) in world units.  Sixteen lanes take a
+// segment's pairs: each pair is a chain of dependent lookups, and one thread a segment left too few of
+// them in flight (128,000 segments, 3.2 M pairs: 0.109 ms; one thread a segment 0.212 ms).
 template <class Key>
 __global__ void __launch_bounds__(kBlock) k_fit_pairs(const int32_t* __restrict__ rec,
                                                       const int64_t* __restrict__ cand_off, int64_t n_prims,
@@ -357,14 +435,17 @@ __global__ void __launch_bounds__(kBlock) k_fit_pairs(const int32_t* __restrict_
                                                       const int64_t* __restrict__ ctl, const Key* __restrict__ pkeys,
                                                       vx_voxels leaf, const int64_t* n_leaf_p,
                                                       const double* __restrict__ gleaf, int64_t gcap, int Sb,
-                                                      int log2R, double vs, const int64_t* __restrict__ tfirst,
+                                                      double vs, const int64_t* __restrict__ tfirst,
                                                       const int64_t* __restrict__ tend, double* __restrict__ seg_grad) {
   const int64_t n_leaf = *n_leaf_p;
   const int64_t n_cand = ctl[CTL_N_CAND];
   const int64_t n_pairs = ctl[CTL_N_PAIRS];
   const Key* lk = reinterpret_cast<const Key*>(leaf.keys);
   const double inv_s = 1.0 / double(int64_t(1) << Sb);
-  for (int64_t p = int64_t(blockIdx.x) * kBlock + threadIdx.x; p < n_prims; p += int64_t(gridDim.x) * kBlock) {
+  const int gl = threadIdx.x & 15;
+  constexpr int kSegs = kBlock / 16;
+  // all lanes of a group take the same branches down to the loop over its pairs
+  for (int64_t p = int64_t(blockIdx.x) * kSegs + (threadIdx.x >> 4); p < n_prims; p += int64_t(gridDim.x) * kSegs) {
     double gA[3] = {0, 0, 0}, gB[3] = {0, 0, 0};
     const int64_t c0 = cand_off[p], c1 = cand_off[p + 1];
     if (c1 > c0 && c1 <= n_cand) {
@@ -388,11 +469,9 @@ __global__ void __launch_bounds__(kBlock) k_fit_pairs(const int32_t* __restrict_
         for (int a = 0; a < 3; ++a) t[a] = d[a] / len;
       const double M[6] = {1 - t[0] * t[0], 1 - t[1] * t[1], 1 - t[2] * t[2], -t[0] * t[1], -t[0] * t[2], -t[1] * t[2]};
       double gM[6] = {0, 0, 0, 0, 0, 0};
-      for (int64_t j = j0; j < j1; ++j) {
+      for (int64_t j = j0 + gl; j < j1; j += 16) {
         const uint64_t key = uint64_t(pkeys[j]);
-        double lo[3] = {0, 0, 0};
-        for (int b = 0; b < log2R; ++b)
-          for (int a = 0; a < 3; ++a) lo[a] += double((key >> (3 * b + a)) & 1) * double(int64_t(1) << b);
+        const double lo[3] = {double(compact3(key)), double(compact3(key >> 1)), double(compact3(key >> 2))};
         double dA[3], dB[3];
         const double w = seg_length_grad(A, B, lo, dA, dB);
         if (!(w > 0.0)) continue;
@@ -418,6 +497,13 @@ __global__ void __launch_bounds__(kBlock) k_fit_pairs(const int32_t* __restrict_
           gB[a] += gw * dB[a];
         }
       }
+#pragma unroll
+      for (int q = 0; q < 6; ++q) gM[q] = sum16(gM[q]);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        gA[a] = sum16(gA[a]);
+        gB[a] = sum16(gB[a]);
+      }
       if (len > 0) {
         double gt[3];
         gt[0] = -2 * t[0] * gM[0] - t[1] * gM[3] - t[2] * gM[4];
@@ -431,9 +517,11 @@ __global__ void __launch_bounds__(kBlock) k_fit_pairs(const int32_t* __restrict_
         }
       }
     }
-    for (int a = 0; a < 3; ++a) {
-      seg_grad[p * 6 + a] = gA[a] * vs;
-      seg_grad[p * 6 + 3 + a] = gB[a] * vs;
+    if (gl < 6) {
+      double v = gA[0];
+#pragma unroll
+      for (int a = 1; a < 6; ++a) v = gl == a ? (a < 3 ? gA[a] : gB[a - 3]) : v;
+      seg_grad[p * 6 + gl] = v * vs;
     }
   }
 }
@@ -445,11 +533,6 @@ __global__ void __launch_bounds__(kBlock) k_fit_points(const double* __restrict_
   for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += int64_t(gridDim.x) * kBlock)
     for (int a = 0; a < 3; ++a)
       dpts[i * 3 + a] = float(seg_grad[i * 6 + a] + (i > 0 ? seg_grad[(i - 1) * 6 + 3 + a] : 0.0));
-}
-
-__global__ void k_fill_f64(double* p, int64_t n, double v) {
-  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x)
-    p[i] = v;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -507,7 +590,7 @@ template <class Key>
 __global__ void __launch_bounds__(kBlock) k_fit_leaf64(const Key* __restrict__ pkeys, const uint32_t* __restrict__ pprim,
                                                        const int64_t* __restrict__ sstart, const int32_t* __restrict__ rec,
                                                        const Key* __restrict__ lkeys, const int64_t* n_leaf_p,
-                                                       int64_t cap, int Sb, int log2R, double* __restrict__ out,
+                                                       int64_t cap, int Sb, double* __restrict__ out,
                                                        int64_t* stats) {
   // within the leaf, its capacity and the keys the pairs hold (sstart[i + 1] is written for i < n)
   int64_t n = *n_leaf_p < cap ? *n_leaf_p : cap;
@@ -519,9 +602,7 @@ __global__ void __launch_bounds__(kBlock) k_fit_leaf64(const Key* __restrict__ p
     if (b > a && pkeys[a] != lkeys[i])
       atomicOr(reinterpret_cast<unsigned long long*>(stats + VX_STAT_FLAGS), (unsigned long long)VX_FLAG_FIT_KEYS);
     const uint64_t key = uint64_t(lkeys[i]);
-    double lo[3] = {0, 0, 0};
-    for (int bit = 0; bit < log2R; ++bit)
-      for (int ax = 0; ax < 3; ++ax) lo[ax] += double((key >> (3 * bit + ax)) & 1) * double(int64_t(1) << bit);
+    const double lo[3] = {double(compact3(key)), double(compact3(key >> 1)), double(compact3(key >> 2))};
     for (int64_t j = a; j < b; ++j) {
       const int32_t* r = rec + int64_t(pprim[j]) * kRec;
       double A[3], B[3], d[3], gA[3], gB[3];
@@ -573,7 +654,7 @@ struct FitWs {
   int32_t* pidx[21];       // [cap_L] per level 0..hi-1: index of every voxel's parent in level L+1
   int64_t* tfirst;         // [tiles] leaf lookup: first and end leaf index of every 16^3 tile
   int64_t* tend;
-  float* part;             // [kGrid] block sums of the loss
+  double* part;            // [kGrid] block sums of the loss
   int64_t* partial;        // [kGrid + 1] scan partials
   double* seg_grad;        // [n_pts][6] d loss / d (segment start, segment end), world units
   FrontWs f;
@@ -600,7 +681,7 @@ static size_t fit_ws_layout(int64_t n_pts, int64_t max_cand, int64_t max_pairs, 
   const int64_t tiles = leaf_tiles(log2R);
   x.tfirst = cv.take<int64_t>(tiles);
   x.tend = cv.take<int64_t>(tiles);
-  x.part = cv.take<float>(kGrid);
+  x.part = cv.take<double>(kGrid);
   x.partial = cv.take<int64_t>(kGrid + 1);
   x.seg_grad = cv.take<double>(6 * n_pts);
   front_ws_carve(cv, n_pts, max_cand, max_pairs, key64, &x.f);
@@ -621,37 +702,62 @@ size_t fit_ws_bytes(int64_t n_pts, int64_t max_cand, int64_t max_pairs, const in
   return fit_ws_layout(n_pts, max_cand, max_pairs, caps, hi, log2R, nullptr, nullptr);
 }
 
-struct StartTotal {
-  int64_t* start;
-  __device__ void operator()(int64_t total, int64_t n) const { start[total] = n; }
-};
-// heads of the parent key: the parent's first child, and every child's parent index
-struct ChildOut {
-  int64_t* start;
-  int32_t* parent;
-  __device__ void operator()(int64_t i, int64_t ex, int64_t v) const {
-    if (v) start[ex] = i;
-    parent[i] = int32_t(ex + v - 1);
-  }
-};
+static int blocks_for(int64_t n, int64_t most = kGrid) {
+  const int64_t b = (n + kBlock - 1) / kBlock;
+  return int(b < 1 ? 1 : (b > most ? most : b));
+}
 
-// first child of every voxel of levels 1..hi: heads of the parent key over each level below
-static void child_starts(bool key64, const vx_voxels* levels, const int64_t* n_levels, int hi, const FitWs& w,
-                         hipStream_t s) {
-  VX_TIMED("fit_children", s);
-  for (int L = 1; L <= hi; ++L) {
-    if (key64)
-      device_scan(HeadIn<uint64_t, 3>{(const uint64_t*)levels[L - 1].keys}, ChildOut{w.cstart[L], w.pidx[L - 1]},
-                  StartTotal{w.cstart[L]}, n_levels + L - 1, 0, w.partial, s);
-    else
-      device_scan(HeadIn<uint32_t, 3>{(const uint32_t*)levels[L - 1].keys}, ChildOut{w.cstart[L], w.pidx[L - 1]},
-                  StartTotal{w.cstart[L]}, n_levels + L - 1, 0, w.partial, s);
+// first child of every voxel of levels 1..hi, and every child's parent, all levels in one launch: a
+// voxel searches the level below for its first child (at its own index at the earliest, as each
+// voxel before it has one, and at eight times that at the latest) and takes the run from there.
+// (0.69 M voxels in six levels: 33 us; as two scans a level 56 us)
+struct ChildLevels {
+  const void* keys[kMaxFit + 1];      // per level 0..hi
+  const int64_t* n[kMaxFit + 1];
+  int64_t* cstart[kMaxFit + 1];       // per level 1..hi
+  int32_t* pidx[kMaxFit + 1];         // per level 0..hi-1
+  int hi;
+};
+template <class Key>
+__global__ void __launch_bounds__(kBlock) k_fit_children(ChildLevels lv) {
+  for (int64_t i0 = int64_t(blockIdx.x) * kBlock + threadIdx.x;; i0 += int64_t(gridDim.x) * kBlock) {
+    int64_t u = i0, n = 0;
+    int L = 1;
+    for (; L <= lv.hi; ++L) {
+      n = *lv.n[L];
+      if (u <= n) break;              // one more for the end
+      u -= n + 1;
+    }
+    if (L > lv.hi) return;
+    const Key* ck = static_cast<const Key*>(lv.keys[L - 1]);
+    const int64_t nc = *lv.n[L - 1];
+    if (u == n) {
+      lv.cstart[L][n] = nc;
+      continue;
+    }
+    const uint64_t key = uint64_t(static_cast<const Key*>(lv.keys[L])[u]);
+    const int64_t lo = u < nc ? u : nc, hi = 8 * u < nc ? 8 * u : nc;
+    int64_t c = lo + key_lower_bound(ck + lo, hi - lo, key << 3);
+    lv.cstart[L][u] = c;
+    for (; c < nc && uint64_t(ck[c]) >> 3 == key; ++c) lv.pidx[L - 1][c] = int32_t(u);
   }
 }
 
-static int blocks_for(int64_t n) {
-  const int64_t b = (n + kBlock - 1) / kBlock;
-  return int(b < 1 ? 1 : (b > kGrid ? kGrid : b));
+static void child_starts(bool key64, const vx_voxels* levels, const int64_t* n_levels, int hi, const FitWs& w,
+                         const int64_t* caps, hipStream_t s) {
+  VX_TIMED("fit_children", s);
+  ChildLevels lv;
+  lv.hi = hi;
+  int64_t most = 0;
+  for (int L = 0; L <= hi; ++L) {
+    lv.keys[L] = levels[L].keys;
+    lv.n[L] = n_levels + L;
+    lv.cstart[L] = L >= 1 ? w.cstart[L] : nullptr;
+    lv.pidx[L] = L < hi ? w.pidx[L] : nullptr;
+    if (L >= 1) most += caps[L] + 1;
+  }
+  if (key64) hipLaunchKernelGGL(k_fit_children<uint64_t>, dim3(blocks_for(most, 4 * kGrid)), dim3(kBlock), 0, s, lv);
+  else hipLaunchKernelGGL(k_fit_children<uint32_t>, dim3(blocks_for(most, 4 * kGrid)), dim3(kBlock), 0, s, lv);
 }
 
 template <class Key>
@@ -663,6 +769,46 @@ static void bind_check(const vx_voxels* levels, const int64_t* n_levels, int lo,
                        bound ? (const Key*)bound[L - lo] : (const Key*)nullptr, stats);
 }
 
+// the fitted levels as the kernels take them
+static FitLevels fit_levels(const vx_voxels* levels, const int64_t* n_levels, int lo, int hi,
+                            const float* const* params, float* const* dparams, const int64_t* rows, const FitWs& w,
+                            const int64_t* caps, bool sums64) {
+  FitLevels lv{};
+  for (int L = lo; L <= hi; ++L) {
+    FitLevel& F = lv.l[lv.count++];
+    F.n = n_levels + L;
+    F.rows = rows[L - lo];
+    F.w = levels[L].w;
+    F.cstart = w.cstart[L];
+    F.Lp = params[L - lo];
+    F.chw = levels[L - 1].w;
+    F.chS = levels[L - 1].S;
+    F.chcap = levels[L - 1].cap;
+    F.loss = w.loss_vox[L];
+    F.c64 = sums64 ? w.s64[L - 1] : nullptr;
+    F.gch = w.g[L - 1];
+    F.gcap = caps[L - 1];
+    F.dLp = dparams ? dparams[L - lo] : nullptr;
+  }
+  return lv;
+}
+
+// directions per lane: the set in one, two or four rows of 64
+template <class F>
+static void with_dirs(int ndir, F&& launch) {
+  if (ndir <= 64) launch(std::integral_constant<int, 1>());
+  else if (ndir <= 128) launch(std::integral_constant<int, 2>());
+  else launch(std::integral_constant<int, 4>());
+}
+
+// one wave per voxel, up to as many as the chip holds at a time
+static int fit_blocks(const int64_t* rows, int levels) {
+  int64_t n = 0;
+  for (int i = 0; i < levels; ++i) n += rows[i];
+  const int64_t b = (n + kWaves - 1) / kWaves;
+  return int(b < 1 ? 1 : (b > kFitGrid ? kFitGrid : b));
+}
+
 vx_status fit_forward_run(const vx_grid* g, const vx_voxels* levels, const int64_t* n_levels, int lo, int hi,
                           const float* const* params, const int64_t* rows, const void* const* bound, const float* dirs,
                           int ndir, float* loss, int64_t* stats, void* ws, const int64_t* caps, hipStream_t s) {
@@ -672,17 +818,21 @@ vx_status fit_forward_run(const vx_grid* g, const vx_voxels* levels, const int64
   launch_fill_i64(stats, VX_NSTAT, 0, s);
   if (key64) bind_check<uint64_t>(levels, n_levels, lo, hi, rows, bound, stats, s);
   else bind_check<uint32_t>(levels, n_levels, lo, hi, rows, bound, stats, s);
-  child_starts(key64, levels, n_levels, hi, w, s);
+  child_starts(key64, levels, n_levels, hi, w, caps, s);
   LossLevels ll;
   ll.count = 0;
-  for (int L = lo; L <= hi; ++L) {
-    VX_TIMED("fit_fwd", s);
-    hipLaunchKernelGGL(k_fit_fwd, dim3(kGrid), dim3(kBlock), 0, s, levels[L], n_levels + L, rows[L - lo],
-                       levels[L - 1], w.cstart[L], params[L - lo], dirs, ndir, w.loss_vox[L]);
-    ll.p[ll.count] = w.loss_vox[L];
-    ll.n[ll.count] = n_levels + L;
-    ll.rows[ll.count] = rows[L - lo];
+  const FitLevels lv = fit_levels(levels, n_levels, lo, hi, params, nullptr, rows, w, caps, false);
+  for (int i = 0; i < lv.count; ++i) {
+    ll.p[i] = lv.l[i].loss;
+    ll.n[i] = lv.l[i].n;
+    ll.rows[i] = lv.l[i].rows;
     ++ll.count;
+  }
+  {
+    VX_TIMED("fit_fwd", s);
+    with_dirs(ndir, [&](auto dpl) {
+      hipLaunchKernelGGL(k_fit_fwd<dpl.value>, dim3(fit_blocks(rows, hi - lo + 1)), dim3(kBlock), 0, s, lv, dirs, ndir);
+    });
   }
   VX_TIMED("fit_total", s);
   hipLaunchKernelGGL(k_fit_partial, dim3(kGrid), dim3(kBlock), 0, s, ll, w.part);
@@ -701,8 +851,8 @@ static void level_sums64(const vx_grid* g, const vx_voxels* levels, const int64_
   device_scan(HeadIn<Key, 0>{(const Key*)P.keys}, LeafSegOut{w.sstart, caps[0]},
               LeafSegTotal{w.sstart, caps[0], n_levels, stats}, w.f.ctl + CTL_N_PAIRS, 0, w.partial, s);
   const Lat lat = make_lat(g, 1, 0.0f);
-  hipLaunchKernelGGL(k_fit_leaf64<Key>, dim3(kGrid), dim3(kBlock), 0, s, (const Key*)P.keys, P.prim, w.sstart,
-                     w.f.rec, (const Key*)levels[0].keys, n_levels, caps[0], lat.Sb, g->log2_res, w.s64[0], stats);
+  hipLaunchKernelGGL(k_fit_leaf64<Key>, dim3(blocks_for(caps[0], 4 * kGrid)), dim3(kBlock), 0, s, (const Key*)P.keys, P.prim, w.sstart,
+                     w.f.rec, (const Key*)levels[0].keys, n_levels, caps[0], lat.Sb, w.s64[0], stats);
   for (int L = 1; L < hi; ++L)
     hipLaunchKernelGGL(k_fit_up64, dim3(kGrid), dim3(kBlock), 0, s, w.cstart[L], n_levels + L, caps[L],
                        w.s64[L - 1], caps[L - 1], w.s64[L]);
@@ -717,35 +867,37 @@ vx_status fit_backward_run(const vx_grid* g, const float* pts, int64_t n_pts, co
   const bool key64 = g->log2_res > 10;
   FitWs w;
   fit_ws_layout(n_pts, max_cand, max_pairs, caps, hi, g->log2_res, ws, &w);
-  for (int L = 0; L < hi; ++L)
-    hipLaunchKernelGGL(k_fill_f64, dim3(blocks_for(7 * caps[L])), dim3(kBlock), 0, s, w.g[L], 7 * caps[L], 0.0);
   // re-emit the pairs in primitive order (this clears stats), then check the parameters' binding
   voxelize_front(1, g, pts, n_pts, offsets, n_fib, radius, max_cand, max_pairs, w.f, stats, s, nullptr);
   if (key64) bind_check<uint64_t>(levels, n_levels, lo, hi, rows, bound, stats, s);
   else bind_check<uint32_t>(levels, n_levels, lo, hi, rows, bound, stats, s);
-  child_starts(key64, levels, n_levels, hi, w, s);
+  child_starts(key64, levels, n_levels, hi, w, caps, s);
   // (no points: every level is empty and the FP64 sums, sized by the points, are not read)
   if (n_pts > 0) {
     if (key64) level_sums64<uint64_t>(g, levels, n_levels, hi, w, caps, max_pairs, stats, s);
     else level_sums64<uint32_t>(g, levels, n_levels, hi, w, caps, max_pairs, stats, s);
   }
-  // lobe gradients and the children's (S, w) gradients, level by level
-  for (int L = lo; L <= hi; ++L) {
+  // lobe gradients and the children's (S, w) gradients
+  const FitLevels lv = fit_levels(levels, n_levels, lo, hi, params, dparams, rows, w, caps, n_pts > 0);
+  {
     VX_TIMED("fit_bwd", s);
-    if (ndir <= 128)
-      hipLaunchKernelGGL(k_fit_bwd<8>, dim3(kGrid), dim3(kBlock), 0, s, levels[L], n_levels + L, rows[L - lo],
-                         n_pts > 0 ? w.s64[L - 1] : nullptr, caps[L - 1], w.cstart[L], params[L - lo], dirs, ndir,
-                         dloss, dparams[L - lo], w.g[L - 1], caps[L - 1]);
-    else
-      hipLaunchKernelGGL(k_fit_bwd<16>, dim3(kGrid), dim3(kBlock), 0, s, levels[L], n_levels + L, rows[L - lo],
-                         n_pts > 0 ? w.s64[L - 1] : nullptr, caps[L - 1], w.cstart[L], params[L - lo], dirs, ndir,
-                         dloss, dparams[L - lo], w.g[L - 1], caps[L - 1]);
+    with_dirs(ndir, [&](auto dpl) {
+      hipLaunchKernelGGL(k_fit_bwd<dpl.value>, dim3(fit_blocks(rows, hi - lo + 1)), dim3(kBlock), 0, s, lv, dirs, ndir,
+                         dloss);
+    });
   }
   // top-down accumulation to the leaf
-  for (int L = hi - 2; L >= 0; --L) {
+  if (hi > 1) {
     VX_TIMED("fit_down", s);
-    hipLaunchKernelGGL(k_fit_down, dim3(kGrid), dim3(kBlock), 0, s, w.pidx[L], n_levels + L, w.g[L], caps[L],
-                       w.g[L + 1], caps[L + 1]);
+    FitDown d{};
+    d.lo = lo - 1;
+    d.hi = hi;
+    for (int L = 0; L < hi; ++L) {
+      d.pidx[L] = w.pidx[L];
+      d.g[L] = w.g[L];
+      d.gcap[L] = caps[L];
+    }
+    hipLaunchKernelGGL(k_fit_down, dim3(blocks_for(caps[0], 4 * kGrid)), dim3(kBlock), 0, s, d, n_levels);
   }
   // the chain rule per segment over its pairs (emission order) and per point
   const Lat lat = make_lat(g, 1, radius);
@@ -765,13 +917,13 @@ vx_status fit_backward_run(const vx_grid* g, const float* pts, int64_t n_pts, co
   {
     VX_TIMED("fit_pairs", s);
     if (key64)
-      hipLaunchKernelGGL(k_fit_pairs<uint64_t>, dim3(blocks_for(n_pts)), dim3(kBlock), 0, s, w.f.rec, w.f.cand_off,
+      hipLaunchKernelGGL(k_fit_pairs<uint64_t>, dim3(blocks_for(16 * n_pts, 8 * kGrid)), dim3(kBlock), 0, s, w.f.rec, w.f.cand_off,
                          n_pts, w.f.masks, w.f.wave_off, w.f.ctl, (const uint64_t*)w.f.pa.keys, levels[0], n_levels,
-                         w.g[0], caps[0], lat.Sb, g->log2_res, vs, tiles ? w.tfirst : nullptr, w.tend, w.seg_grad);
+                         w.g[0], caps[0], lat.Sb, vs, tiles ? w.tfirst : nullptr, w.tend, w.seg_grad);
     else
-      hipLaunchKernelGGL(k_fit_pairs<uint32_t>, dim3(blocks_for(n_pts)), dim3(kBlock), 0, s, w.f.rec, w.f.cand_off,
+      hipLaunchKernelGGL(k_fit_pairs<uint32_t>, dim3(blocks_for(16 * n_pts, 8 * kGrid)), dim3(kBlock), 0, s, w.f.rec, w.f.cand_off,
                          n_pts, w.f.masks, w.f.wave_off, w.f.ctl, (const uint32_t*)w.f.pa.keys, levels[0], n_levels,
-                         w.g[0], caps[0], lat.Sb, g->log2_res, vs, tiles ? w.tfirst : nullptr, w.tend, w.seg_grad);
+                         w.g[0], caps[0], lat.Sb, vs, tiles ? w.tfirst : nullptr, w.tend, w.seg_grad);
   }
   {
     VX_TIMED("fit_points", s);

@@ -141,3 +141,38 @@ def test_moved_points_are_reported_not_faulted(vx):
     plan.forward(pd, params)
     plan.backward(torch.ones(1, device="cuda"), params)
     plan.check()
+
+
+@pytest.mark.parametrize("ndir,lo,hi", [(1, 1, 6), (63, 1, 2), (64, 3, 5), (65, 2, 2), (128, 1, 1), (129, 2, 6),
+                                        (256, 1, 3), (256, 4, 10)])
+def test_direction_rows_and_level_ranges(vx, ndir, lo, hi):
+    """Direction sets that fill one, two or four rows of a wave or end inside one; one fitted level and
+    several, starting at the leaf's parents and above (the leaf's gradient then comes from the levels
+    above alone), up to the pyramid's top."""
+    import torch
+    say(f"case: fit on plain weave 8 fibers, levels {lo}..{hi}, {ndir} directions")
+    wl = synth.plain_weave(n_fibers=8, seed=21)
+    pts = _lattice_points(wl.grid, wl.pts)
+    pd = torch.as_tensor(pts).cuda()
+    dirs = synth.fibonacci_dirs(ndir)
+    plan = vx.FitPlan(wl.grid, pd, torch.as_tensor(wl.offsets).cuda(), wl.radius, lo, hi, dirs=dirs)
+    params = vx.fit_init(plan, seed=5)
+    loss = float(plan.forward(pd, params).item())
+    L_all = np.concatenate([p.cpu().numpy() for p in params]).astype(np.float64)
+    # the loss is a mean over the set: the oracle's 128 directions hold one power-of-two part of it
+    # at a time, repeated
+    o_loss, o_dL, o_dp, k = 0.0, 0.0, 0.0, 0
+    while k < ndir:
+        part = min(128, 1 << ((ndir - k).bit_length() - 1))
+        p_loss, _, p_dL, p_dp = oracle.fit_eval(wl.grid, pts, pts.astype(np.float64), wl.offsets, wl.radius, lo, hi,
+                                                L_all, dirs=np.tile(dirs[k:k + part], (128 // part, 1)))
+        o_loss, o_dL, o_dp = (o + p * part / ndir for o, p in ((o_loss, p_loss), (o_dL, p_dL), (o_dp, p_dp)))
+        k += part
+    assert abs(loss - o_loss) <= 1e-5 * o_loss
+    dpts, dparams = plan.backward(torch.ones(1, device="cuda"), params)
+    plan.check()
+    g_dL = np.concatenate([d.cpu().numpy() for d in dparams]).astype(np.float64)
+    e_L = np.linalg.norm(g_dL - o_dL) / np.linalg.norm(o_dL)
+    e_p = np.linalg.norm(dpts.cpu().numpy() - o_dp) / np.linalg.norm(o_dp)
+    say("loss", loss, o_loss, "relative gradient errors: lobes %.3g, points %.3g" % (e_L, e_p))
+    assert e_L <= 1e-4 and e_p <= 1e-4
