@@ -73,8 +73,8 @@ bool resolve_tuning(const vx_tuning* t, int kind, Tuning* out) {
   u.tile_bits = kTileBits;
   u.unit_budget = kind == 0 ? 1536 : kUnitCand;
   // persistent grids well above the resident blocks (768 to 1024 per launch), so that no tail of
-  // late blocks runs alone; the parent reduce walks children per thread and likes fewer blocks
-  const int defaults[kTuneCount] = {16384, 8192, 16384, 512, 8192};
+  // late blocks runs alone; the pyramid levels go up to kGrid (their scan has one partial a block)
+  const int defaults[kTuneCount] = {16384, 8192, 16384, 1024, 8192};
   for (int i = 0; i < kTuneCount; ++i) u.grids[i] = defaults[i];
   if (t) {
     if (t->tile_bits != 0) {
@@ -354,7 +354,7 @@ vx_status lod_run(const vx_grid* grid, const vx_voxels* leaf, const int64_t* n_l
   for (; L < levels; ++L) {
     const vx_voxels& in = L == 1 ? *leaf : out[L - 2];
     if (K == 1 && in.cap <= kTailMax) break;       // the small top levels go in one launch
-    lod_level(key64, in, n_levels + L - 1, out[L - 1], n_levels + L, n_levels + levels, pstart,
+    lod_level(key64, in, n_levels + L - 1, out[L - 1], n_levels + L, n_levels + levels, K > 1 ? pstart : nullptr,
               partial, tu.grids[kTuneLod], s);
     if (K > 1) {
       if (L == 1)
@@ -555,7 +555,7 @@ vx_status vx_batch_build(const vx_patch* patches, const vx_patch* patches_dev, i
   int L = 1;
   for (; L < levels; ++L) {
     if (K == 1 && out[L - 1].cap <= kTailMax) break;
-    lod_level(true, out[L - 1], n_levels + L - 1, out[L], n_levels + L, n_levels + levels, pstart,
+    lod_level(true, out[L - 1], n_levels + L - 1, out[L], n_levels + L, n_levels + levels, K > 1 ? pstart : nullptr,
               partial, tu.grids[kTuneLod], s, true);
     if (K > 1) {
       if (L == 1)

@@ -849,7 +849,7 @@ static void level_sums64(const vx_grid* g, const vx_voxels* levels, const int64_
   const PairBufs P = radix_sort_pairs(sizeof(Key) == 8, 3 * g->log2_res, w.f.pa, w.pb, w.pc, w.f.ctl + CTL_N_PAIRS,
                                       max_pairs, w.hist, w.partial, s);
   device_scan(HeadIn<Key, 0>{(const Key*)P.keys}, LeafSegOut{w.sstart, caps[0]},
-              LeafSegTotal{w.sstart, caps[0], n_levels, stats}, w.f.ctl + CTL_N_PAIRS, 0, w.partial, s);
+              LeafSegTotal{w.sstart, caps[0], n_levels, stats}, w.f.ctl + CTL_N_PAIRS, max_pairs, w.partial, s);
   const Lat lat = make_lat(g, 1, 0.0f);
   hipLaunchKernelGGL(k_fit_leaf64<Key>, dim3(blocks_for(caps[0], 4 * kGrid)), dim3(kBlock), 0, s, (const Key*)P.keys, P.prim, w.sstart,
                      w.f.rec, (const Key*)levels[0].keys, n_levels, caps[0], lat.Sb, w.s64[0], stats);

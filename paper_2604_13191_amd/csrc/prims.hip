@@ -376,7 +376,7 @@ void voxelize_front(int kind, const vx_grid* g, const float* data, int64_t n_pri
   {
     VX_TIMED("scan_pairs", s);
     device_scan(PopIn{w.masks}, ArrOut{w.wave_off}, PairTotal{w.wave_off, w.ctl, stats, max_pairs},
-                w.ctl + CTL_N_CHUNKS, 0, w.partial, s);
+                w.ctl + CTL_N_CHUNKS, cdiv(max_cand, 64), w.partial, s);
   }
   VX_TIMED(kind == 0 ? "emit_tri" : "emit_fib", s);
 #define VX_EMIT(KD, K)                                                                                        \

@@ -566,7 +566,7 @@ void samp_back(int kind, const vx_grid* g, int64_t max_samples, const SampWs& w,
     VX_TIMED("sample_heads", s);
     hipLaunchKernelGGL(k_samp_heads<Key>, dim3(blocks_for(max_samples)), dim3(kBlock), 0, s, sorted, w.ctl, w.mask);
     device_scan(MaskIn{w.mask}, MaskOut{w.mask, w.start, out->cap + 2}, SegTotal{w.start, w.ctl, out->cap + 2},
-                w.ctl + SC_WORDS, 0, w.partial, s);
+                w.ctl + SC_WORDS, (max_samples + 63) / 64, w.partial, s);
     hipLaunchKernelGGL(k_samp_finish, dim3(1), dim3(64), 0, s, w.ctl, stats, out->cap);
   }
   VX_TIMED("sample_reduce", s);

@@ -290,28 +290,69 @@ __device__ __forceinline__ void lod_parent(const vx_voxels& in, const Key* ikeys
   for (int k = 0; k < 6; ++k) out.S[k * co + p] = S[k];
 }
 
-struct LodTotal {
-  int64_t* start;
-  int64_t* n_out;     // clamped count of the new level
-  int64_t* flags;
-  int64_t cap;
-  __device__ void operator()(int64_t total, int64_t n) const {
-    const bool over = total > cap;
-    if (over) flag_or_s(flags, VX_FLAG_VOXEL_CAPACITY);
-    const int64_t eff = over ? cap : total;
-    start[eff] = n;      // only read up to the clamped count
-    *n_out = eff;
-  }
-};
-
-
+// One level: ranks of the heads as in k_scan_apply, and the parents summed right there -- a round's
+// heads are listed in LDS, then each thread takes a parent and its children.  pstart (for the lobes
+// of the level; may be nullptr) gets the parents' first children and, at the end, n.
 template <class Key, bool BATCH>
-__global__ void __launch_bounds__(kBlock) k_lod_reduce(vx_voxels in, const int64_t* __restrict__ start,
-                                                       const int64_t* __restrict__ n_ptr, vx_voxels out) {
-  const int64_t n = *n_ptr;
+__global__ void __launch_bounds__(kBlock) k_lod_apply(vx_voxels in, const int64_t* __restrict__ n_ptr, vx_voxels out,
+                                                      int64_t* __restrict__ n_out, int64_t* flags,
+                                                      int64_t* __restrict__ pstart,
+                                                      const int64_t* __restrict__ partial) {
+  __shared__ int64_t tmp[kWaves + 1];
+  __shared__ int32_t head[kBlock * kScanRun];
   const Key* ikeys = reinterpret_cast<const Key*>(in.keys);
-  for (int64_t p = int64_t(blockIdx.x) * kBlock + threadIdx.x; p < n; p += int64_t(gridDim.x) * kBlock)
-    lod_parent<Key, BATCH>(in, ikeys, start[p], start[p + 1], out, p);
+  const int64_t n = *n_ptr;
+  const int64_t chunk = scan_chunk(n);
+  const int64_t b0 = int64_t(blockIdx.x) * chunk;
+  const int64_t b1 = b0 + chunk < n ? b0 + chunk : n;
+  const auto total = [&](int64_t all) {
+    const bool over = all > out.cap;
+    if (over) flag_or_s(flags, VX_FLAG_VOXEL_CAPACITY);
+    if (pstart && !over) pstart[all] = n;       // (over: the heads fill the start at out.cap themselves)
+    *n_out = over ? out.cap : all;
+  };
+  const bool alone = gridDim.x == 1;
+  int64_t base = 0;
+  if (!alone) {
+    int64_t all;
+    base = block_scan_base(partial, tmp, all);
+    if (blockIdx.x == 0 && threadIdx.x == 0) total(all);
+  }
+  const HeadIn<Key, 3, BATCH> is_head{ikeys};
+  for (int64_t t0 = b0; t0 < b1; t0 += int64_t(kBlock) * kScanRun) {
+    const int64_t i0 = t0 + int64_t(threadIdx.x) * kScanRun;
+    int v[kScanRun], run = 0;
+#pragma unroll
+    for (int j = 0; j < kScanRun; ++j) {
+      v[j] = i0 + j < b1 ? int(is_head(i0 + j)) : 0;
+      run += v[j];
+    }
+    int64_t tot;
+    int ex = int(block_exclusive_scan(int64_t(run), tmp, tot));
+#pragma unroll
+    for (int j = 0; j < kScanRun; ++j) {
+      if (v[j]) {
+        head[ex] = int(i0 - t0) + j;
+        if (pstart && base + ex <= out.cap) pstart[base + ex] = i0 + j;
+      }
+      ex += v[j];
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < int(tot); q += kBlock) {
+      const int64_t a = t0 + head[q];
+      int64_t b;
+      if (q + 1 < int(tot)) {
+        b = t0 + head[q + 1];
+      } else {                          // the last parent's children may reach past the round
+        const Key pk = parent_key<Key, BATCH>(ikeys[a]);
+        for (b = a + 1; b < n && parent_key<Key, BATCH>(ikeys[b]) == pk;) ++b;
+      }
+      if (base + q < out.cap) lod_parent<Key, BATCH>(in, ikeys, a, b, out, base + q);
+    }
+    base += tot;
+    __syncthreads();
+  }
+  if (alone && threadIdx.x == 0) total(base);
 }
 
 constexpr int kLodBlock = 1024;
@@ -442,28 +483,26 @@ void lod_init(const int64_t* src, int64_t cap, int64_t* n_levels, int64_t count,
   hipLaunchKernelGGL(k_lod_init, dim3(1), dim3(64), 0, s, src, cap, n_levels, count);
 }
 
-void lod_level(bool key64, const vx_voxels& in, const int64_t* n_in, const vx_voxels& out, int64_t* n_out,
-               int64_t* flags, int64_t* pstart, int64_t* partial, int grid_blocks, hipStream_t s, bool batch) {
-  {
+template <class Key, bool BATCH>
+static void lod_level_as(const vx_voxels& in, const int64_t* n_in, const vx_voxels& out, int64_t* n_out, int64_t* flags,
+                         int64_t* pstart, int64_t* partial, int blocks, hipStream_t s) {
+  if (blocks > 1) {
     VX_TIMED("lod_heads", s);
-    if (batch)
-      device_scan(HeadIn<uint64_t, 3, true>{(const uint64_t*)in.keys}, HeadOut{pstart},
-                  LodTotal{pstart, n_out, flags, out.cap}, n_in, 0, partial, s);
-    else if (key64)
-      device_scan(HeadIn<uint64_t, 3>{(const uint64_t*)in.keys}, HeadOut{pstart},
-                  LodTotal{pstart, n_out, flags, out.cap}, n_in, 0, partial, s);
-    else
-      device_scan(HeadIn<uint32_t, 3>{(const uint32_t*)in.keys}, HeadOut{pstart},
-                  LodTotal{pstart, n_out, flags, out.cap}, n_in, 0, partial, s);
+    using Heads = HeadIn<Key, 3, BATCH>;
+    hipLaunchKernelGGL(k_scan_partial<Heads>, dim3(blocks), dim3(kBlock), 0, s, Heads{(const Key*)in.keys}, n_in,
+                       int64_t(0), partial);
   }
   VX_TIMED("lod_reduce", s);
-  const dim3 grid(grid_blocks);
-  if (batch)
-    hipLaunchKernelGGL((k_lod_reduce<uint64_t, true>), grid, dim3(kBlock), 0, s, in, pstart, n_out, out);
-  else if (key64)
-    hipLaunchKernelGGL((k_lod_reduce<uint64_t, false>), grid, dim3(kBlock), 0, s, in, pstart, n_out, out);
-  else
-    hipLaunchKernelGGL((k_lod_reduce<uint32_t, false>), grid, dim3(kBlock), 0, s, in, pstart, n_out, out);
+  hipLaunchKernelGGL((k_lod_apply<Key, BATCH>), dim3(blocks), dim3(kBlock), 0, s, in, n_in, out, n_out, flags, pstart,
+                     partial);
+}
+
+void lod_level(bool key64, const vx_voxels& in, const int64_t* n_in, const vx_voxels& out, int64_t* n_out,
+               int64_t* flags, int64_t* pstart, int64_t* partial, int grid_blocks, hipStream_t s, bool batch) {
+  const int blocks = scan_blocks(in.cap, grid_blocks < kGrid ? grid_blocks : kGrid);
+  if (batch) lod_level_as<uint64_t, true>(in, n_in, out, n_out, flags, pstart, partial, blocks, s);
+  else if (key64) lod_level_as<uint64_t, false>(in, n_in, out, n_out, flags, pstart, partial, blocks, s);
+  else lod_level_as<uint32_t, false>(in, n_in, out, n_out, flags, pstart, partial, blocks, s);
 }
 
 void lod_tail(bool key64, bool batch, const vx_voxels* lv, int64_t* const* n, int count, int64_t* flags,

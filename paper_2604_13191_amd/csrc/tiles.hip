@@ -1017,7 +1017,7 @@ __global__ void __launch_bounds__(kBlock) k_unit_sums_apply(const int64_t* __res
   const int64_t b0 = int64_t(blockIdx.x) * chunk;
   const int64_t b1 = b0 + chunk < n ? b0 + chunk : n;
   int64_t pre = 0, tp = 0, tc = 0, tv = 0;
-  for (int i = threadIdx.x; i < kGrid; i += kBlock) {
+  for (int i = threadIdx.x; i < int(gridDim.x); i += kBlock) {
     const int64_t v = partial[3 * i + 2];
     if (i < int(blockIdx.x)) pre += v;
     if (blockIdx.x == 0) {
@@ -1178,6 +1178,8 @@ vx_status tile_voxelize(int kind, const vx_grid* g, const float* data, int64_t n
       hipLaunchKernelGGL(k_rec_count, dim3(pgrid), dim3(kBlock), 0, s, w.box, w.cand_cnt, n_prims, tb, w.roff);
     device_scan(ArrIn64{w.roff}, ArrOut64{w.roff}, RecTotal{w.roff, w.ctl, stats, max_rec}, nullptr, n_prims,
                 w.partial, s);
+    // a counting call without room for records (or units, below) ends at its count
+    if (max_rec == 0) return hipGetLastError() == hipSuccess ? VX_OK : VX_ERR_HIP;
     if (key64)
       hipLaunchKernelGGL(k_rec_emit<uint64_t>, dim3(pgrid), dim3(kBlock), 0, s, w.rec, w.box, w.roff, n_prims, w.ctl, tb,
                          batch ? 1 : 0, (uint64_t*)w.ra.keys, w.ra.prim);
@@ -1196,21 +1198,23 @@ vx_status tile_voxelize(int kind, const vx_grid* g, const float* data, int64_t n
     VX_TIMED("tile_heads", s);
     if (key64)
       device_scan(HeadIn<uint64_t, 0>{(const uint64_t*)R.keys}, HeadOut{w.tstart}, TileTotal{w.tstart, w.ctl},
-                  w.ctl + CTL_N_REC, 0, w.partial, s);
+                  w.ctl + CTL_N_REC, max_rec, w.partial, s);
     else
       device_scan(HeadIn<uint32_t, 0>{(const uint32_t*)R.keys}, HeadOut{w.tstart}, TileTotal{w.tstart, w.ctl},
-                  w.ctl + CTL_N_REC, 0, w.partial, s);
+                  w.ctl + CTL_N_REC, max_rec, w.partial, s);
   }
   {
     VX_TIMED("unit_plan", s);
-    const int grid = tu.grids[kTunePlan];
+    // (a grid beyond the chip's fill only where there may be as many tiles: records are many to a tile)
+    const int grid = bounded_grid(tu.grids[kTunePlan], max_rec / 8 > kGrid ? max_rec / 8 : kGrid);
     const int64_t budget = tu.unit_budget;
 #define VX_PLAN(P, K)                                                                                        \
   hipLaunchKernelGGL((k_unit_plan<P, K>), dim3(grid), dim3(kBlock), 0, s, w.box, (const K*)R.keys, R.prim, w.tstart, \
                      w.ctl, tb, batch ? 1 : 0, budget, w.ucnt, w.uoff, w.units)
     if (key64) VX_PLAN(0, uint64_t); else VX_PLAN(0, uint32_t);
     device_scan(UnitCountIn{w.ucnt}, ArrOut64{w.uoff}, UnitTotal{w.uoff, w.ctl, stats, max_units}, w.ctl + CTL_N_TILES,
-                0, w.partial, s);
+                max_rec, w.partial, s);
+    if (max_units == 0) return hipGetLastError() == hipSuccess ? VX_OK : VX_ERR_HIP;
     if (key64) VX_PLAN(1, uint64_t); else VX_PLAN(1, uint32_t);
 #undef VX_PLAN
   }
@@ -1218,7 +1222,7 @@ vx_status tile_voxelize(int kind, const vx_grid* g, const float* data, int64_t n
     VX_TIMED(kind == 0 ? "unit_tri" : "unit_fib", s);
     const Lat L = make_lat(g, kind, radius);
     const Lat* lats = batch ? batch->lats : nullptr;
-    const int ugrid = tu.grids[kTuneUnit];
+    const int ugrid = bounded_grid(tu.grids[kTuneUnit], max_units);
 #define VX_UNIT(KD, C)                                                                                           \
   do {                                                                                                          \
     constexpr size_t bytes_ = unit_lds_bytes<KD, C>();                                                          \
@@ -1248,15 +1252,16 @@ vx_status tile_voxelize(int kind, const vx_grid* g, const float* data, int64_t n
   }
   {
     VX_TIMED("unit_compact", s);
-    hipLaunchKernelGGL(k_unit_sums_partial, dim3(kGrid), dim3(kBlock), 0, s, w.unp, w.units, w.unv, w.ctl,
+    const int blocks = scan_blocks(max_units, kGrid), cgrid = bounded_grid(tu.grids[kTuneCompact], max_units);
+    hipLaunchKernelGGL(k_unit_sums_partial, dim3(blocks), dim3(kBlock), 0, s, w.unp, w.units, w.unv, w.ctl,
                        w.partial);
-    hipLaunchKernelGGL(k_unit_sums_apply, dim3(kGrid), dim3(kBlock), 0, s, w.unv, w.ctl, w.partial, w.upos, stats,
+    hipLaunchKernelGGL(k_unit_sums_apply, dim3(blocks), dim3(kBlock), 0, s, w.unv, w.ctl, w.partial, w.upos, stats,
                        out->cap);
     if (key64)
-      hipLaunchKernelGGL(k_unit_compact<uint64_t>, dim3(tu.grids[kTuneCompact]), dim3(kBlock), 0, s, w.unv,
+      hipLaunchKernelGGL(k_unit_compact<uint64_t>, dim3(cgrid), dim3(kBlock), 0, s, w.unv,
                          w.usoff, w.upos, w.ctl, w.st, *out);
     else
-      hipLaunchKernelGGL(k_unit_compact<uint32_t>, dim3(tu.grids[kTuneCompact]), dim3(kBlock), 0, s, w.unv,
+      hipLaunchKernelGGL(k_unit_compact<uint32_t>, dim3(cgrid), dim3(kBlock), 0, s, w.unv,
                          w.usoff, w.upos, w.ctl, w.st, *out);
   }
   return hipGetLastError() == hipSuccess ? VX_OK : VX_ERR_HIP;

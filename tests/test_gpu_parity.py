@@ -305,3 +305,49 @@ def test_repeat_runs_identical(vx):
     b = plan.run().check().numpy()
     for k in a:
         assert np.array_equal(a[k], b[k])
+
+
+@pytest.mark.parametrize("n,K,dense", [(1, 2, True), (511, 2, False), (512, 2, True), (513, 2, False), (1025, 2, True),
+                                       (2049, 1, True), (4097, 1, False), (30000, 3, True), (600001, 1, False),
+                                       (600001, 1, True)])
+def test_lod_levels_are_sums_in_order(vx, n, K, dense):
+    """Levels built by one block and by many, with parents across the blocks' and rounds' edges: every
+    level is exactly the float32 sums of the one below in key order, with its counts and child masks;
+    and a level over its capacity is reported."""
+    import torch
+    log2_res, levels = 10, 5
+    rng = np.random.default_rng(n + K)
+    keys = np.arange(n) + 3 if dense else np.sort(rng.choice(1 << 30, n, replace=False))
+    keys = keys.astype(np.uint32)
+    leaf = vx.alloc_voxels(n, log2_res, "cuda", False)
+    vals = rng.uniform(0.1, 1.0, (7, n)).astype(np.float32)
+    cnt = rng.integers(1, 5, n).astype(np.uint32)
+    leaf.keys.copy_(torch.as_tensor(keys.view(np.int32)))
+    leaf.count.copy_(torch.as_tensor(cnt.view(np.int32)))
+    leaf.w.copy_(torch.as_tensor(vals[0]))
+    leaf.S.copy_(torch.as_tensor(vals[1:]))
+    leaf.n = n
+    print(f"case: pyramid of {n} given voxels, K = {K}", flush=True)
+    grid = synth.Grid((0.0, 0.0, 0.0), 1.0, log2_res)
+    out = vx.build_lod(grid, leaf, levels, K=K)
+    for L in range(1, levels):
+        parent = keys >> 3
+        start = np.flatnonzero(np.r_[True, parent[1:] != parent[:-1]])
+        end = np.r_[start[1:], len(keys)]
+        pv = np.zeros((7, len(start)), np.float32)
+        pc = np.zeros(len(start), np.uint32)
+        pm = np.zeros(len(start), np.uint8)
+        for c in range(8):
+            on = start + c < end
+            i = start[on] + c
+            pv[:, on] += vals[:, i]
+            pc[on] += cnt[i]
+            pm[on] |= (1 << (keys[i] & 7)).astype(np.uint8)
+        keys, vals, cnt = parent[start], pv, pc
+        g = out[L].numpy()
+        assert out[L].n == len(keys)
+        assert np.array_equal(g["keys"], keys) and np.array_equal(g["count"], cnt) and np.array_equal(g["mask"], pm)
+        assert np.array_equal(g["w"], vals[0]) and np.array_equal(g["S"].T, vals[1:])
+    if out[1].n > 1:
+        with pytest.raises(vx.VxError):
+            vx.build_lod(grid, leaf, levels, K=K, caps=[out[1].n - 1] + [n] * (levels - 2))
