@@ -271,10 +271,21 @@ class VoxelizePlan:
     The capacities come from the library's own counts: counting calls report the
     primitive-tile records, then the work units, then the leaf voxels (device stats, read back
     once each).  ``run()`` then enqueues the whole voxelize pass with no host sync.
+
+    A small set of primitives is counted by one whole pass into roomy buffers instead; what did
+    not fit there is counted as above.  ``_keep``: keep that pass's voxels (``_take_first``).
     """
 
+    # A counting call of a small set is launches and a read-back, not work: one call on a sphere of
+    # 20,480 triangles takes 0.20 ms counted by one pass and 0.46 ms by three calls at 64^3, 0.28 and
+    # 0.63 ms at 256^3.  A pass whose voxels do not fit has still given every total and costs what the
+    # third counting call does (512^3, 1.0 M voxels: 0.96 and 1.09 ms), so the limits only bound the
+    # roomy buffers: under 60 MB.
+    FIRST_MAX_PRIMS = 1 << 16
+    FIRST_UNITS, FIRST_VOXELS = 1 << 17, 1 << 18
+
     def __init__(self, kind, grid, data, offsets=None, radius=0.0, max_records=None, max_units=None, out_cap=None,
-                 tuning=None):
+                 tuning=None, _keep=False):
         import torch
         self.L = load()
         self.kind = kind
@@ -295,8 +306,12 @@ class VoxelizePlan:
             self.n_fib = int(self.offsets.numel() - 1)
         self.radius = float(radius)
         self.stats = torch.zeros(VX_NSTAT, dtype=torch.int64, device=self.device)
+        self._first = None
         if max_records is None or max_units is None or out_cap is None:
-            r, u, v = self._count(max_records, max_units)
+            known = (max_records, max_units, None)
+            if known == (None, None, None) and out_cap is None and self.n_prims <= self.FIRST_MAX_PRIMS:
+                known = self._count_whole(_keep)
+            r, u, v = known if known[2] is not None else self._count(*known[:2])
             max_records = r if max_records is None else max_records
             max_units = u if max_units is None else max_units
             out_cap = v if out_cap is None else out_cap
@@ -342,7 +357,6 @@ class VoxelizePlan:
             uu = 0 if u is None else u
             ws = self._ws_for(rr, uu, 1)
             self._call(rr, uu, _ptr(ws), ws.numel(), cout, s)
-            self.L.vx_check_stats(_ptr(self.stats), s)
             h = self.stats.cpu().numpy()
             if h[STAT_FLAGS] & (FLAG_INPUT | FLAG_OFFSETS):
                 raise VxError(4, "voxelize")
@@ -355,6 +369,38 @@ class VoxelizePlan:
             del ws
         return r, u, v
 
+    def _count_whole(self, keep):
+        """The three totals from one whole pass; those after a capacity it exceeded are None."""
+        import torch
+        cap = 4 * self.n_prims + (1 << 14)
+        try:
+            out = alloc_voxels(self.FIRST_VOXELS, self.grid.log2_res, self.device, False)
+            ws = self._ws_for(cap, self.FIRST_UNITS, self.FIRST_VOXELS)
+        except torch.OutOfMemoryError:
+            return None, None, None
+        self._call(cap, self.FIRST_UNITS, _ptr(ws), ws.numel(), out.cstruct(), _stream())
+        h = self.stats.cpu().numpy()
+        if h[STAT_FLAGS] & (FLAG_INPUT | FLAG_OFFSETS):
+            raise VxError(4, "voxelize")
+        r, u, v = int(h[STAT_RECORDS]), int(h[STAT_UNITS]), int(h[STAT_VOXELS])
+        if r > cap:
+            return r, None, None
+        if u > self.FIRST_UNITS:
+            return r, u, None
+        if keep and v <= self.FIRST_VOXELS:
+            self._first = (out, h)
+        return r, u, v
+
+    def _take_first(self):
+        """The voxels that counting by a whole pass left (the plan must not have run since), or None."""
+        if self._first is None:
+            return None
+        (first, h), self._first = self._first, None
+        n = int(h[STAT_VOXELS])
+        for name in ("keys", "count", "w", "S"):
+            getattr(self.out, name)[..., :n].copy_(getattr(first, name)[..., :n])
+        return self._read(h)
+
     def run(self, stream=None):
         self._call(self.max_records, self.max_units, _ptr(self.ws), self.ws.numel(), self._cout, _stream(stream))
         return self
@@ -364,6 +410,9 @@ class VoxelizePlan:
         h = self.stats.cpu().numpy()
         if st != 0:
             raise VxError(st, f"voxelize (stats {h.tolist()})")
+        return self._read(h)
+
+    def _read(self, h):
         self.out.n = int(h[STAT_VOXELS])
         self.n_pairs = int(h[STAT_PAIRS])
         self.n_cand = int(h[STAT_CAND])
@@ -685,16 +734,16 @@ class OccupancyPlan:
 
 def voxelize_triangles(tris, grid, **kw):
     """Triangle soup float32 [n, 3, 3] on the GPU -> leaf Voxels (plan kept on .plan)."""
-    p = VoxelizePlan(0, grid, tris, **kw).run()
-    v = p.check()
+    p = VoxelizePlan(0, grid, tris, _keep=True, **kw)
+    v = p._take_first() or p.run().check()
     v.plan = p
     return v
 
 
 def voxelize_fibers(pts, offsets, radius, grid, **kw):
     """Polylines: float32 [m, 3] points + int64 CSR offsets [F + 1] -> leaf Voxels."""
-    p = VoxelizePlan(1, grid, pts, offsets=offsets, radius=radius, **kw).run()
-    v = p.check()
+    p = VoxelizePlan(1, grid, pts, offsets=offsets, radius=radius, _keep=True, **kw)
+    v = p._take_first() or p.run().check()
     v.plan = p
     return v
 
@@ -704,7 +753,7 @@ def build_lod(grid, leaf: Voxels, levels, K=1, iters=2, n_leaf_dev=None, caps=No
     return_lobes, also the per-level lobes [level 1, ...] (Sec. 4.4)."""
     import torch
     if n_leaf_dev is None:
-        n_leaf_dev = torch.tensor([leaf.n], dtype=torch.int64, device=leaf.w.device)
+        n_leaf_dev = torch.full((1,), leaf.n, dtype=torch.int64, device=leaf.w.device)
     p = LodPlan(grid, leaf, n_leaf_dev, levels, K, iters, caps, tuning=tuning).run()
     out = p.check()
     if return_lobes:
@@ -712,11 +761,13 @@ def build_lod(grid, leaf: Voxels, levels, K=1, iters=2, n_leaf_dev=None, caps=No
     return out
 
 
-def _count_dev(n, cap, device):
+def _count_dev(n, cap, device, stream=None):
     import torch
     if n is None:
         n = cap
     if isinstance(n, int):
+        if stream is None:          # a fill in the order of the stream; a copy from the host waits for it
+            return torch.full((1,), n, dtype=torch.int64, device=device)
         return torch.tensor([n], dtype=torch.int64, device=device)
     return n
 
@@ -732,7 +783,7 @@ def sggx_compact(w, S, n=None, eps=1e-3, vectors=True, stream=None):
     if S.shape != (6, cap) or w.dtype != torch.float32 or S.dtype != torch.float32:
         raise VxError(1, "sggx_compact: w [cap] and S [6, cap] float32")
     w, S = w.contiguous(), S.contiguous()
-    n_dev = _count_dev(n, cap, w.device)
+    n_dev = _count_dev(n, cap, w.device, stream)
     lam = torch.empty((3, cap), dtype=torch.float32, device=w.device)
     vec = torch.empty((9, cap), dtype=torch.float32, device=w.device) if vectors else None
     code = torch.empty((cap, 6), dtype=torch.uint8, device=w.device)
@@ -751,7 +802,7 @@ def sggx_decode(code, n=None, stream=None):
     if code.shape != (cap, 6) or code.dtype != torch.uint8:
         raise VxError(1, "sggx_decode: code uint8 [cap, 6]")
     code = code.contiguous()
-    n_dev = _count_dev(n, cap, code.device)
+    n_dev = _count_dev(n, cap, code.device, stream)
     S = torch.empty((6, cap), dtype=torch.float32, device=code.device)
     st = load().vx_sggx_decode(_ptr(code), _ptr(n_dev), cap, _ptr(S), _stream(stream))
     if st != 0:

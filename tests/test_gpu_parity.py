@@ -351,3 +351,48 @@ def test_lod_levels_are_sums_in_order(vx, n, K, dense):
     if out[1].n > 1:
         with pytest.raises(vx.VxError):
             vx.build_lod(grid, leaf, levels, K=K, caps=[out[1].n - 1] + [n] * (levels - 2))
+
+
+@pytest.mark.parametrize("limits", [{}, {"FIRST_MAX_PRIMS": 0}, {"FIRST_UNITS": 3}, {"FIRST_VOXELS": 100},
+                                    {"FIRST_UNITS": 3, "FIRST_VOXELS": 100}])
+@pytest.mark.parametrize("kind", ["tris", "few huge tris", "fibers", "none"])
+def test_one_call_counts(vx, monkeypatch, kind, limits):
+    """Voxelization in one call, counted by one pass or by counting calls, whichever total did not fit:
+    the voxels, the capacities and the totals are those of a plan built by counting calls and run."""
+    import torch
+    print(f"case: one call on {kind}, {limits}", flush=True)
+    if kind == "fibers":
+        wl = synth.random_fibers(12, 40, 8, seed=3, step=3.0, margin=4.0)
+        args = (_dev(wl.pts),), {"offsets": _dev(wl.offsets), "radius": wl.radius}
+        call = lambda: vx.voxelize_fibers(_dev(wl.pts), _dev(wl.offsets), wl.radius, wl.grid)
+    else:
+        wl = synth.random_triangles(300, 8, seed=5, scale=6.0, margin=2.0)
+        t = wl.tris[:0] if kind == "none" else wl.tris
+        if kind == "few huge tris":           # 16,400 records and more from two primitives
+            e = np.float32(wl.grid.extent)
+            wl.grid.log2_res = 11
+            t = np.array([[[0, 0, 0.1], [1, 0, 0.5], [0, 1, 0.9]], [[1, 1, 0.2], [1, 0, 0.6], [0, 1, 0.4]]],
+                         np.float32) * e
+        args = (_dev(t),), {}
+        call = lambda: vx.voxelize_triangles(_dev(t), wl.grid)
+    with monkeypatch.context() as m:
+        m.setattr(vx.VoxelizePlan, "FIRST_MAX_PRIMS", -1)
+        p = vx.VoxelizePlan(1 if kind == "fibers" else 0, wl.grid, *args[0], **args[1]).run()
+        want = p.check()
+    for k, v in limits.items():
+        monkeypatch.setattr(vx.VoxelizePlan, k, v)
+    got = call()
+    q = got.plan
+    for a in ("max_records", "max_units", "n_pairs", "n_cand", "n_records", "n_units"):
+        assert getattr(p, a) == getattr(q, a), a
+    assert got.n == want.n and got.cap == want.cap
+    a, b = want.numpy(), got.numpy()
+    assert all(np.array_equal(a[k], b[k]) for k in a)
+    c = q.run().check().numpy()               # the plan goes on as any other
+    assert all(np.array_equal(a[k], c[k]) for k in a)
+    if kind == "tris":
+        bad = t.copy()
+        bad[7, 1, 2] = np.nan
+        with pytest.raises(vx.VxError) as e:
+            vx.voxelize_triangles(_dev(bad), wl.grid)
+        assert e.value.status == 4
