@@ -341,6 +341,26 @@ VX_HD inline __attribute__((noinline)) bool cap_exact(int64_t c0, int64_t c1, in
   return false;
 }
 
+// 1 / x to a few units in the last place
+VX_HD inline double recip(double x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+#else
+  return 1.0 / x;
+#endif
+}
+// a / d, correctly rounded, from y = recip(d), for a and d integers below 2^26 or both scaled by one
+// power of two: q = a y is off by a few units, its remainder a - q d is exact (at most 28 bits above
+// the last place of q, d being an integer), and a / d lies at least 2^-80 (relative) from the middle
+// of two doubles, far more than the 2^-100 that the last step is off before its rounding.  Three
+// instructions against the fifteen of a quotient, where several share their divisor.
+VX_HD inline double quotient(double a, double d, double y) {
+  const double q = a * y;
+  return fma(fma(-q, d, a), y, q);
+}
+
 // exact capsule / closed box test: min over t in [0,1] of f(t) = dist^2(c + t d, [0, s]^3)
 // against rho^2.  FP64 with an error bound (all inputs are exact integers below 2^26; every
 // rounding of the bracketing, the interpolation and the evaluation stays far inside
@@ -434,7 +454,7 @@ VX_HD inline bool cap_bracket(const int32_t* r, const int64_t v[3], int64_t s, i
   for (int a = 0; a < 3; ++a) {
     double t0 = 0.0, t1 = 0.0;
     if (q.di[a] != 0) {
-      const double inv = 1.0 / q.d[a];
+      const double inv = recip(q.d[a]);
       t0 = fmin(fmax(-q.c[a] * inv, 0.0), 1.0);
       t1 = fmin(fmax((ds - q.c[a]) * inv, 0.0), 1.0);
     }
@@ -457,7 +477,7 @@ VX_HD inline bool cap_bracket(const int32_t* r, const int64_t v[3], int64_t s, i
   if (t_lo < 0.0) ts = 0.0;                 // f' > 0 on [0, 1]
   else if (t_hi > 1.0) ts = 1.0;            // f' < 0 on [0, 1]
   else if (t_hi <= t_lo || g_hi - g_lo <= 0.0) ts = t_lo;
-  else ts = fmin(fmax(t_lo - g_lo * (t_hi - t_lo) / (g_hi - g_lo), t_lo), t_hi);
+  else ts = fmin(fmax(t_lo - g_lo * (t_hi - t_lo) * recip(g_hi - g_lo), t_lo), t_hi);
   const double fmin_ = fdist2(ts, q.c, q.d, ds);
   if (fmin_ + q.err <= r2) return true;
   if (fmin_ - q.err > r2) return false;
@@ -472,20 +492,21 @@ VX_HD inline bool cap_touch(const int32_t* r, const int64_t v[3], int64_t s, int
 // ---------------------------------------------------------------------------------------------
 // weights
 // ---------------------------------------------------------------------------------------------
-// length of the segment inside [v, v+1)^3 in voxel units (half-open for axis-parallel segments)
+// length of the segment inside [v, v+1)^3 in voxel units (half-open for axis-parallel segments);
+// the differences fit int32 (lattice coordinates lie within [-2^24, 2^24], voxel corners below 2^23)
 VX_HD inline float seg_length(const int32_t* r, const int64_t v[3], int Sb, float len_vox) {
   double t0 = 0.0, t1 = 1.0;
-  const double inv_s = 1.0 / double(int64_t(1) << Sb);
+  const int32_t s = int32_t(1) << Sb;
   bool empty = false;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const int64_t ci = int64_t(r[a]) - (v[a] << Sb);
-    const int64_t di = int64_t(r[3 + a]) - int64_t(r[a]);
+    const int32_t ci = r[a] - int32_t(v[a] << Sb);
+    const int32_t di = r[3 + a] - r[a];
     if (di == 0) {
-      empty = empty || !(ci >= 0 && ci < (int64_t(1) << Sb));
+      empty = empty || !(ci >= 0 && ci < s);
     } else {
-      const double c = double(ci) * inv_s, d = double(di) * inv_s;
-      const double ta = -c / d, tb = (1.0 - c) / d;
+      const double d = double(di), y = recip(d);
+      const double ta = quotient(double(-ci), d, y), tb = quotient(double(s - ci), d, y);
       t0 = fmax(t0, fmin(ta, tb));
       t1 = fmin(t1, fmax(ta, tb));
     }
@@ -495,7 +516,7 @@ VX_HD inline float seg_length(const int32_t* r, const int64_t v[3], int Sb, floa
 }
 
 // Length (voxel units) of the segment A-B inside [lo, lo+1)^3 and its derivatives with respect
-// to both ends, FP64 voxel coordinates.  A clipped end slides inside its clipping plane when an
+// to both ends, FP64 voxel coordinates (lattice points: multiples of one power of two, below 2^26 of it).  A clipped end slides inside its clipping plane when an
 // end point moves: its velocity is the end point's velocity projected along d onto that plane.
 VX_HD inline double seg_length_grad(const double A[3], const double B[3], const double lo[3], double gA[3],
                                     double gB[3]) {
@@ -512,7 +533,8 @@ VX_HD inline double seg_length_grad(const double A[3], const double B[3], const 
       if (!(A[a] >= lo[a] && A[a] < lo[a] + 1.0)) return 0.0;
       continue;
     }
-    const double t0 = (lo[a] - A[a]) / d[a], t1 = (lo[a] + 1.0 - A[a]) / d[a];
+    const double y = recip(d[a]);
+    const double t0 = quotient(lo[a] - A[a], d[a], y), t1 = quotient(lo[a] + 1.0 - A[a], d[a], y);
     const double lo_t = t0 < t1 ? t0 : t1, hi_t = t0 < t1 ? t1 : t0;
     if (lo_t > t_in) { t_in = lo_t; ax_in = a; }
     if (hi_t < t_out) { t_out = hi_t; ax_out = a; }

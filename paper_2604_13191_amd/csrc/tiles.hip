@@ -348,14 +348,15 @@ struct UnitLds {
   uint32_t* prim;     // [budget]
   uint16_t* ckey;     // [budget]   per candidate of the batch: kTouch | its unit-local key,
                       // kUndecided, or 0 for a miss
-  uint16_t* queue;    // [budget]   the batch's undecided candidates (fibers: in the space of w, whose
-                      // weights come after the batches; triangles: of idx)
+  uint16_t* queue;    // [budget]   triangles: the batch's undecided candidates, in the space of idx
+                      // (fibers: in that of w, past the weights of the pairs so far)
   uint16_t* idx;      // [budget]   triangles: the slots of a batch's new pairs; after the batches:
                       // grouped order -> pair (fibers: in the space of ckey)
   uint64_t* sbm;      // [64] batch: bit c set where a slot's first candidate is c
   uint32_t* spre;     // [64] slot starts below each word
-  int32_t* brec;      // [kBlock][9] the slot's primitive vertices (record words 0..8; after
-                      // the batches: the per-key counters, then starts)
+  int32_t* brec;      // [kBlock][9] the slot's primitive vertices (record words 0..8; fibers: words
+                      // 0..5 and the segment's length; after the batches: the per-key counters, then
+                      // starts)
   // the current record batch; after the batches its space holds the voxels' keys
   double* binv;       // [kBlock] fibers: the slot's 1 / |B - A|^2 (lattice units); triangles:
                       // tri_area_under's factor from projected to true area
@@ -426,7 +427,7 @@ __device__ __forceinline__ UnitLds carve_unit_lds(char* base) {
   L.key = reinterpret_cast<uint16_t*>(take(CAND * 2));
   L.ckey = reinterpret_cast<uint16_t*>(take(CAND * 2));
   L.idx = KIND == 0 ? reinterpret_cast<uint16_t*>(take(CAND * 2)) : L.ckey;
-  L.queue = KIND == 0 ? L.idx : reinterpret_cast<uint16_t*>(L.w);
+  L.queue = L.idx;
   L.spre = reinterpret_cast<uint32_t*>(take(64 * 4));
   L.brec = reinterpret_cast<int32_t*>(take(kBlock * 9 * 4));
   L.tmp32 = reinterpret_cast<int32_t*>(take((kWaves + 1) * 4));
@@ -469,6 +470,7 @@ __device__ __forceinline__ int32_t load_batch(const UnitLds& S, const int32_t* _
       r[4 * k + 3] = v.w;
     }
     if (KIND == 0) dir = dirs[p];
+    else dir.w = dirs[p].w;
     c = int32_t(clip_box(r, o, sz, lo, n));
   }
   // candidates (below 2^21 per batch) and kept slots (bits 21 and up) in one scan
@@ -481,9 +483,10 @@ __device__ __forceinline__ int32_t load_batch(const UnitLds& S, const int32_t* _
     S.boff[q] = off;
     S.bbox[q] = pack_slot_box(o, lo, n);
 #pragma unroll
-    for (int k = 0; k < 9; ++k) S.brec[q * 9 + k] = r[k];
+    for (int k = 0; k < (KIND == 0 ? 9 : 6); ++k) S.brec[q * 9 + k] = r[k];
     if (KIND == 1) {
       S.bpatch[q] = r[15];
+      S.brec[q * 9 + 6] = __float_as_int(dir.w);
       S.binv[q] = cap_inv_len2(r);
     } else {
       uint32_t how;
@@ -601,6 +604,9 @@ __device__ __forceinline__ void write_voxel(const Stage& st, int64_t i, uint64_t
 // Bound by VALU issue (three quarters of the cycles) and the latencies above.  The whole brushed
 // surface (149 M pairs): 7.95 -> 5.75 ms with the area by integration (2.2 ms of it; 3.7 before), unit
 // codes spread over 4 bits instead of 21, and half the candidates decided by a vertex in the box.
+// Fibers are weighed from the records in LDS, one reciprocal an axis: 14 patches (64,000 units) 2.46 ->
+// 2.21 ms, a weave (10,000 units) 0.515 -> 0.460 ms against records gathered again from memory after
+// the batches and two divisions an axis.
 template <int KIND, int CAND>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(unit_waves<KIND>(CAND)))) k_unit(const int32_t* __restrict__ rec, const float4* __restrict__ dirs,
                                                  const uint32_t* __restrict__ rprim,
@@ -672,13 +678,16 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
       // Test in two rounds so that lanes stay busy: a cheap filter decides most candidates and
       // queues the rest (fibers: the centre-ball filter; triangles: a vertex in the box), then the
       // queue gets the full test.
-      // Each wave works on its own candidates and drains its own queue (a quarter of the queue
-      // space: a wave holds at most a quarter of a unit's candidates); every candidate records
+      // Each wave works on its own candidates and drains its own queue (fibers: 16-bit entries from the
+      // first free weight on; the pairs so far and the batch's candidates are within the budget, and
+      // the four waves' rounded-up shares within twice the batch's, or its last); every candidate records
       // its outcome in place, and the touching ones are then compacted in candidate order,
       // which is primitive order.
       const int wv = tid >> 6, lane = tid & 63;
       const uint64_t lt = (uint64_t(1) << lane) - 1;
-      uint16_t* wq = S.queue + wv * (CAND / kWaves);
+      uint16_t* wq = KIND == 0 ? S.queue + wv * (CAND / kWaves)
+                               : reinterpret_cast<uint16_t*>(S.w + (np < CAND - cb ? np : CAND - cb)) +
+                                     wv * 64 * ((cb + kBlock - 1) / kBlock);
       int32_t nq = 0;                                  // this wave's queue (uniform)
       for (int32_t b0 = wv * 64; b0 < cb; b0 += kBlock) {
         const int32_t c = b0 + lane;
@@ -746,23 +755,31 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
             if (q < CAND) {
               const int sl = find_slot(S, c);
               S.key[q] = uint16_t(S.ckey[c] & (kTouch - 1));
-              S.prim[q] = uint32_t(S.bprim[sl]);
-              if (KIND == 0) S.idx[q] = uint16_t(sl);
+              if (KIND == 0) {
+                S.prim[q] = uint32_t(S.bprim[sl]);
+                S.idx[q] = uint16_t(sl);
+              } else {
+                S.prim[q] = uint32_t(sl);             // until the pair is weighed
+              }
             } else {
               flag_set(stats, VX_FLAG_UNIT_CAPACITY);   // planning and test disagree: never expected
             }
           }
           base += int32_t(__popcll(mh));
         }
-        // triangles: the batch's pairs are weighed now, from the records still in LDS
-        if (KIND == 0) {
-          __syncthreads();
-          const int32_t q1 = np + tot < CAND ? np + tot : CAND;
-          for (int32_t q = np + tid; q < q1; q += kBlock) {
-            const int sl = S.idx[q];
-            int32_t v[3];
-            cell_voxel(U.o, c0 + S.key[q], v);
-            S.w[q] = tri_area_under(S.brec + sl * 9, v, L.Sb, uint32_t(S.bpatch[sl]), S.binv[sl]);
+        // the batch's pairs are weighed now, from the records still in LDS
+        __syncthreads();
+        const int32_t q1 = np + tot < CAND ? np + tot : CAND;
+        for (int32_t q = np + tid; q < q1; q += kBlock) {
+          const int sl = KIND == 0 ? int(S.idx[q]) : int(S.prim[q]);
+          const int32_t* r = S.brec + sl * 9;
+          int32_t v[3];
+          cell_voxel(U.o, c0 + S.key[q], v);
+          if (KIND == 0) {
+            S.w[q] = tri_area_under(r, v, L.Sb, uint32_t(S.bpatch[sl]), S.binv[sl]);
+          } else {
+            S.w[q] = fib_weight(r, v, lat_q(lats, S.bpatch[sl], L).Sb, __int_as_float(r[6]));
+            S.prim[q] = uint32_t(S.bprim[sl]);
           }
         }
         np += tot;
@@ -795,16 +812,6 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
     uint16_t* kst = reinterpret_cast<uint16_t*>(S.brec);                 // [4096] then starts
     uint16_t* vkey = S.vkey;                                             // [nv] key of voxel v
     for (int32_t j = tid; j < kUnitKeys / 2; j += kBlock) kcw[j] = 0u;
-    if (KIND == 1) {                              // (triangles were weighed batch by batch)
-      for (int32_t i = tid; i < npairs; i += kBlock) {
-        const uint32_t p = S.prim[i];
-        const int32_t* r = rec + int64_t(p) * kRec;
-        const LatQ Lp = lat_q(lats, r[15], L);
-        int32_t v[3];
-        cell_voxel(U.o, c0 + S.key[i], v);
-        S.w[i] = fib_weight(r, v, Lp.Sb, dirs[p].w);
-      }
-    }
     __syncthreads();
     uint32_t slot[CAND / kBlock];
 #pragma unroll
