@@ -14,12 +14,21 @@
 // outside the grid get a key above every voxel's and are dropped after the sort.
 #pragma clang fp contract(off)
 
+#include "geom.hpp"
 #include "vx_internal.hpp"
 
 namespace vx {
 namespace {
 
-enum { SC_TOTAL = 0, SC_SEGS = 1, SC_VOX = 2, SC_QMAX = 3, SC_INSIDE = 4, SC_OUTSIDE = 5, SC_WORDS = 6 };
+enum { SC_TOTAL = 0, SC_SEGS = 1, SC_VOX = 2, SC_QMAX = 3, SC_SORT = 4, SC_OUTSIDE = 5, SC_WORDS = 6,
+       SC_RECORDS = 7 };
+
+// A record: the voxel's key, the id of a chord or triangle and how many of its samples lie there, in
+// one word or with the key apart.
+struct RecordBits {
+  int id, cnt;        // of the id, and above it of the count less one
+  bool packed;        // key << (cnt + id) | (count - 1) << id | id; else the key and the rest apart
+};
 
 struct SampWs {
   int64_t* ctl;       // [8] (SC_*)
@@ -27,22 +36,37 @@ struct SampWs {
   double* q;          // triangles: [n] squared twice-area
   float4* dirs;       // fibers: [n_pts * m] chord tangents; triangles: [n] normals; with the weight of
                       // each of the chord's or triangle's samples
-  PairBufs a, b;      // samples (key, chord or triangle id), ping-pong for the sort; packed: no prim
-  int id_bits;        // packed samples: key << id_bits | id; 0: key and id apart
+  PairBufs a, b;      // sample records (key, chord or triangle id), ping-pong for the sort; packed: no prim
+  RecordBits bits;
+  int32_t* filled;    // triangles: [kEmitGrid * kWaves] records that each wave of the emission wrote
   int32_t* hist;
   int64_t* partial;
   uint64_t* mask;     // [max_samples / 64] one bit per sorted sample: the first of its key
   int64_t* start;     // [max_vox + 2] first sample of every key
 };
 
-// 64-bit keys with the id below the voxel's bits where the two and the outside bit fit one word: a sort
-// pass then moves 16 bytes a sample, not 24 (41.7 M samples: 0.19 ms, 0.25 ms apart).  32-bit keys stay
-// apart from their ids: packing them would save nothing and double what the digit counts read.
-int samp_id_bits(int kind, int64_t n_prims, int log2R, int sub) {
+// One word where 64-bit keys, the bit for samples outside (fibers) and the id fit it: a sort pass then moves 16 bytes a
+// record, not 24 (41.7 M: 0.19 ms, 0.25 ms apart).  32-bit keys stay apart: packing them would save
+// nothing and double what the digit counts read.  Counts take what bits are left, up to the 6 that a
+// wave's 64 samples need.
+RecordBits record_bits(int kind, int64_t n_prims, int log2R, int sub) {
   const int64_t ids = n_prims * (kind == 0 ? 1 : int64_t(sub));
-  int bits = 1;
-  while (bits < 32 && (int64_t(1) << bits) < ids) ++bits;
-  return log2R > 10 && 3 * log2R + 1 + bits <= 64 ? bits : 0;
+  RecordBits r{1, 0, false};
+  while (r.id < 32 && (int64_t(1) << r.id) < ids) ++r.id;
+  const int left = 64 - (3 * log2R + (kind == 0 ? 0 : 1) + r.id);
+  r.packed = log2R > 10 && left >= 0;
+  const int room = r.packed ? left : 32 - r.id;
+  r.cnt = kind != 0 ? 0 : (room < 6 ? room : 6);
+  return r;
+}
+
+// Blocks of the emission of triangles' samples, whose waves take equal stretches of them: a few rows of
+// 64 at least (the sort's first pass serves its blocks' stretches one by one), one fill of the chip at
+// most: six blocks a CU by their LDS (41.7 M samples: 0.30 ms; 0.33 with four, 0.31 with eight).
+constexpr int kEmitGrid = 1536;
+int emit_blocks(int64_t max_samples) {
+  const int64_t b = (max_samples + 1024 * kWaves - 1) / (1024 * kWaves);
+  return int(b < 1 ? 1 : (b > kEmitGrid ? kEmitGrid : b));
 }
 
 size_t samp_ws_layout(int kind, int64_t n_prims, int64_t max_samples, int64_t max_vox, int log2R, int sub,
@@ -54,12 +78,13 @@ size_t samp_ws_layout(int kind, int64_t n_prims, int64_t max_samples, int64_t ma
   x.q = cv.take<double>(kind == 0 ? n_prims : 1);
   x.dirs = cv.take<float4>(kind == 0 ? n_prims : n_prims * int64_t(sub));
   const int kb = log2R > 10 ? 8 : 4;
-  x.id_bits = samp_id_bits(kind, n_prims, log2R, sub);
+  x.bits = record_bits(kind, n_prims, log2R, sub);
   for (PairBufs* p : {&x.a, &x.b}) {
     p->keys = cv.take<uint8_t>(max_samples * kb);
     p->w = nullptr;
-    p->prim = x.id_bits ? nullptr : cv.take<uint32_t>(max_samples);
+    p->prim = x.bits.packed ? nullptr : cv.take<uint32_t>(max_samples);
   }
+  x.filled = cv.take<int32_t>(kind == 0 ? kEmitGrid * kWaves : 0);
   x.hist = cv.take<int32_t>(int64_t(kRadixBuckets) * kGrid);
   x.partial = cv.take<int64_t>(kGrid + 1);
   x.mask = cv.take<uint64_t>((max_samples + 63) / 64);
@@ -174,18 +199,19 @@ __global__ void __launch_bounds__(kBlock) k_samp_fib_count(const float* __restri
   }
 }
 
-// the emitted samples; the sort's buffers
+// the emitted records: the sort's buffers
 template <class Key>
 struct SampOut {
   Key* keys;
   uint32_t* ids;
-  int id_bits;
-  __device__ __forceinline__ void put(int64_t o, Key key, uint32_t id) const {
-    if (id_bits) {
-      keys[o] = Key(uint64_t(key) << id_bits | id);
+  RecordBits bits;
+  __device__ __forceinline__ void put(int64_t o, Key key, uint32_t id, int count) const {
+    const uint64_t low = uint64_t(count - 1) << bits.id | id;
+    if (bits.packed) {
+      keys[o] = Key(uint64_t(key) << (bits.id + bits.cnt) | low);
     } else {
       keys[o] = key;
-      ids[o] = id;
+      ids[o] = uint32_t(low);
     }
   }
 };
@@ -219,7 +245,7 @@ __global__ void __launch_bounds__(kBlock) k_samp_fib_emit(const float* __restric
         for (int x = 0; x < 3; ++x) X[x] = fma(fr, d[x], A[x]);
         const Key key = sample_key<Key>(X, G, outside);
         outs += key == outside;
-        out.put(o, key, id);
+        out.put(o, key, id, 1);
         ++o;
       }
     }
@@ -303,59 +329,85 @@ __global__ void __launch_bounds__(kBlock) k_samp_tri_count(const float* __restri
 
 __device__ __forceinline__ double radical_inverse2(uint32_t k) { return double(__brev(k)) * 0x1p-32; }
 
-// Each block takes an equal range of the samples, whatever triangles they fall in, and walks through
-// the range's triangles 256 at a time: their frames and first samples go to LDS, then one thread a sample
-// finds its triangle by bisection there.  Bound by FP64 arithmetic and the writes, which are contiguous
-// (41.7 M samples of 4.7 M triangles: 0.24 ms; with one thread a triangle, its writes apart, 0.50 ms).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Each wave takes an equal stretch of the samples, whatever triangles they fall in, and walks through
+// its triangles 64 at a time: their frames and first samples go to LDS, then one lane a sample finds
+// its triangle by bisection there.  A triangle's samples that fall in one voxel leave as one record
+// with their count, where the first of them stood: the sort keeps records in this order, so the
+// voxel adds the same numbers in the same order.  They find each other, within a row of 64, through
+// a table in LDS: the lowest lane of a slot is taken for the first if key and triangle agree (two
+// voxels in one slot: the other's samples stay single).  A wave's records lie at the start of its
+// stretch; samples outside the grid leave none.  Bound by FP64 arithmetic (41.7 M samples of 4.7 M triangles: 0.30 ms, leaving 16.7 M
+// records; 0.24 ms as records of one sample each, but every sort pass 0.25 ms instead of 0.11).
+constexpr int kSampSlots = 256;
 template <class Key>
 __global__ void __launch_bounds__(kBlock) k_samp_tri_emit(const float* __restrict__ tris, int64_t n, Grid64 G,
                                                           const int64_t* __restrict__ soff,
                                                           int64_t* __restrict__ ctl, int64_t cap, Key outside,
-                                                          SampOut<Key> out) {
-  __shared__ double fr[9][kBlock];                  // third vertex; the edges from it to the other two
-  __shared__ int32_t first[kBlock + 1];             // less the tile's first sample
+                                                          SampOut<Key> out, int32_t* __restrict__ filled) {
+  __shared__ double frames[kWaves][10][64];         // third vertex; edges from it to the others; 1 / samples
+  __shared__ int32_t firsts[kWaves][65];            // less the tile's first sample
+  __shared__ uint32_t slots[kWaves][kSampSlots], more[kWaves][64];
+  const int lane = lane_id(), wv = threadIdx.x >> 6, wave = int(blockIdx.x) * kWaves + wv;
+  double(*fr)[64] = frames[wv];
+  int32_t* first = firsts[wv];
+  uint32_t* slot = slots[wv];
   const int64_t total = ctl[SC_TOTAL];
-  if (total > cap) return;
-  const int64_t range = (total + gridDim.x - 1) / gridDim.x;
-  const int64_t o0 = int64_t(blockIdx.x) * range, o1 = o0 + range < total ? o0 + range : total;
-  if (o0 >= o1) return;
+  const int64_t waves = int64_t(gridDim.x) * kWaves, range = (total + waves - 1) / waves;
+  const int64_t o0 = wave * range, o1 = o0 + range < total ? o0 + range : total;
+  if (total > cap || o0 >= o1) {                    // over capacity: nothing is written
+    if (lane == 0) filled[wave] = 0;
+    return;
+  }
   // the triangle of sample o0: the last t with soff[t] <= o0, 64 probes a round
   int64_t tlo = 0, thi = n;
   while (thi - tlo > 1) {
-    const int64_t step = (thi - tlo + 63) / 64, p = tlo + lane_id() * step;
+    const int64_t step = (thi - tlo + 63) / 64, p = tlo + lane * step;
     const int64_t c = __popcll(__ballot(p < thi && soff[p] <= o0));
     tlo += (c - 1) * step;
     thi = tlo + step < thi ? tlo + step : thi;
   }
-  const int tid = threadIdx.x;
-  int64_t outs = 0;
-  for (int64_t t0 = tlo; t0 < n; t0 += kBlock) {
-    const int nt = int(n - t0 < kBlock ? n - t0 : kBlock);
+#pragma unroll
+  for (int i = 0; i < kSampSlots; i += 64) slot[i + lane] = 0xffffffffu;
+  uint32_t row = 0xffffffffu >> 6;                  // counts down: a row's entries are below all earlier ones
+  const int most = 1 << out.bits.cnt;               // samples of a record
+  int64_t outs = 0, o = o0;
+  for (int64_t t0 = tlo; t0 < n; t0 += 64) {
+    const int nt = int(n - t0 < 64 ? n - t0 : 64);
     const int64_t base = soff[t0];
     if (base >= o1) break;
-    if (tid < nt) {
+    if (lane < nt) {
       double g[3][3], c[3];
-      tri_grid(tris, t0 + tid, G, g, c);
+      tri_grid(tris, t0 + lane, G, g, c);
 #pragma unroll
       for (int x = 0; x < 3; ++x) {
-        fr[x][tid] = g[2][x];
-        fr[3 + x][tid] = g[0][x] - g[2][x];
-        fr[6 + x][tid] = g[1][x] - g[2][x];
+        fr[x][lane] = g[2][x];
+        fr[3 + x][lane] = g[0][x] - g[2][x];
+        fr[6 + x][lane] = g[1][x] - g[2][x];
       }
-      first[tid] = int32_t(soff[t0 + tid] - base);
+      const int64_t s0 = soff[t0 + lane];
+      first[lane] = int32_t(s0 - base);
+      fr[9][lane] = recip(double(soff[t0 + lane + 1] - s0));
     }
-    if (tid == 0) first[nt] = int32_t(soff[t0 + nt] - base);
-    __syncthreads();
+    if (lane == 0) first[nt] = int32_t(soff[t0 + nt] - base);
+    wave_lds_fence();
     const int32_t q0 = int32_t(o0 > base ? o0 - base : 0);
     const int32_t q1 = int32_t(o1 - base < first[nt] ? o1 - base : first[nt]);
-    for (int32_t q = q0 + tid; q < q1; q += kBlock) {
+    for (int32_t qr = q0; qr < q1; qr += 64, --row) {
+      const int32_t q = qr + lane < q1 ? qr + lane : q1 - 1;     // past the end: the last sample again, dropped
+      const bool on = qr + lane < q1;
       int lo = 0, hi = nt;
       while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (first[mid] <= q) lo = mid; else hi = mid;
       }
       const int32_t k = q - first[lo];
-      const double u1 = (double(k) + 0.5) / double(first[lo + 1] - first[lo]);
+      // (half-odd numbers below 2^21 over integers below it: the correctly rounded quotient)
+      const double u1 = quotient(double(k) + 0.5, double(first[lo + 1] - first[lo]), fr[9][lo]);
       const double u2 = radical_inverse2(uint32_t(k));
       // Heitz's map, both halves by selects
       const bool up = u2 > u1;
@@ -366,10 +418,37 @@ __global__ void __launch_bounds__(kBlock) k_samp_tri_emit(const float* __restric
 #pragma unroll
       for (int x = 0; x < 3; ++x) X[x] = fma(b0, fr[3 + x][lo], fma(b1, fr[6 + x][lo], fr[x][lo]));
       const Key key = sample_key<Key>(X, G, outside);
-      outs += key == outside;
-      out.put(base + q, key, uint32_t(t0 + lo));
+      outs += on && key == outside;
+      bool put = on;
+      int count = 1;
+      if (most > 1) {
+        const uint32_t h = (uint32_t(key) * 0x9e3779b1u + uint32_t(uint64_t(key) >> 32) + uint32_t(lo) * 0x85ebca6bu) >> 24;
+        more[wv][lane] = 0;
+        if (on) atomicMin(&slot[h], row << 6 | uint32_t(lane));
+        wave_lds_fence();
+        const int lead = on ? int(slot[h] & 63u) : lane;
+        bool same = __shfl(lo, lead, 64) == lo && __shfl(uint32_t(key), lead, 64) == uint32_t(key);
+        if (sizeof(Key) == 8)
+          same = same && __shfl(uint32_t(uint64_t(key) >> 32), lead, 64) == uint32_t(uint64_t(key) >> 32);
+        if (on && same && lead != lane)              // joins the first's record while that has room
+          put = int(atomicAdd(&more[wv][lead], 1u)) >= most - 1;
+        wave_lds_fence();
+        const int joined = int(more[wv][lane]);
+        if (put && (lead == lane || !same)) count = 1 + (joined < most - 1 ? joined : most - 1);
+        wave_lds_fence();
+      }
+      put = put && key != outside;
+      const uint64_t m = __ballot(put);
+      if (put)
+        out.put(o + __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0)), key,
+                uint32_t(t0 + lo), count);
+      o += __popcll(m);
     }
-    __syncthreads();
+    wave_lds_fence();
+  }
+  if (lane == 0) {
+    filled[wave] = int32_t(o - o0);
+    atomicAdd(reinterpret_cast<unsigned long long*>(ctl + SC_RECORDS), (unsigned long long)(o - o0));
   }
   add_outside(outs, ctl);
 }
@@ -395,11 +474,11 @@ struct CntIn {
   const int64_t* a;
   __device__ int64_t operator()(int64_t i) const { return a[i]; }
 };
-// the sort's element count: the samples, or none when they did not fit; and its 64s
-__global__ void k_samp_n(int64_t* ctl, int64_t cap) {
+// the sort's element count: the records (merged) or samples, or none when they did not fit; and its 64s
+__global__ void k_samp_n(int64_t* ctl, int64_t cap, bool merged) {
   if (threadIdx.x != 0) return;
-  const int64_t n = ctl[SC_TOTAL] <= cap ? ctl[SC_TOTAL] : 0;
-  ctl[SC_INSIDE] = n;
+  const int64_t n = ctl[SC_TOTAL] <= cap ? ctl[merged ? SC_RECORDS : SC_TOTAL] : 0;
+  ctl[SC_SORT] = n;
   ctl[SC_WORDS] = (n + 63) / 64;
 }
 // voxel starts from the head masks: a word's offset is the voxels that start before it
@@ -421,42 +500,47 @@ struct SegTotal {
   int64_t* ctl;
   int64_t cap;
   __device__ void operator()(int64_t total, int64_t) const {
-    if (total < cap) start[total] = ctl[SC_INSIDE];
+    if (total < cap) start[total] = ctl[SC_SORT];
     ctl[SC_SEGS] = total;
   }
 };
 
-// voxels = key segments, less the trailing one of samples outside the grid
-__global__ void k_samp_finish(int64_t* ctl, int64_t* stats, int64_t vcap) {
+// voxels = key segments, less the trailing one of samples outside the grid (fibers)
+__global__ void k_samp_finish(int kind, int64_t* ctl, int64_t* stats, int64_t cap, int64_t vcap) {
   if (threadIdx.x != 0) return;
   const int64_t out = ctl[SC_OUTSIDE];
-  const int64_t nv = ctl[SC_SEGS] - (out > 0);
-  stats[VX_STAT_PAIRS] = ctl[SC_INSIDE] - out;
+  const int64_t nv = ctl[SC_SEGS] - (kind == 1 && out > 0);
+  stats[VX_STAT_PAIRS] = ctl[SC_TOTAL] <= cap ? ctl[SC_TOTAL] - out : 0;
   stats[VX_STAT_VOXELS] = nv;
   if (nv > vcap)
     atomicOr(reinterpret_cast<unsigned long long*>(stats + VX_STAT_FLAGS), (unsigned long long)VX_FLAG_VOXEL_CAPACITY);
   ctl[SC_VOX] = nv <= vcap ? nv : 0;
 }
 
-// the sorted samples' keys and ids
+// the sorted records' keys, ids and counts
 template <class Key>
 struct Sorted {
   const Key* keys;
   const uint32_t* ids;
-  int id_bits;
-  __device__ __forceinline__ Key key(int64_t i) const { return Key(uint64_t(keys[i]) >> id_bits); }
+  RecordBits bits;
+  __device__ __forceinline__ Key key(int64_t i) const {
+    return bits.packed ? Key(uint64_t(keys[i]) >> (bits.id + bits.cnt)) : keys[i];
+  }
   template <bool PACKED>
-  __device__ __forceinline__ uint32_t id(int64_t i) const {
-    return PACKED ? uint32_t(keys[i]) & uint32_t((uint64_t(1) << id_bits) - 1) : ids[i];
+  __device__ __forceinline__ uint32_t id(int64_t i, int& count) const {
+    const uint64_t r = PACKED ? uint64_t(keys[i]) : uint64_t(ids[i]);
+    count = 1 + int((r >> bits.id) & ((uint64_t(1) << bits.cnt) - 1));
+    return uint32_t(r & ((uint64_t(1) << bits.id) - 1));
   }
 };
+
 // one bit a sample: does its voxel start here?  One read of the samples instead of the two that a scan
-// over them takes (41.7 M samples: 0.14 ms with the scan over the masks, 0.22 ms).
+// over them takes (16.7 M records: 0.06 ms with the scan over the masks).
 template <class Key>
 __global__ void __launch_bounds__(kBlock) k_samp_heads(Sorted<Key> s, const int64_t* __restrict__ ctl,
                                                        uint64_t* __restrict__ mask) {
   constexpr int kRows = 8;
-  const int64_t n = ctl[SC_INSIDE], words = ctl[SC_WORDS];
+  const int64_t n = ctl[SC_SORT], words = ctl[SC_WORDS];
   const int64_t waves = int64_t(gridDim.x) * kWaves, wave = int64_t(blockIdx.x) * kWaves + (threadIdx.x >> 6);
   for (int64_t w0 = wave * kRows; w0 < words; w0 += waves * kRows) {
     Key k[kRows], p[kRows];
@@ -481,28 +565,27 @@ __global__ void __launch_bounds__(kBlock) k_samp_back(const Key* __restrict__ ki
                                                       Key* __restrict__ kout, uint32_t* __restrict__ iout,
                                                       const int64_t* __restrict__ ctl) {
   if (ctl[SC_OUTSIDE] == 0) return;
-  const int64_t n = ctl[SC_INSIDE];
+  const int64_t n = ctl[SC_SORT];
   for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += int64_t(gridDim.x) * kBlock) {
     kout[i] = kin[i];
     if (iin) iout[i] = iin[i];
   }
 }
 
-// A wave sums 64 voxels, one a lane, each voxel's samples in order.  The voxels' samples are one stretch
-// of the sorted list: its ids are read and their directions gathered 512 at a time, whoever's they are,
-// into LDS, and each lane takes its own from there.  Bound by the gathers (41.7 M samples, 3.1 M voxels:
-// 0.14 ms; with each lane reading its own samples from memory 0.54 ms).
+// A wave sums 64 voxels, one a lane, each voxel's samples in order.  The voxels' records are one stretch
+// of the sorted list: their ids are read and their directions gathered 512 at a time, whoever's they
+// are, into LDS, and each lane takes its own from there, a record's direction as often as it counts.
+// Bound by the gathers (41.7 M samples in 16.7 M records, 3.1 M voxels: 0.10 ms; with each lane reading
+// its own samples from memory 0.54 ms).
 constexpr int kReduceTile = 512;
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 template <int KIND, class Key, bool PACKED>
 __global__ void __launch_bounds__(kBlock) k_samp_reduce(Sorted<Key> sorted, const int64_t* __restrict__ start,
                                                         const float4* __restrict__ dirs,
                                                         const int64_t* __restrict__ ctl, vx_voxels out) {
   __shared__ float4 stage[kWaves][kReduceTile];
+  __shared__ uint8_t counts[kWaves][kReduceTile];   // 1 to 64
   float4* st = stage[threadIdx.x >> 6];
+  uint8_t* sc = counts[threadIdx.x >> 6];
   const int64_t nv = ctl[SC_VOX];
   const int64_t waves = int64_t(gridDim.x) * kWaves, wave = int64_t(blockIdx.x) * kWaves + (threadIdx.x >> 6);
   for (int64_t v0 = wave * 64; v0 < nv; v0 += waves * 64) {
@@ -510,24 +593,32 @@ __global__ void __launch_bounds__(kBlock) k_samp_reduce(Sorted<Key> sorted, cons
     const int64_t a = start[v < vend ? v : vend], b = start[v < vend ? v + 1 : vend];
     const int64_t last = start[vend];
     Moment m{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    uint32_t samples = 0;
     for (int64_t j0 = start[v0]; j0 < last; j0 += kReduceTile) {
       float4 d[kReduceTile / 64];
 #pragma unroll
       for (int r = 0; r < kReduceTile / 64; ++r) {
         const int64_t j = j0 + r * 64 + lane_id();
-        d[r] = dirs[sorted.template id<PACKED>(j < last ? j : last - 1)];
+        int c;
+        d[r] = dirs[sorted.template id<PACKED>(j < last ? j : last - 1, c)];
+        sc[r * 64 + lane_id()] = uint8_t(c);
       }
 #pragma unroll
       for (int r = 0; r < kReduceTile / 64; ++r)
         st[r * 64 + lane_id()] = d[r];
       wave_lds_fence();
       const int lo = int(a > j0 ? a - j0 : 0), hi = int(b - j0 < kReduceTile ? b - j0 : kReduceTile);
-      for (int q = lo; q < hi; ++q) accum_pair<KIND>(m, st[q].w, st[q]);
+      for (int q = lo; q < hi; ++q) {
+        const float4 t = st[q];
+        const int c = sc[q];
+        samples += uint32_t(c);
+        for (int i = 0; i < c; ++i) accum_pair<KIND>(m, t.w, t);
+      }
       wave_lds_fence();
     }
     if (v >= vend) continue;
     static_cast<Key*>(out.keys)[v] = sorted.key(a);
-    out.count[v] = uint32_t(b - a);
+    out.count[v] = samples;
     out.w[v] = m.W;
     out.S[v] = m.xx;
     out.S[out.cap + v] = m.yy;
@@ -546,35 +637,38 @@ int blocks_for(int64_t n) {
 template <class Key>
 void samp_back(int kind, const vx_grid* g, int64_t max_samples, const SampWs& w, const vx_voxels* out,
                int64_t* stats, hipStream_t s) {
-  // one bit above the voxels' keys holds the samples outside the grid.  Where the voxels' bits fill
-  // the digits, that bit would cost a pass of its own (0.26 ms of 41.7 M samples): it runs only when
-  // there are such samples, and its empty launches take 15 us.
+  // Fibers: one bit above the voxels' keys holds the samples outside the grid.  Where the voxels' bits
+  // fill the digits, that bit would cost a pass of its own (0.26 ms of 41.7 M samples): it runs only
+  // when there are such samples, and its empty launches take 15 us.
   const int voxel_bits = 3 * g->log2_res;
-  const bool own_pass = voxel_bits % kRadixBits == 0;
-  hipLaunchKernelGGL(k_samp_n, dim3(1), dim3(64), 0, s, w.ctl, max_samples);
-  const PairBufs P = radix_sort_pairs(sizeof(Key) == 8, own_pass ? voxel_bits : voxel_bits + 1, w.a, w.b, w.a,
-                                      w.ctl + SC_INSIDE, max_samples, w.hist, w.partial, s, w.id_bits);
+  const bool own_pass = kind == 1 && voxel_bits % kRadixBits == 0;
+  hipLaunchKernelGGL(k_samp_n, dim3(1), dim3(64), 0, s, w.ctl, max_samples, kind == 0);
+  const int low = w.bits.packed ? w.bits.id + w.bits.cnt : 0;
+  const PairBufs P = radix_sort_pairs(sizeof(Key) == 8, kind == 0 || own_pass ? voxel_bits : voxel_bits + 1, w.a, w.b, w.a,
+                                      w.ctl + SC_SORT, max_samples, w.hist, w.partial, s, low,
+                                      SortRegions{w.ctl + SC_TOTAL, kind == 0 ? w.filled : nullptr,
+                                                  emit_blocks(max_samples) * kWaves});
   if (own_pass) {
     const PairBufs Q = P.keys == w.a.keys ? w.b : w.a;
-    radix_sort_pass(sizeof(Key) == 8, P, Q, w.ctl + SC_INSIDE, max_samples, voxel_bits + w.id_bits, w.hist,
+    radix_sort_pass(sizeof(Key) == 8, P, Q, w.ctl + SC_SORT, max_samples, voxel_bits + low, w.hist,
                     w.partial, w.ctl + SC_OUTSIDE, s);
     hipLaunchKernelGGL(k_samp_back<Key>, dim3(blocks_for(max_samples)), dim3(kBlock), 0, s, (const Key*)Q.keys,
                        Q.prim, (Key*)P.keys, P.prim, w.ctl);
   }
-  const Sorted<Key> sorted{(const Key*)P.keys, P.prim, w.id_bits};
+  const Sorted<Key> sorted{(const Key*)P.keys, P.prim, w.bits};
   {
     VX_TIMED("sample_heads", s);
     hipLaunchKernelGGL(k_samp_heads<Key>, dim3(blocks_for(max_samples)), dim3(kBlock), 0, s, sorted, w.ctl, w.mask);
     device_scan(MaskIn{w.mask}, MaskOut{w.mask, w.start, out->cap + 2}, SegTotal{w.start, w.ctl, out->cap + 2},
                 w.ctl + SC_WORDS, (max_samples + 63) / 64, w.partial, s);
-    hipLaunchKernelGGL(k_samp_finish, dim3(1), dim3(64), 0, s, w.ctl, stats, out->cap);
+    hipLaunchKernelGGL(k_samp_finish, dim3(1), dim3(64), 0, s, kind, w.ctl, stats, max_samples, out->cap);
   }
   VX_TIMED("sample_reduce", s);
   const auto reduce = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(blocks_for(out->cap)), dim3(kBlock), 0, s, sorted, w.start, w.dirs, w.ctl, *out);
   };
   if constexpr (sizeof(Key) == 8) {
-    if (w.id_bits) return kind == 0 ? reduce(k_samp_reduce<0, Key, true>) : reduce(k_samp_reduce<1, Key, true>);
+    if (w.bits.packed) return kind == 0 ? reduce(k_samp_reduce<0, Key, true>) : reduce(k_samp_reduce<1, Key, true>);
   }
   kind == 0 ? reduce(k_samp_reduce<0, Key, false>) : reduce(k_samp_reduce<1, Key, false>);
 }
@@ -619,12 +713,12 @@ vx_status sample_voxelize(int kind, const vx_grid* g, const float* data, int64_t
     const uint64_t out64 = uint64_t(1) << (3 * g->log2_res);
 #define VX_SAMP_EMIT(K)                                                                                              \
   if (kind == 0)                                                                                                     \
-    hipLaunchKernelGGL(k_samp_tri_emit<K>, dim3(blocks_for(max_samples)), dim3(kBlock), 0, s, data, n_prims, G,     \
-                       w.cnt, w.ctl, max_samples, K(out64), (SampOut<K>{(K*)w.a.keys, w.a.prim, w.id_bits}));             \
+    hipLaunchKernelGGL(k_samp_tri_emit<K>, dim3(emit_blocks(max_samples)), dim3(kBlock), 0, s, data, n_prims, G,     \
+                       w.cnt, w.ctl, max_samples, K(out64), (SampOut<K>{(K*)w.a.keys, w.a.prim, w.bits}), w.filled);      \
   else                                                                                                               \
     hipLaunchKernelGGL(k_samp_fib_emit<K>, dim3(blocks_for(n_prims)), dim3(kBlock), 0, s, data, n_prims, offsets,   \
                        n_fib, sp->chords_per_segment, sp->samples_per_chord, G, w.cnt, w.ctl, max_samples, K(out64), \
-                       (SampOut<K>{(K*)w.a.keys, w.a.prim, w.id_bits}))
+                       (SampOut<K>{(K*)w.a.keys, w.a.prim, w.bits}))
     if (key64) { VX_SAMP_EMIT(uint64_t); } else { VX_SAMP_EMIT(uint32_t); }
 #undef VX_SAMP_EMIT
   }

@@ -42,6 +42,30 @@ __device__ __forceinline__ int64_t sort_chunk(int64_t n) {
   return (c + kSortBlock - 1) / kSortBlock * kSortBlock;
 }
 
+// the stretches that a block serves: its chunk of dense input, or its share of the regions
+struct SortSpan {
+  int r, r1;
+  int64_t b0, b1;
+};
+__device__ __forceinline__ SortSpan first_span(const SortRegions& g) {
+  if (!g.filled) return SortSpan{0, 1, 0, 0};
+  return SortSpan{int(int64_t(blockIdx.x) * g.regions / gridDim.x), int(int64_t(blockIdx.x + 1) * g.regions / gridDim.x),
+                  0, 0};
+}
+__device__ __forceinline__ bool next_span(SortSpan& s, const SortRegions& g, const int64_t* n_ptr) {
+  if (s.r >= s.r1) return false;
+  if (g.filled) {
+    s.b0 = s.r * ((*g.slots + g.regions - 1) / g.regions);
+    s.b1 = s.b0 + g.filled[s.r];
+  } else {
+    const int64_t n = *n_ptr, chunk = sort_chunk(n);
+    s.b0 = int64_t(blockIdx.x) * chunk;
+    s.b1 = s.b0 + chunk < n ? s.b0 + chunk : n;
+  }
+  ++s.r;
+  return true;
+}
+
 // Digit counts of every block's chunk: hist[d][block], or hist[block][d] for the fused scatter.
 // Eight rows of 512 keys are loaded together; runs of one digit in a row (common: records of one tile)
 // are added once each, by their first lanes.  Bound by the read with keys spread widely (41.7 M 64-bit
@@ -49,23 +73,21 @@ __device__ __forceinline__ int64_t sort_chunk(int64_t n) {
 // counters otherwise (47.6 M records: 0.16 ms; every lane adding by itself 0.22 ms).
 template <class Key, bool FUSED>
 __global__ void __launch_bounds__(kSortBlock) k_radix_hist(const Key* __restrict__ keys, const int64_t* n_ptr, int shift,
-                                                           int32_t* __restrict__ hist, const int64_t* only_if) {
+                                                           int32_t* __restrict__ hist, const int64_t* only_if,
+                                                           SortRegions regions) {
   __shared__ int32_t h[kSortWaves][kBuckets];
   if (only_if && *only_if == 0) return;
   const int t = threadIdx.x, w = t >> 6, lane = lane_id();
 #pragma unroll
   for (int q = 0; q < kSortWaves; ++q) h[q][t] = 0;
   __syncthreads();
-  const int64_t n = *n_ptr;
-  const int64_t chunk = sort_chunk(n);
-  const int64_t b0 = int64_t(blockIdx.x) * chunk;
-  const int64_t b1 = b0 + chunk < n ? b0 + chunk : n;
-  for (int64_t t0 = b0; t0 < b1; t0 += kSortTile) {
+  SortSpan span = first_span(regions);
+  while (next_span(span, regions, n_ptr)) for (int64_t t0 = span.b0; t0 < span.b1; t0 += kSortTile) {
     int dg[kSortE];
 #pragma unroll
     for (int j = 0; j < kSortE; ++j) {
       const int64_t i = t0 + j * kSortBlock + t;
-      dg[j] = i < b1 ? int((keys[i] >> shift) & (kBuckets - 1)) : -1;
+      dg[j] = i < span.b1 ? int((keys[i] >> shift) & (kBuckets - 1)) : -1;
     }
 #pragma unroll
     for (int j = 0; j < kSortE; ++j) {
@@ -109,7 +131,7 @@ __global__ void __launch_bounds__(kSortBlock) k_radix_scatter(const Key* __restr
                                                               const uint32_t* __restrict__ pin, Key* __restrict__ kout,
                                                               uint32_t* __restrict__ pout, const int64_t* n_ptr,
                                                               int shift, const int32_t* __restrict__ hist,
-                                                              const int64_t* only_if) {
+                                                              const int64_t* only_if, SortRegions regions) {
   __shared__ uint16_t cnt[kSortWaves][kBuckets];       // per wave: counts, then first slots in the tile
   __shared__ int32_t place[kBuckets];                  // output position less tile slot, per digit
   __shared__ Key sk[kSortTile];
@@ -139,12 +161,9 @@ __global__ void __launch_bounds__(kSortBlock) k_radix_scatter(const Key* __restr
   } else {
     run = hist[int64_t(t) * gridDim.x + blockIdx.x];
   }
-  const int64_t n = *n_ptr;
-  const int64_t chunk = sort_chunk(n);
-  const int64_t b0 = int64_t(blockIdx.x) * chunk;
-  const int64_t b1 = b0 + chunk < n ? b0 + chunk : n;
-  for (int64_t t0 = b0; t0 < b1; t0 += kSortTile) {
-    const int ntile = int(b1 - t0 < kSortTile ? b1 - t0 : kSortTile);
+  SortSpan span = first_span(regions);
+  while (next_span(span, regions, n_ptr)) for (int64_t t0 = span.b0; t0 < span.b1; t0 += kSortTile) {
+    const int ntile = int(span.b1 - t0 < kSortTile ? span.b1 - t0 : kSortTile);
     Key k[kSortE];
     uint32_t pv[kSortE];
     int rk[kSortE];
@@ -217,17 +236,19 @@ __global__ void __launch_bounds__(kSortBlock) k_radix_scatter(const Key* __restr
 
 template <class Key>
 static void radix_pass(const PairBufs& src, const PairBufs& dst, const int64_t* n_dev, int64_t cap, int shift,
-                       int32_t* hist, int64_t* partial, const int64_t* only_if, hipStream_t s) {
-  const int blocks = sort_blocks(cap);
+                       int32_t* hist, int64_t* partial, const int64_t* only_if, const SortRegions& regions,
+                       hipStream_t s) {
+  // (with gaps, a few regions a block: each costs a tile, full or not)
+  const int blocks = regions.filled ? bounded_grid(kSortGrid, regions.regions / 4) : sort_blocks(cap);
   const bool fused = blocks <= kSortFused;
   {
     VX_TIMED("radix_hist", s);
     if (fused)
       hipLaunchKernelGGL((k_radix_hist<Key, true>), dim3(blocks), dim3(kSortBlock), 0, s, (const Key*)src.keys, n_dev,
-                         shift, hist, only_if);
+                         shift, hist, only_if, regions);
     else
       hipLaunchKernelGGL((k_radix_hist<Key, false>), dim3(blocks), dim3(kSortBlock), 0, s, (const Key*)src.keys, n_dev,
-                         shift, hist, only_if);
+                         shift, hist, only_if, regions);
   }
   if (!fused) {
     VX_TIMED("radix_scan", s);
@@ -236,7 +257,7 @@ static void radix_pass(const PairBufs& src, const PairBufs& dst, const int64_t* 
   VX_TIMED("radix_scatter", s);
   const auto scatter = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kSortBlock), 0, s, (const Key*)src.keys, src.prim, (Key*)dst.keys,
-                       dst.prim, n_dev, shift, hist, only_if);
+                       dst.prim, n_dev, shift, hist, only_if, regions);
   };
   if constexpr (sizeof(Key) == 8) {
     if (!src.prim)
@@ -247,16 +268,18 @@ static void radix_pass(const PairBufs& src, const PairBufs& dst, const int64_t* 
 
 void radix_sort_pass(bool key64, const PairBufs& src, const PairBufs& dst, const int64_t* n_dev, int64_t cap,
                      int shift, int32_t* hist, int64_t* partial, const int64_t* only_if, hipStream_t s) {
-  if (key64) radix_pass<uint64_t>(src, dst, n_dev, cap, shift, hist, partial, only_if, s);
-  else radix_pass<uint32_t>(src, dst, n_dev, cap, shift, hist, partial, only_if, s);
+  if (key64) radix_pass<uint64_t>(src, dst, n_dev, cap, shift, hist, partial, only_if, {}, s);
+  else radix_pass<uint32_t>(src, dst, n_dev, cap, shift, hist, partial, only_if, {}, s);
 }
 
 PairBufs radix_sort_pairs(bool key64, int key_bits, const PairBufs& in, const PairBufs& t0, const PairBufs& t1,
                           const int64_t* n_dev, int64_t cap, int32_t* hist, int64_t* partial, hipStream_t s,
-                          int first_bit) {
+                          int first_bit, const SortRegions& regions) {
   PairBufs src = in, dst = t0, spare = t1;
   for (int shift = first_bit; shift < first_bit + key_bits; shift += kDigitBits) {
-    radix_sort_pass(key64, src, dst, n_dev, cap, shift, hist, partial, nullptr, s);
+    const SortRegions g = shift == first_bit ? regions : SortRegions{};
+    if (key64) radix_pass<uint64_t>(src, dst, n_dev, cap, shift, hist, partial, nullptr, g, s);
+    else radix_pass<uint32_t>(src, dst, n_dev, cap, shift, hist, partial, nullptr, g, s);
     src = dst;
     const PairBufs x = dst;
     dst = spare;

@@ -309,9 +309,16 @@ void launch_fill_i64(int64_t* p, int64_t n, int64_t v, hipStream_t s);
 // (prim == nullptr, 64-bit keys only) the keys alone are sorted, by the key_bits bits from first_bit.
 constexpr int kRadixBuckets = 512;          // digit values of the record sort (hist is kRadixBuckets x kGrid)
 constexpr int kRadixBits = 9;
+// Input with gaps (the first pass closes them): `regions` stretches of ceil(*slots / regions) slots,
+// the first filled[r] of each in use, *n_dev in all.
+struct SortRegions {
+  const int64_t* slots;
+  const int32_t* filled;      // nullptr: no gaps
+  int regions;
+};
 PairBufs radix_sort_pairs(bool key64, int key_bits, const PairBufs& in, const PairBufs& t0, const PairBufs& t1,
                           const int64_t* n_dev, int64_t cap, int32_t* hist, int64_t* partial, hipStream_t s,
-                          int first_bit = 0);
+                          int first_bit = 0, const SortRegions& regions = {});
 // one pass by the digit at `shift`; with only_if, nothing is done where *only_if is 0
 void radix_sort_pass(bool key64, const PairBufs& src, const PairBufs& dst, const int64_t* n_dev, int64_t cap,
                      int shift, int32_t* hist, int64_t* partial, const int64_t* only_if, hipStream_t s);

@@ -190,3 +190,17 @@ def test_sort_paths(vx, log2_res, n, N, inside):
     ref = oracle.sample_triangles(wl.grid, tris, N)
     assert p.n_inside == ref.n_pairs and (p.n_inside == p.n_samples) == inside
     say(compare_samples(g, ref, f"{n} triangles, R = {R}, N = {N}"))
+
+
+@pytest.mark.parametrize("log2_res,n,N,scale", [(10, 37, 3000, 0.4), (11, 900, 64, 0.2), (12, 5000, 40, 0.2),
+                                                (12, 3, 20000, 3.0), (19, 12, 700, 0.3), (20, 8, 700, 0.3),
+                                                (20, 200, 300, 0.3)])
+def test_samples_sharing_voxels(vx, log2_res, n, N, scale):
+    """Many samples of a triangle in one voxel, across the rows of 64 that emit them: with room for their
+    count beside the key and id, for a little of it, and for none."""
+    wl = synth.random_triangles(n, log2_res, seed=n + N, scale=scale, margin=-2.0)
+    say(f"case: sampled random triangles {n} of about {scale} voxels, R = {1 << log2_res}, N = {N}")
+    p, g = _tris(vx, wl.grid, wl.tris, N)
+    ref = oracle.sample_triangles(wl.grid, wl.tris, N)
+    assert p.n_inside == ref.n_pairs and p.n_samples > 2 * len(ref.keys)
+    say(compare_samples(g, ref, f"{n} triangles, R = {1 << log2_res}, N = {N}"))
