@@ -298,12 +298,30 @@ __device__ __forceinline__ void lod_parent(const vx_voxels& in, const Key* ikeys
   const int64_t ci = in.cap, co = out.cap;
   uint32_t c = 0, mask = 0;
   float W = 0.f, S[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int64_t j = a; j < b; ++j) {
-    c += in.count[j];
-    mask |= 1u << uint32_t(ikeys[j] & 7);
-    W += in.w[j];
+  // kAtOnce children at a time: their loads do not wait for one another, the sums stay in order (14
+  // patches' pyramid 0.52 -> 0.46 ms; two at a time 0.48, all eight 0.50)
+  constexpr int kAtOnce = 4;
+  for (int64_t j0 = a; j0 < b; j0 += kAtOnce) {
+    uint32_t cc[kAtOnce], low[kAtOnce];
+    float ww[kAtOnce], ss[kAtOnce][6];
 #pragma unroll
-    for (int k = 0; k < 6; ++k) S[k] += in.S[k * ci + j];
+    for (int q = 0; q < kAtOnce; ++q) {
+      const int64_t j = j0 + q < b ? j0 + q : b - 1;
+      cc[q] = in.count[j];
+      low[q] = uint32_t(ikeys[j] & 7);
+      ww[q] = in.w[j];
+#pragma unroll
+      for (int k = 0; k < 6; ++k) ss[q][k] = in.S[k * ci + j];
+    }
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q) {
+      const bool on = j0 + q < b;
+      c += on ? cc[q] : 0u;
+      mask |= on ? 1u << low[q] : 0u;
+      W = on ? W + ww[q] : W;
+#pragma unroll
+      for (int k = 0; k < 6; ++k) S[k] = on ? S[k] + ss[q][k] : S[k];
+    }
   }
   reinterpret_cast<Key*>(out.keys)[p] = parent_key<Key, BATCH>(ikeys[a]);
   out.count[p] = c;
