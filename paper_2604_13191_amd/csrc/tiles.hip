@@ -352,18 +352,18 @@ struct UnitLds {
                       // (fibers: in that of w, past the weights of the pairs so far)
   uint16_t* idx;      // [budget]   triangles: the slots of a batch's new pairs; after the batches:
                       // grouped order -> pair (fibers: in the space of ckey)
+  uint64_t* kbits;    // [64] one-wave blocks: bit k set where a pair of key k was found
   uint64_t* sbm;      // [64] batch: bit c set where a slot's first candidate is c
   uint32_t* spre;     // [64] slot starts below each word
-  int32_t* brec;      // [kBlock][9] the slot's primitive vertices (record words 0..8; fibers: words
-                      // 0..5 and the segment's length; after the batches: the per-key counters, then
-                      // starts)
+  int32_t* brec;      // [threads][9] the slot's primitive vertices (record words 0..8; fibers: words
+                      // 0..5 and the segment's length; after the batches: the counters, then starts)
   // the current record batch; after the batches its space holds the voxels' keys
-  double* binv;       // [kBlock] fibers: the slot's 1 / |B - A|^2 (lattice units); triangles:
+  double* binv;       // [threads] fibers: the slot's 1 / |B - A|^2 (lattice units); triangles:
                       // tri_area_under's factor from projected to true area
-  int32_t* bprim;     // [kBlock]
-  uint32_t* bbox;     // [kBlock] the slot's candidate box in the unit (pack_slot_box)
-  int32_t* boff;      // [kBlock] candidate offsets within the batch
-  int32_t* bpatch;    // [kBlock] the slot's patch (batched fibers); triangles: tri_area_under's `how`
+  int32_t* bprim;     // [threads]
+  uint32_t* bbox;     // [threads] the slot's candidate box in the unit (pack_slot_box)
+  int32_t* boff;      // [threads] candidate offsets within the batch
+  int32_t* bpatch;    // [threads] the slot's patch (batched fibers); triangles: tri_area_under's `how`
   uint16_t* vkey;     // [budget]
   int32_t* tmp32;     // [kWaves + 1]
   int32_t* misc;      // [8]
@@ -376,8 +376,6 @@ template <int KIND>
 constexpr int32_t stable_mean() { return KIND == 0 ? 24 : 4; }
 // keys of a unit's range: at most one 16^3 tile
 constexpr int32_t kUnitKeys = 4096;
-static_assert(kBlock * 9 * 4 >= kUnitKeys * 2, "per-key counters live in the record batch's space");
-static_assert(kBlock * 16 == kUnitKeys, "each thread owns 16 keys in the scan of the counters");
 
 // a candidate's outcome and key in one 16-bit word (keys below 4096)
 constexpr uint16_t kTouch = 0x8000, kUndecided = 0x4000;
@@ -389,11 +387,11 @@ static_assert(kUnitKeys <= kUndecided, "keys fit below the flags");
 // more than the registers it takes.  With packed boxes, shared space and the arrival slots in registers
 // the brushed surface's units (1536) went from 49 to 38 KB and 6.43 to 5.75 ms, a fabric's (3072) from
 // 77 to 53 KB and 0.68 to 0.50 ms.
-template <int KIND, int CAND>
+template <int KIND, int CAND, int NT = kBlock>
 constexpr size_t unit_lds_bytes() {
-  constexpr size_t batch = kBlock * (8 + 4 * 4) > CAND * 2 ? kBlock * (8 + 4 * 4) : CAND * 2;
-  return size_t(CAND) * (2 + 4 + 4 + 2 + (KIND == 0 ? 2 : 0)) + 64 * 8 + 64 * 4 + kBlock * 9 * 4 + batch +
-         (kWaves + 2) * 4 + 8 * 4;
+  constexpr size_t batch = NT * (8 + 4 * 4) > CAND * 2 ? NT * (8 + 4 * 4) : CAND * 2;
+  return size_t(CAND) * (2 + 4 + 4 + 2 + (KIND == 0 ? 2 : 0)) + 64 * 8 + (NT == 64 ? 64 * 8 : 0) + 64 * 4 + NT * 9 * 4 +
+         batch + (NT / 64 + 2) * 4 + 8 * 4;
 }
 template <int KIND>
 constexpr int unit_waves(int cand) {
@@ -405,7 +403,36 @@ static_assert(4 * unit_lds_bytes<0, 1536>() <= 160 * 1024, "four units per CU");
 static_assert(3 * unit_lds_bytes<1, 3072>() <= 160 * 1024, "three units per CU");
 static_assert(4 * unit_lds_bytes<1, 1536>() <= 160 * 1024, "four units per CU");
 
-template <int KIND, int CAND>
+// Small units (fibers), a wave each: four waves take a unit of a hundred candidates no faster than one
+// does, since all that they do is wait.  The four waves of a block claim their staging ranges
+// together: single claims, all on one counter, come 16 ns apart at best.  A strand's 6,300 units: 65
+// us; by blocks of four waves 102 us, by single waves with claims of their own 99 us.
+constexpr int kSmallCand = 384;
+constexpr size_t small_lds_bytes() { return (unit_lds_bytes<1, kSmallCand, 64>() + 15) / 16 * 16; }
+static_assert(4 * (kWaves * small_lds_bytes() + 64) <= 160 * 1024, "sixteen small units per CU");
+
+// barriers and scans of the threads that share a unit: a block, or one wave of it (NT = 64)
+template <int NT>
+__device__ __forceinline__ void unit_sync() {
+  if (NT == 64) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    __syncthreads();
+  }
+}
+template <int NT>
+__device__ __forceinline__ int32_t unit_scan(int32_t v, int32_t* tmp, int32_t& total) {
+  if constexpr (NT == 64) {
+    const int32_t inc = wave_inclusive_scan(v);
+    total = __builtin_amdgcn_readlane(inc, 63);
+    return inc - v;
+  } else {
+    return block_exclusive_scan(v, tmp, total);
+  }
+}
+
+template <int KIND, int CAND, int NT>
 __device__ __forceinline__ UnitLds carve_unit_lds(char* base) {
   UnitLds L;
   size_t off = 0;
@@ -414,13 +441,14 @@ __device__ __forceinline__ UnitLds carve_unit_lds(char* base) {
     off += (bytes + 7) & ~size_t(7);
     return p;
   };
+  L.kbits = reinterpret_cast<uint64_t*>(take(NT == 64 ? 64 * 8 : 0));
   L.sbm = reinterpret_cast<uint64_t*>(take(64 * 8));
-  char* batch = take(kBlock * (8 + 4 * 4) > CAND * 2 ? kBlock * (8 + 4 * 4) : CAND * 2);
+  char* batch = take(NT * (8 + 4 * 4) > CAND * 2 ? NT * (8 + 4 * 4) : CAND * 2);
   L.binv = reinterpret_cast<double*>(batch);
-  L.bprim = reinterpret_cast<int32_t*>(batch + kBlock * 8);
-  L.bbox = reinterpret_cast<uint32_t*>(batch + kBlock * 12);
-  L.boff = reinterpret_cast<int32_t*>(batch + kBlock * 16);
-  L.bpatch = reinterpret_cast<int32_t*>(batch + kBlock * 20);
+  L.bprim = reinterpret_cast<int32_t*>(batch + NT * 8);
+  L.bbox = reinterpret_cast<uint32_t*>(batch + NT * 12);
+  L.boff = reinterpret_cast<int32_t*>(batch + NT * 16);
+  L.bpatch = reinterpret_cast<int32_t*>(batch + NT * 20);
   L.vkey = reinterpret_cast<uint16_t*>(batch);
   L.w = reinterpret_cast<float*>(take(CAND * 4));
   L.prim = reinterpret_cast<uint32_t*>(take(CAND * 4));
@@ -429,8 +457,8 @@ __device__ __forceinline__ UnitLds carve_unit_lds(char* base) {
   L.idx = KIND == 0 ? reinterpret_cast<uint16_t*>(take(CAND * 2)) : L.ckey;
   L.queue = L.idx;
   L.spre = reinterpret_cast<uint32_t*>(take(64 * 4));
-  L.brec = reinterpret_cast<int32_t*>(take(kBlock * 9 * 4));
-  L.tmp32 = reinterpret_cast<int32_t*>(take((kWaves + 1) * 4));
+  L.brec = reinterpret_cast<int32_t*>(take(NT * 9 * 4));
+  L.tmp32 = reinterpret_cast<int32_t*>(take((NT / 64 + 1) * 4));
   L.misc = reinterpret_cast<int32_t*>(take(8 * 4));
   return L;
 }
@@ -442,22 +470,23 @@ __device__ __forceinline__ uint32_t pack_slot_box(const int32_t o[3], const int3
          (uint32_t(n[0] - 1) << 12) | (uint32_t(n[1] - 1) << 16);
 }
 
-// Load records [j0, j0 + kBlock) of the tile clipped to the unit box, keeping those with
+// Load records [j0, j0 + NT) (NT: threads of the block) of the tile clipped to the unit box, keeping those with
 // candidates in it (compacted, in record order, with a copy of their vertices); returns the
 // batch's candidate total and the number of slots kept.  Contains __syncthreads().
-template <int KIND>
+template <int KIND, int NT>
 __device__ __forceinline__ int32_t load_batch(const UnitLds& S, const int32_t* __restrict__ rec,
                                               const uint32_t* __restrict__ rprim, const float4* __restrict__ dirs,
                                               int64_t j0, int64_t e, int Sb,
                                               const int32_t o[3], const int32_t sz[3], int& nslot) {
-  const int64_t j = j0 + threadIdx.x;
+  const int tid = threadIdx.x % NT;
+  const int64_t j = j0 + tid;
   int32_t c = 0, lo[3], n[3];
   uint32_t p = 0;
   // the whole record (and the triangle's normal and doubled area) in registers at once: one round
   // of loads after the primitive id, none after the scan below
   int32_t r[kRec];
   float4 dir = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (threadIdx.x < 64) S.sbm[threadIdx.x] = 0;
+  if (tid < 64) S.sbm[tid] = 0;
   if (j < e) {
     p = rprim[j];
     const int4* r4 = reinterpret_cast<const int4*>(rec + int64_t(p) * kRec);
@@ -475,7 +504,7 @@ __device__ __forceinline__ int32_t load_batch(const UnitLds& S, const int32_t* _
   }
   // candidates (below 2^21 per batch) and kept slots (bits 21 and up) in one scan
   int32_t tot;
-  const int32_t ex = block_exclusive_scan(c | (c > 0 ? (1 << 21) : 0), S.tmp32, tot);
+  const int32_t ex = unit_scan<NT>(c | (c > 0 ? (1 << 21) : 0), S.tmp32, tot);
   if (c > 0) {
     const int q = ex >> 21;
     const int32_t off = ex & ((1 << 21) - 1);
@@ -498,13 +527,13 @@ __device__ __forceinline__ int32_t load_batch(const UnitLds& S, const int32_t* _
     atomicOr(reinterpret_cast<unsigned long long*>(&S.sbm[off >> 6]), 1ull << (off & 63));
   }
   nslot = tot >> 21;
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    const uint32_t cnt = uint32_t(__popcll(S.sbm[threadIdx.x]));
+  unit_sync<NT>();
+  if (tid < 64) {
+    const uint32_t cnt = uint32_t(__popcll(S.sbm[tid]));
     const uint32_t inc = wave_inclusive_scan(cnt);
-    S.spre[threadIdx.x] = inc - cnt;
+    S.spre[tid] = inc - cnt;
   }
-  __syncthreads();
+  unit_sync<NT>();
   return tot & ((1 << 21) - 1);
 }
 
@@ -607,37 +636,71 @@ __device__ __forceinline__ void write_voxel(const Stage& st, int64_t i, uint64_t
 // Fibers are weighed from the records in LDS, one reciprocal an axis: 14 patches (64,000 units) 2.46 ->
 // 2.21 ms, a weave (10,000 units) 0.515 -> 0.460 ms against records gathered again from memory after
 // the batches and two divisions an axis.
-template <int KIND, int CAND>
+template <int KIND, int CAND, int NT>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(unit_waves<KIND>(CAND)))) k_unit(const int32_t* __restrict__ rec, const float4* __restrict__ dirs,
                                                  const uint32_t* __restrict__ rprim,
                                                  const int64_t* __restrict__ tstart, const Unit* __restrict__ units,
                                                  const int64_t* __restrict__ ctl, Lat L, const Lat* __restrict__ lats,
                                                  int64_t* __restrict__ unv, int64_t* __restrict__ unp,
                                                  int64_t* __restrict__ usoff, Stage st, int64_t* stage_ctr,
-                                                 int64_t* stats) {
+                                                 int64_t* stats, int small) {
   extern __shared__ double lds_dyn[];
+  constexpr int kW = NT / 64;
+  constexpr bool kOne = NT == 64;                     // a unit of up to CAND candidates per wave
+  constexpr int kAtOnce = kBlock / NT;                // units in flight in the block
   static_assert(CAND <= 0xffff, "pair positions are 16-bit");
-  static_assert(CAND % (kWaves * 64) == 0, "each wave's queue holds all of its candidates");
-  const UnitLds S = carve_unit_lds<KIND, CAND>(reinterpret_cast<char*>(lds_dyn));
+  static_assert(CAND % (kW * 64) == 0, "each wave's queue holds all of its candidates");
+  char* const lds = reinterpret_cast<char*>(lds_dyn);
+  const UnitLds S = carve_unit_lds<KIND, CAND, NT>(kOne ? lds + (threadIdx.x / NT) * small_lds_bytes() : lds);
+  int64_t* const claims = reinterpret_cast<int64_t*>(lds + kWaves * small_lds_bytes());   // [kWaves + 1] (kOne)
   const int64_t n_units = ctl[CTL_N_UNITS];
-  const int tid = threadIdx.x;
-  for (int64_t u = blockIdx.x; u < n_units; u += gridDim.x) {
+  const int tid = threadIdx.x % NT;
+  // the four waves' claims together; every wave calls it once a round
+  const auto claim_together = [&](int32_t nv) -> int64_t {
+    const int wv = threadIdx.x / 64;
+    if (tid == 0) claims[wv] = nv;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int64_t all = 0;
+      for (int i = 0; i < kWaves; ++i) {
+        const int64_t n = claims[i];
+        claims[i] = all;
+        all += n;
+      }
+      claims[kWaves] = all ? int64_t(atomicAdd(reinterpret_cast<unsigned long long*>(stage_ctr), (unsigned long long)all))
+                           : 0;
+    }
+    __syncthreads();
+    return claims[kWaves] + claims[wv];               // (the next round's first barrier comes after this read)
+  };
+  for (int64_t u0 = int64_t(blockIdx.x) * kAtOnce; u0 < n_units; u0 += int64_t(gridDim.x) * kAtOnce) {
+    const int64_t u = kOne ? u0 + threadIdx.x / NT : u0;
+    if (kOne && u >= n_units) {
+      (void)claim_together(0);
+      continue;
+    }
     const Unit U = units[u];
+    if (kOne && U.cand > CAND) {
+      (void)claim_together(0);
+      continue;
+    }
+    if (!kOne && U.cand <= small) continue;           // (small: what single waves take, 0: none)
     const int64_t s = tstart[U.tile], e = tstart[U.tile + 1];
     int32_t usz[3];
     unit_box(U.lev, U.ncell, usz);
     const uint64_t m0 = morton3(uint32_t(U.o[0]), uint32_t(U.o[1]), uint32_t(U.o[2]));   // the unit's first key
     const uint32_t c0 = uint32_t(m0) & 4095u;                                              // its code in the cell
-    const bool stream = U.cand > CAND;          // a single voxel holding too many candidates
+    const bool stream = !kOne && U.cand > CAND;          // a single voxel holding too many candidates
     int32_t np = 0;                                   // pairs so far (uniform)
+    if (kOne) S.kbits[tid] = 0;                       // (the batch's barriers come before the first pair)
     Moment acc{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // streaming sums (thread 0)
     uint32_t acc_n = 0;
-    for (int64_t j0 = s; j0 < e; j0 += kBlock) {
+    for (int64_t j0 = s; j0 < e; j0 += NT) {
       int nb;
-      const int32_t cb = load_batch<KIND>(S, rec, rprim, dirs, j0, e, L.Sb, U.o, usz, nb);
+      const int32_t cb = load_batch<KIND, NT>(S, rec, rprim, dirs, j0, e, L.Sb, U.o, usz, nb);
       (void)nb;
       if (stream) {
-        for (int32_t b0 = 0; b0 < cb; b0 += kBlock) {
+        for (int32_t b0 = 0; b0 < cb; b0 += NT) {
           const int32_t c = b0 + tid;
           bool hit = false;
           float wgt = 0.f;
@@ -659,19 +722,19 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
             }
           }
           int32_t tot;
-          const int32_t pos = block_exclusive_scan(int32_t(hit), S.tmp32, tot);
+          const int32_t pos = unit_scan<NT>(int32_t(hit), S.tmp32, tot);
           // one voxel: sum this chunk's hits in order (thread 0), chunk by chunk
           if (hit) {
             S.w[pos] = wgt;
             S.prim[pos] = p;
           }
-          __syncthreads();
+          unit_sync<NT>();
           if (tid == 0) {
             for (int32_t i = 0; i < tot; ++i) accum_pair<KIND>(acc, S.w[i], dirs[S.prim[i]]);
             acc_n += uint32_t(tot);
           }
           np += tot;
-          __syncthreads();
+          unit_sync<NT>();
         }
         continue;
       }
@@ -685,11 +748,11 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
       // which is primitive order.
       const int wv = tid >> 6, lane = tid & 63;
       const uint64_t lt = (uint64_t(1) << lane) - 1;
-      uint16_t* wq = KIND == 0 ? S.queue + wv * (CAND / kWaves)
+      uint16_t* wq = KIND == 0 ? S.queue + wv * (CAND / kW)
                                : reinterpret_cast<uint16_t*>(S.w + (np < CAND - cb ? np : CAND - cb)) +
-                                     wv * 64 * ((cb + kBlock - 1) / kBlock);
+                                     wv * 64 * ((cb + NT - 1) / NT);
       int32_t nq = 0;                                  // this wave's queue (uniform)
-      for (int32_t b0 = wv * 64; b0 < cb; b0 += kBlock) {
+      for (int32_t b0 = wv * 64; b0 < cb; b0 += NT) {
         const int32_t c = b0 + lane;
         int res = 0;                                   // 0 miss, 1 touch, 2 undecided
         if (c < cb) {
@@ -729,10 +792,10 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
         }
         S.ckey[c] = hit ? uint16_t(kTouch | (cell_code(v) - c0)) : uint16_t(0);
       }
-      __syncthreads();
+      unit_sync<NT>();
       // ordered compaction: wave w takes candidates [w span, (w + 1) span)
       {
-        const int32_t span = ((cb + kWaves * 64 - 1) / (kWaves * 64)) * 64;
+        const int32_t span = ((cb + kW * 64 - 1) / (kW * 64)) * 64;
         const int32_t w0 = wv * span, w1 = w0 + span < cb ? w0 + span : cb;
         int32_t cnt = 0;
         for (int32_t b0 = w0; b0 < w1; b0 += 64) {
@@ -740,9 +803,9 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
           cnt += int32_t(__popcll(__ballot(c < w1 && (S.ckey[c] & kTouch) != 0)));
         }
         if (lane == 0) S.tmp32[wv] = cnt;
-        __syncthreads();
+        unit_sync<NT>();
         int32_t base = np, tot = 0;
-        for (int i = 0; i < kWaves; ++i) {
+        for (int i = 0; i < kW; ++i) {
           if (i < wv) base += S.tmp32[i];
           tot += S.tmp32[i];
         }
@@ -754,7 +817,9 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
             const int32_t q = base + int32_t(__popcll(mh & lt));
             if (q < CAND) {
               const int sl = find_slot(S, c);
-              S.key[q] = uint16_t(S.ckey[c] & (kTouch - 1));
+              const uint32_t key = S.ckey[c] & (kTouch - 1u);
+              S.key[q] = uint16_t(key);
+              if (kOne) atomicOr(reinterpret_cast<uint32_t*>(S.kbits) + (key >> 5), 1u << (key & 31u));
               if (KIND == 0) {
                 S.prim[q] = uint32_t(S.bprim[sl]);
                 S.idx[q] = uint16_t(sl);
@@ -768,9 +833,9 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
           base += int32_t(__popcll(mh));
         }
         // the batch's pairs are weighed now, from the records still in LDS
-        __syncthreads();
+        unit_sync<NT>();
         const int32_t q1 = np + tot < CAND ? np + tot : CAND;
-        for (int32_t q = np + tid; q < q1; q += kBlock) {
+        for (int32_t q = np + tid; q < q1; q += NT) {
           const int sl = KIND == 0 ? int(S.idx[q]) : int(S.prim[q]);
           const int32_t* r = S.brec + sl * 9;
           int32_t v[3];
@@ -783,7 +848,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
           }
         }
         np += tot;
-        __syncthreads();
+        unit_sync<NT>();
       }
     }
     if (stream) {
@@ -801,71 +866,116 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
         unp[u] = np;
         usoff[u] = b;
       }
-      __syncthreads();
+      unit_sync<NT>();
       continue;
     }
     const int32_t npairs = np < CAND ? np : CAND;
     // Group the pairs by voxel with one counter per key of the unit's range (at most 4096 keys;
     // 16-bit counts packed two to a word, in the record batch's space, dead now).  Each pair's
     // arrival slot among its voxel's pairs stays in its thread's registers until it is placed.
-    uint32_t* kcw = reinterpret_cast<uint32_t*>(S.brec);                 // [2048] packed counts
-    uint16_t* kst = reinterpret_cast<uint16_t*>(S.brec);                 // [4096] then starts
+    // One-wave blocks have room for a counter per voxel only: a key's rank among the unit's keys, by
+    // the bits set as the pairs were found, numbers its voxel and takes the key's place with the pair.
+    // (In the large units those bits and ranks cost more than 4096 counters: a weave 0.91 ms, 0.89.)
+    uint32_t* kcw = reinterpret_cast<uint32_t*>(S.brec);                 // packed counts
+    uint16_t* kst = reinterpret_cast<uint16_t*>(S.brec);                 // then starts, by key or voxel
     uint16_t* vkey = S.vkey;                                             // [nv] key of voxel v
-    for (int32_t j = tid; j < kUnitKeys / 2; j += kBlock) kcw[j] = 0u;
-    __syncthreads();
-    uint32_t slot[CAND / kBlock];
-#pragma unroll
-    for (int q = 0; q < CAND / kBlock; ++q) {
-      const int32_t i = tid + q * kBlock;
-      slot[q] = 0;
-      if (i < npairs) {
-        const uint32_t k = S.key[i], sh = 16u * (k & 1u);
-        slot[q] = (atomicAdd(&kcw[k >> 1], 1u << sh) >> sh) & 0xffffu;
-      }
-    }
-    __syncthreads();
-    // starts and the voxel list: thread t owns keys [16 t, 16 t + 16); one block scan of the
-    // (pairs, voxels) counts packed in one word (at most 3072 pairs and 4096 voxels)
+    uint32_t slot[CAND / NT];
     int32_t nv;
-    {
-      uint32_t c[16];
-      uint32_t sp = 0, sv = 0;
+    if constexpr (kOne) {
+      static_assert(NT * 9 * 4 >= CAND * 2, "the voxels' counters live in the record batch's space");
+      const int32_t bits = int32_t(__popcll(S.kbits[tid]));
+      const int32_t upto = wave_inclusive_scan(bits);
+      nv = __builtin_amdgcn_readlane(upto, 63);
+      for (int32_t j = tid; j < (nv + 1) / 2; j += NT) kcw[j] = 0u;
+      unit_sync<NT>();
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const uint32_t w2 = kcw[tid * 8 + j];
-        c[2 * j] = w2 & 0xffffu;
-        c[2 * j + 1] = w2 >> 16;
+      for (int q = 0; q < CAND / NT; ++q) {
+        const int32_t i = tid + q * NT;
+        slot[q] = 0;
+        if (q * NT >= npairs) continue;               // (uniform)
+        const uint32_t k = i < npairs ? S.key[i] : 0u;
+        const uint32_t pre = uint32_t(__shfl(upto - bits, int(k >> 6), 64));
+        if (i < npairs) {
+          const uint32_t v = pre + uint32_t(__popcll(S.kbits[k >> 6] & ((1ull << (k & 63)) - 1)));
+          const uint32_t sh = 16u * (v & 1u);
+          slot[q] = (atomicAdd(&kcw[v >> 1], 1u << sh) >> sh) & 0xffffu;
+          S.key[i] = uint16_t(v);
+          if (slot[q] == 0) vkey[v] = uint16_t(k);
+        }
       }
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        sp += c[k];
-        sv += c[k] != 0u ? 1u : 0u;
+      unit_sync<NT>();
+      // starts: lane t owns `own` voxels (whole words) from own * t on
+      const int32_t own = 2 * ((nv + 2 * NT - 1) / (2 * NT)), w0 = tid * own / 2;
+      uint32_t sum = 0;
+      for (int32_t j = 0; j < own / 2; ++j) {
+        const uint32_t n2 = 2 * (w0 + j) < nv ? kcw[w0 + j] : 0u;
+        sum += (n2 & 0xffffu) + (n2 >> 16);
       }
-      int32_t tot;
-      const uint32_t pre = uint32_t(block_exclusive_scan(int32_t(sp | (sv << 16)), S.tmp32, tot));
-      nv = tot >> 16;
-      uint32_t rp = pre & 0xffffu, rv = pre >> 16;
+      uint32_t at = wave_inclusive_scan(sum) - sum;
+      for (int32_t j = 0; j < own / 2 && 2 * (w0 + j) < nv; ++j) {
+        const uint32_t n2 = kcw[w0 + j];
+        kcw[w0 + j] = at | (at + (n2 & 0xffffu)) << 16;
+        at += (n2 & 0xffffu) + (n2 >> 16);
+      }
+    } else {
+      static_assert(kOne || (NT * 9 * 4 >= kUnitKeys * 2 && NT * 16 == kUnitKeys), "sixteen keys a thread");
+      for (int32_t j = tid; j < kUnitKeys / 2; j += NT) kcw[j] = 0u;
+      unit_sync<NT>();
 #pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        const uint32_t key = uint32_t(tid) * 16u + uint32_t(k);
-        kst[key] = uint16_t(rp);
-        if (c[k] != 0u) vkey[rv++] = uint16_t(key);
-        rp += c[k];
+      for (int q = 0; q < CAND / NT; ++q) {
+        const int32_t i = tid + q * NT;
+        slot[q] = 0;
+        if (i < npairs) {
+          const uint32_t k = S.key[i], sh = 16u * (k & 1u);
+          slot[q] = (atomicAdd(&kcw[k >> 1], 1u << sh) >> sh) & 0xffffu;
+        }
+      }
+      unit_sync<NT>();
+      // starts and the voxel list: thread t owns keys [16 t, 16 t + 16); one block scan of the
+      // (pairs, voxels) counts packed in one word (at most 3072 pairs and 4096 voxels)
+      {
+        uint32_t c[16];
+        uint32_t sp = 0, sv = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const uint32_t w2 = kcw[tid * 8 + j];
+          c[2 * j] = w2 & 0xffffu;
+          c[2 * j + 1] = w2 >> 16;
+        }
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          sp += c[k];
+          sv += c[k] != 0u ? 1u : 0u;
+        }
+        int32_t tot;
+        const uint32_t pre = uint32_t(unit_scan<NT>(int32_t(sp | (sv << 16)), S.tmp32, tot));
+        nv = tot >> 16;
+        uint32_t rp = pre & 0xffffu, rv = pre >> 16;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          const uint32_t key = uint32_t(tid) * 16u + uint32_t(k);
+          kst[key] = uint16_t(rp);
+          if (c[k] != 0u) vkey[rv++] = uint16_t(key);
+          rp += c[k];
+        }
       }
     }
-    if (tid == 0) {
-      // claim the staging range now; the claim's round trip overlaps the placement below
-      const int64_t b = nv ? int64_t(atomicAdd(reinterpret_cast<unsigned long long*>(stage_ctr),
-                                               (unsigned long long)nv))
-                           : 0;
+    // claim the staging range now; the claim's round trip overlaps the placement below
+    int64_t b = 0;
+    if constexpr (kOne) {
+      b = claim_together(nv);
+    } else if (tid == 0) {
+      b = nv ? int64_t(atomicAdd(reinterpret_cast<unsigned long long*>(stage_ctr), (unsigned long long)nv)) : 0;
       S.misc[1] = int32_t(b & 0xffffffff);
       S.misc[2] = int32_t(b >> 32);
+    }
+    if (tid == 0) {
       if (b + nv > st.cap) flag_set(stats, VX_FLAG_VOXEL_CAPACITY);
       unv[u] = nv;
       unp[u] = np;
       usoff[u] = b;
     }
-    __syncthreads();
+    unit_sync<NT>();
     // Place the pairs by voxel.  Sparse units (few pairs per voxel) place by arrival slot and
     // restore primitive order per voxel by insertion sort below; dense ones place stably: one
     // wave walks the list (primitive order) and lanes holding the same key find each other by
@@ -873,8 +983,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
     const bool stable = npairs > stable_mean<KIND>() * nv;
     if (!stable) {
 #pragma unroll
-      for (int q = 0; q < CAND / kBlock; ++q) {
-        const int32_t i = tid + q * kBlock;
+      for (int q = 0; q < CAND / NT; ++q) {
+        const int32_t i = tid + q * NT;
         if (i < npairs) S.idx[kst[S.key[i]] + slot[q]] = uint16_t(i);
       }
     } else if (tid < 64) {
@@ -901,20 +1011,20 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       }
     }
-    __syncthreads();
-    const int64_t b = int64_t(uint32_t(S.misc[1])) | (int64_t(S.misc[2]) << 32);
+    unit_sync<NT>();
+    if constexpr (!kOne) b = int64_t(uint32_t(S.misc[1])) | (int64_t(S.misc[2]) << 32);
     const uint64_t hi = lats ? uint64_t(uint32_t(rec[int64_t(rprim[s]) * kRec + 15])) << kPatchShift : 0ull;
     if (b + nv <= st.cap) {
-      for (int32_t v = tid; v < nv; v += kBlock) {
+      for (int32_t v = tid; v < nv; v += NT) {
         // its pairs: [start, next start), or (stably placed: the starts have run to the ends) [last
         // end, end)
         uint32_t a, z;
         if (!stable) {
-          a = kst[vkey[v]];
-          z = v + 1 < nv ? uint32_t(kst[vkey[v + 1]]) : uint32_t(npairs);
+          a = kst[kOne ? v : int32_t(vkey[v])];
+          z = v + 1 < nv ? uint32_t(kst[kOne ? v + 1 : int32_t(vkey[v + 1])]) : uint32_t(npairs);
         } else {
-          a = v ? uint32_t(kst[vkey[v - 1]]) : 0u;
-          z = kst[vkey[v]];
+          a = v ? uint32_t(kst[kOne ? v - 1 : int32_t(vkey[v - 1])]) : 0u;
+          z = kst[kOne ? v : int32_t(vkey[v])];
         }
         // the voxel's pairs in list order, which is primitive order (insertion sort)
         for (uint32_t i = a + 1; !stable && i < z; ++i) {
@@ -946,7 +1056,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
         write_voxel<KIND>(st, b + v, hi | (m0 + vkey[v]), z - a, m);
       }
     }
-    __syncthreads();
+    unit_sync<NT>();
   }
 }
 
@@ -1230,29 +1340,36 @@ vx_status tile_voxelize(int kind, const vx_grid* g, const float* data, int64_t n
     const Lat L = make_lat(g, kind, radius);
     const Lat* lats = batch ? batch->lats : nullptr;
     const int ugrid = bounded_grid(tu.grids[kTuneUnit], max_units);
-#define VX_UNIT(KD, C)                                                                                           \
+    // Small units go to single waves where the capacities, taken from counts, say that units hold few
+    // records (fewer records than units: long segments, whose units are full, or no counts).  Unit
+    // kernels of strands and weaves at 4.5 records a unit 104 us, 65 with single waves; at 7.4 133 and
+    // 91; at 11 149 and 120; at 12.4 47 and 49; at 16.5 156 and 178, since the two kernels' rests add up.
+    const int small = kind == 1 && max_units <= max_rec && max_rec <= 12 * max_units ? kSmallCand : 0;
+    const int sgrid = bounded_grid(tu.grids[kTuneUnit], (max_units + kWaves - 1) / kWaves);
+#define VX_UNIT(KD, C, T, GRID, BYTES)                                                                           \
   do {                                                                                                          \
-    constexpr size_t bytes_ = unit_lds_bytes<KD, C>();                                                          \
+    constexpr size_t bytes_ = BYTES;                                                                            \
     static bool attr_ = false;                                                                                  \
     if (!attr_) {                                                                                               \
-      (void)hipFuncSetAttribute((const void*)k_unit<KD, C>, hipFuncAttributeMaxDynamicSharedMemorySize,        \
+      (void)hipFuncSetAttribute((const void*)k_unit<KD, C, T>, hipFuncAttributeMaxDynamicSharedMemorySize,     \
                                 int(bytes_));                                                                   \
       attr_ = true;                                                                                             \
     }                                                                                                           \
-    hipLaunchKernelGGL((k_unit<KD, C>), dim3(ugrid), dim3(kBlock), bytes_, s, w.rec, w.dirs, R.prim, w.tstart,  \
-                       w.units, w.ctl, L, lats, w.unv, w.unp, w.usoff, w.st, w.stage_ctr, stats);              \
+    hipLaunchKernelGGL((k_unit<KD, C, T>), dim3(GRID), dim3(kBlock), bytes_, s, w.rec, w.dirs, R.prim, w.tstart,     \
+                       w.units, w.ctl, L, lats, w.unv, w.unp, w.usoff, w.st, w.stage_ctr, stats, small);       \
   } while (0)
-#define VX_UNIT_KIND(KD)                                        \
-  switch (tu.unit_budget) {                                     \
-    case 1024: VX_UNIT(KD, 1024); break;                        \
-    case 1536: VX_UNIT(KD, 1536); break;                        \
-    case 2048: VX_UNIT(KD, 2048); break;                        \
-    default: VX_UNIT(KD, 3072); break;                          \
+#define VX_UNIT_KIND(KD)                                                              \
+  switch (tu.unit_budget) {                                                           \
+    case 1024: VX_UNIT(KD, 1024, kBlock, ugrid, (unit_lds_bytes<KD, 1024>())); break; \
+    case 1536: VX_UNIT(KD, 1536, kBlock, ugrid, (unit_lds_bytes<KD, 1536>())); break; \
+    case 2048: VX_UNIT(KD, 2048, kBlock, ugrid, (unit_lds_bytes<KD, 2048>())); break; \
+    default: VX_UNIT(KD, 3072, kBlock, ugrid, (unit_lds_bytes<KD, 3072>())); break;  \
   }
     if (kind == 0) {
       VX_UNIT_KIND(0);
     } else {
       VX_UNIT_KIND(1);
+      if (small) VX_UNIT(1, kSmallCand, 64, sgrid, kWaves * small_lds_bytes() + 64);
     }
 #undef VX_UNIT_KIND
 #undef VX_UNIT

@@ -396,3 +396,38 @@ def test_one_call_counts(vx, monkeypatch, kind, limits):
         with pytest.raises(vx.VxError) as e:
             vx.voxelize_triangles(_dev(bad), wl.grid)
         assert e.value.status == 4
+
+
+@pytest.mark.parametrize("kind,n,size,log2_res", [("fibers", 3, 40, 8), ("fibers", 64, 80, 9), ("bundle", 40, 8, 6),
+                                                  ("tris", 300, 6.0, 8), ("tris", 2000, 1.0, 7),
+                                                  ("tris", 40, 0.2, 12), ("needle tris", 200, 30.0, 8)])
+def test_small_units_alike(vx, kind, n, size, log2_res):
+    """Units of up to 384 candidates in one-wave blocks (taken when the capacities say that units hold few
+    records) give the very voxels that blocks of four waves give, larger units among them or not."""
+    print(f"case: small units, {n} {kind} of {size}, R = {1 << log2_res}", flush=True)
+    if "tris" in kind:
+        wl = synth.random_triangles(n, log2_res, seed=n, scale=size, margin=2.0)
+        t = wl.tris.copy()
+        if kind == "needle tris":
+            t[:, 2] = t[:, 1] + np.float32(wl.grid.extent / (8 << log2_res))
+        mk = lambda **kw: vx.VoxelizePlan(0, wl.grid, _dev(t), **kw)
+    elif kind == "bundle":                    # many parallel fibers through the same voxels
+        rng = np.random.default_rng(n)
+        wl = synth.random_fibers(n, int(size), log2_res, seed=1, step=1.0, margin=1.0)
+        line = np.linspace(0.3, 0.7, int(size))[None, :, None] * np.array([1.0, 0.9, 0.8]) * wl.grid.extent
+        pts = (line + rng.normal(0, 0.3 * wl.grid.extent / (1 << log2_res), (n, 1, 3))).reshape(-1, 3)
+        mk = lambda **kw: vx.VoxelizePlan(1, wl.grid, _dev(pts.astype(np.float32)), offsets=_dev(wl.offsets),
+                                          radius=wl.radius, **kw)
+    else:
+        wl = synth.random_fibers(n, int(size), log2_res, seed=n, step=1.0, margin=4.0)
+        mk = lambda **kw: vx.VoxelizePlan(1, wl.grid, _dev(wl.pts), offsets=_dev(wl.offsets), radius=wl.radius, **kw)
+    p = mk().run()
+    a = p.check().numpy()
+    r, u = p.n_records, p.n_units
+    print("records", r, "units", u, "pairs", p.n_pairs, "voxels", len(a["keys"]), flush=True)
+    assert u > 0
+    # every unit by four waves: capacities that say nothing; some by one: more records than units, but few
+    wide = mk(max_records=r, max_units=8 * r + u, out_cap=p.out.cap).run().check().numpy()
+    q = mk(max_records=max(r, u), max_units=max(u, max(r, u) // 8 + 1), out_cap=p.out.cap).run()
+    one = q.check().numpy()
+    assert all(np.array_equal(wide[k], a[k]) and np.array_equal(wide[k], one[k]) for k in a)
