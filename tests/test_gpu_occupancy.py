@@ -162,3 +162,26 @@ def test_errors(vx):
     big = synth.Grid((0.0, 0.0, 0.0), 16.0, 18)
     with pytest.raises(vx.VxError):                     # log2_res above 17
         vx.OccupancyPlan(0, big, _dev(a.tris), lod)
+
+
+@pytest.mark.parametrize("axis", [0, 1, 2])
+@pytest.mark.parametrize("radius", [0.0, 0.0625, 0.4375, 2.25])
+def test_capsules_along_and_across_columns(vx, axis, radius):
+    """Segments that move least along each axis: across it, nearly across, along the other two, points,
+    ends inside the voxel and far outside it, radii of none, half, several and many sub-cells, with
+    ends on sub-cell corners and half-cells, so that spheres, cylinders and their end planes all
+    pass through centres, faces and corners of sub-cells somewhere."""
+    rng = np.random.default_rng(7 * axis + int(radius * 100))
+    grid = synth.Grid((0.0, 0.0, 0.0), 8.0, 3)
+    n = 24
+    a = rng.integers(8, 56, size=(n, 3)) * 1.0
+    d = rng.integers(-20, 21, size=(n, 3)) * 1.0
+    d[:, axis] = rng.integers(-1, 2, size=n) * rng.choice([0.0, 0.125, 1.0], size=n)
+    d[::6, (axis + 1) % 3] = 0.0
+    d[::8] = 0.0                                          # points
+    a[1::3] += 0.5
+    pts = (np.stack([a, a + d], 1).reshape(-1, 3) / 8.0).astype(np.float32)
+    off = np.arange(0, 2 * n + 1, 2)
+    say(f"case: occupancy, {n} segments across axis {axis}, radius {radius}, 8^3, 3 levels")
+    lod, occ, _ = _pyramid(vx, 1, grid, _dev(pts), 3, _dev(off), radius)
+    compare(lod, occ, occupancy_fibers(grid, pts, off, radius, 3), f"axis {axis} radius {radius}")
