@@ -1038,11 +1038,15 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
         }
         Moment m{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         for (uint32_t i0 = a; i0 < z; i0 += 8) {
-          // the loads of a group do not wait for each other, the sums stay in order
+          // the loads of a group do not wait for each other, the sums stay in order.  Cleared first:
+          // values that no load sets would be kept over the whole unit, and from one to the next
+          // (28 registers spilled; the brushed surface 6.07 -> 5.83 ms, 64 strands 67 -> 55 us)
           float4 t[8];
           float wv[8];
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
+            t[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+            wv[k] = 0.f;
             if (i0 + k < z) {
               const uint16_t x = S.idx[i0 + k];
               t[k] = dirs[S.prim[x]];
