@@ -631,7 +631,7 @@ __device__ __forceinline__ void write_voxel(const Stage& st, int64_t i, uint64_t
 }
 
 // Bound by VALU issue (three quarters of the cycles) and the latencies above.  The whole brushed
-// surface (149 M pairs): 7.95 -> 5.75 ms with the area by integration (2.2 ms of it; 3.7 before), unit
+// surface (149 M pairs): 7.95 -> 5.99 ms with the area by integration (2.4 ms of it; 3.7 before), unit
 // codes spread over 4 bits instead of 21, and half the candidates decided by a vertex in the box.
 // Fibers are weighed from the records in LDS, one reciprocal an axis: 14 patches (64,000 units) 2.46 ->
 // 2.21 ms, a weave (10,000 units) 0.515 -> 0.460 ms against records gathered again from memory after

@@ -106,3 +106,20 @@ def test_pieces_make_the_whole(area, sb):
         total = sum(area[0](q, np.array([x, y, z]), sb) for x in range(lo[0], hi[0] + 1)
                     for y in range(lo[1], hi[1] + 1) for z in range(lo[2], hi[2] + 1))
         assert abs(total - whole) <= 2e-7 * whole, (q.tolist(), total, whole)
+
+
+@pytest.mark.parametrize("sb", [11, 13, 17])
+def test_both_routines_round_alike(area, sb):
+    """A piece close to a boundary between two floats takes the other routine: the last bits agree."""
+    rng = np.random.default_rng(20 + sb)
+    s, taken = 1 << sb, 0
+    for i in range(9000):
+        q = _triangle(rng, (0, 1, 2, 5)[i % 4], s)
+        lo, hi = np.maximum(-((-q.min(0)) // s) - 1, 0), q.max(0) // s
+        if not np.cross(q[1] - q[0], q[2] - q[0]).any():
+            continue
+        v = np.array([int(rng.integers(a, b + 1)) for a, b in zip(lo, hi)], np.int64)
+        got, ref = area[0](q, v, sb), area[1](q, v, sb)
+        taken += ref > 0.0
+        assert got == ref, (q.tolist(), v.tolist(), got, ref)
+    assert taken > 1500
