@@ -13,10 +13,16 @@
 // (each zeroes one off-diagonal entry), until the off-diagonal part is below 2^-52 of the
 // diagonal or after 12 sweeps.  Quotients and square roots use the hardware reciprocal and
 // reciprocal-square-root estimates refined by Newton steps.  The kernel streams 28 bytes in and up to
-// 82 bytes out per voxel; bound by HBM and by the rotations about alike (5.13 M voxels: 0.170 ms;
-// 0.122 ms with one sweep; with a quotient in every rotation 0.184 ms).  Eigenvalues and vectors are
-// written past the caches: what reads the codes next, as the decoder does, then finds them there
-// (decoding 0.031 ms instead of 0.038).
+// 82 bytes out per voxel; bound by HBM and by the rotations about alike (5.13 M voxels: 0.184 to
+// 0.193 ms from run to run; 0.122 ms with one sweep).  Eigenvalues and vectors are written past the
+// caches: what reads the codes next, as the decoder does, then finds them there (decoding 0.030 ms
+// instead of 0.038).
+//
+// The rotations' operations decide bytes.  Where the ratio of two sums of 24 bits is the square of an
+// odd number over 510, the value that a code rounds lies exactly on a tie (one code in about 10^8 of a
+// fabric's), and the last places of the FP64 arithmetic say which way it goes.  A rotation by two
+// reciprocal roots and no quotient takes 0.170 ms, but turns 174 of 512 such ties the other way than
+// codes written so far.
 #include "vx_internal.hpp"
 
 namespace vx {
@@ -45,16 +51,13 @@ __device__ __forceinline__ void jacobi_rotate(double (&a)[3][3], double (&V)[3][
   constexpr int R = 3 - P - Q;
   const double apq = a[P][Q];
   if (!(fabs(apq) > skip)) return;        // already negligible against the diagonal
-  // the rotation by the smaller angle: with r = 1 / sqrt(d^2 + 4 a_pq^2), cos 2a = |d| r and
-  // sin 2a = 2 a_pq sgn(d) r, so c = sqrt((1 + |d| r) / 2) and s = sin 2a / (2 c): two reciprocal
-  // roots and no quotient
+  // tangent of the rotation angle, the smaller root of t^2 + 2 theta t - 1 = 0 with
+  // theta = d / (2 a_pq): t = 2 a_pq sgn(d) / (|d| + sqrt(d^2 + 4 a_pq^2)), one quotient
   const double d = a[Q][Q] - a[P][P];
-  const double r = rsqrt_nr(fma(d, d, 4.0 * apq * apq));
-  const double c2 = fma(0.5 * fabs(d), r, 0.5);
-  const double rc = rsqrt_nr(c2);
-  const double c = c2 * rc;
-  const double s = (d < 0.0 ? -apq : apq) * r * rc;
-  const double t = s * rc;
+  const double q = fma(d, d, 4.0 * apq * apq);
+  const double t = (d < 0.0 ? -2.0 * apq : 2.0 * apq) * rcp_nr(fabs(d) + q * rsqrt_nr(q));
+  const double c = rsqrt_nr(fma(t, t, 1.0));
+  const double s = t * c;
   a[P][P] -= t * apq;
   a[Q][Q] += t * apq;
   a[P][Q] = a[Q][P] = 0.0;
@@ -129,7 +132,7 @@ __global__ void __launch_bounds__(kCBlock) k_sggx_compact(const float* __restric
         const double diag = fabs(a[0][0]) + fabs(a[1][1]) + fabs(a[2][2]);
         if (!(off > 0x1p-52 * diag)) break;
         // entries below 2^-56 of the diagonal are left alone (their sum stays under the stop
-        // level); the floor 2^-500 keeps 4 a_pq^2 a normal number, so every reciprocal root of a
+        // level); the floor 2^-500 keeps 4 a_pq^2 a normal number, so every quotient of a
         // rotation is finite
         const double skip = fmax(0x1p-56 * diag, 0x1p-500);
         jacobi_rotate<0, 1>(a, V, skip);

@@ -8,6 +8,7 @@ only where the eigenvalues are apart, so they are compared where the gaps exceed
 lambda_1 and the sign rule is decided by a margin; everywhere else they are checked for being
 a valid frame (orthonormal, rebuilding the oracle's fitted matrix).
 """
+import math
 import sys
 
 import numpy as np
@@ -214,3 +215,40 @@ def test_full_size_plain_weave_properties(vx):
     dec = vx.sggx_decode(code.to(torch.uint8).contiguous(), n=n)[:, :n].double()
     sig = torch.sqrt(fit[:3] / fit[:3].max(dim=0).values)
     assert (sig - torch.sqrt(dec[:3].clamp_min(0))).abs().max() <= 0.5 / 255 + 1e-5
+
+
+def tie_moments(n, seed):
+    """(w, S) with S_xx / S_yy = (m / 510)^2 exactly, m odd: the value that the code of the first axis
+    rounds is m / 2, a tie.  Returns the lower of its two neighbours too."""
+    g = np.random.default_rng(seed)
+    w, S, low = np.empty(n, np.float32), np.empty((6, n), np.float32), np.empty(n, np.int64)
+    for i in range(n):
+        m = 2 * int(g.integers(64, 254)) + 1
+        f = math.gcd(m, 510)
+        a, b = (m // f) ** 2, (510 // f) ** 2
+        k = int(g.integers((1 << 23) // b + 1, (1 << 24) // b))
+        lo, hi = a * k, b * k                                  # whole numbers below 2^24
+        S[:3, i] = lo, hi, int(g.uniform(0.6, 0.95) * hi)
+        S[3:, i] = g.uniform(-0.2, 0.2, size=3) * lo
+        S[:, i] *= np.float32(2.0 ** -23)
+        w[i] = g.uniform(0.5, 4.0)
+        low[i] = (m - 1) // 2
+    return w, S, low
+
+
+# a bit a voxel: rounded up
+TIES_UP = ("689160e5cd9203e3989445c8908e40020000c6644012050884800086d926409020c2762462aa09958e6781ba0584"
+           "26068167842000512080393002500cc92c24")
+
+
+def test_ties_round_as_ever(vx):
+    """Sums of 24 bits make exact ties (one code in 10^8 of a fabric's): the last places of the FP64
+    arithmetic decide them, so the bytes of stored codes hang on every one of its operations."""
+    import torch
+    n = 512
+    say(f"case: sggx_compact, {n} voxels on a rounding tie")
+    w, S, low = tie_moments(n, 29)
+    _, _, code = vx.sggx_compact(torch.as_tensor(w).cuda(), torch.as_tensor(S).cuda(), eps=EPS, vectors=False)
+    up = code.cpu().numpy()[:, 0].astype(np.int64) - low
+    want = np.unpackbits(np.frombuffer(bytes.fromhex(TIES_UP), np.uint8)).astype(np.int64)
+    assert np.array_equal(up, want), f"{int((up != want).sum())} of {n} ties rounded the other way"
