@@ -185,3 +185,32 @@ def test_capsules_along_and_across_columns(vx, axis, radius):
     say(f"case: occupancy, {n} segments across axis {axis}, radius {radius}, 8^3, 3 levels")
     lod, occ, _ = _pyramid(vx, 1, grid, _dev(pts), 3, _dev(off), radius)
     compare(lod, occ, occupancy_fibers(grid, pts, off, radius, 3), f"axis {axis} radius {radius}")
+
+
+@pytest.mark.parametrize("log2", [12, 15, 16, 17])
+def test_capsules_from_far_away(vx, log2):
+    """Segments that begin a grid's length outside the grid and end a few voxels inside it, nearly along
+    an axis, on grids up to the largest: the distances are differences of numbers up to 2^40 sub-cells
+    squared.  The first two are wrong by single sub-cells when their rounding is not allowed for."""
+    rng = np.random.default_rng(log2)
+    far, s = 1 << 23, 1 << (23 - log2)
+    segs = [([0, 4194448, 4194561], [8388607, 4194448, 4194560]), ([3, 4194376, 4194433], [8388603, 4194376, 4194432])]
+    segs = [(np.array(a), np.array(b)) for a, b in segs]
+    for a, b in segs:                                       # moved by whole voxels: the last four stay inside
+        a[0] -= far - 4 * s
+        b[0] -= far - 4 * s
+    for i in range(16):
+        a = rng.integers(8 * s, far - 8 * s, size=3)
+        b = a + rng.integers(-far // 10000, far // 10000 + 1, size=3) * (i % 2) + rng.integers(-2, 3, size=3)
+        ax = i % 3
+        a[ax], b[ax] = -far + rng.integers(0, 8), 3 * s + rng.integers(0, s)
+        b = np.clip(b, 8 * s if s < 64 else s, far - s)
+        b[ax] = min(int(b[ax]), 4 * s)
+        segs.append((a, b))
+    pts = (np.array(segs).reshape(-1, 3) / float(s)).astype(np.float32)
+    assert np.array_equal(np.rint(pts.astype(np.float64) * s), np.array(segs).reshape(-1, 3))
+    off = np.arange(0, 2 * len(segs) + 1, 2)
+    grid = synth.Grid((0.0, 0.0, 0.0), float(1 << log2), log2)
+    say(f"case: occupancy, {len(segs)} segments from outside the grid, radius 0.5, {1 << log2}^3, 3 levels")
+    lod, occ, _ = _pyramid(vx, 1, grid, _dev(pts), 3, _dev(off), 0.5)
+    say(compare(lod, occ, occupancy_fibers(grid, pts, off, 0.5, 3), f"from far away, {1 << log2}^3"))
