@@ -655,7 +655,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
   int64_t* const claims = reinterpret_cast<int64_t*>(lds + kWaves * small_lds_bytes());   // [kWaves + 1] (kOne)
   const int64_t n_units = ctl[CTL_N_UNITS];
   const int tid = threadIdx.x % NT;
-  // the four waves' claims together; every wave calls it once a round
+  // the four waves' claims together; all waves of the block call it once a round, from one place
   const auto claim_together = [&](int32_t nv) -> int64_t {
     const int wv = threadIdx.x / 64;
     if (tid == 0) claims[wv] = nv;
@@ -674,18 +674,14 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
     return claims[kWaves] + claims[wv];               // (the next round's first barrier comes after this read)
   };
   for (int64_t u0 = int64_t(blockIdx.x) * kAtOnce; u0 < n_units; u0 += int64_t(gridDim.x) * kAtOnce) {
-    const int64_t u = kOne ? u0 + threadIdx.x / NT : u0;
-    if (kOne && u >= n_units) {
-      (void)claim_together(0);
-      continue;
-    }
-    const Unit U = units[u];
-    if (kOne && U.cand > CAND) {
-      (void)claim_together(0);
-      continue;
-    }
+    // (a wave's index by readfirstlane: uniform, and so is all that hangs on it.)  A wave that has no
+    // small unit this round walks through with an empty one, so that the block's barriers stand where
+    // all four waves pass
+    const int64_t u = kOne ? u0 + __builtin_amdgcn_readfirstlane(threadIdx.x / 64) : u0;
+    const Unit U = units[u < n_units ? u : u0];
     if (!kOne && U.cand <= small) continue;           // (small: what single waves take, 0: none)
-    const int64_t s = tstart[U.tile], e = tstart[U.tile + 1];
+    const bool live = !kOne || (u < n_units && U.cand <= CAND);
+    const int64_t s = live ? tstart[U.tile] : 0, e = live ? tstart[U.tile + 1] : 0;
     int32_t usz[3];
     unit_box(U.lev, U.ncell, usz);
     const uint64_t m0 = morton3(uint32_t(U.o[0]), uint32_t(U.o[1]), uint32_t(U.o[2]));   // the unit's first key
@@ -969,7 +965,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
       S.misc[1] = int32_t(b & 0xffffffff);
       S.misc[2] = int32_t(b >> 32);
     }
-    if (tid == 0) {
+    if (tid == 0 && live) {
       if (b + nv > st.cap) flag_set(stats, VX_FLAG_VOXEL_CAPACITY);
       unv[u] = nv;
       unp[u] = np;
@@ -1013,7 +1009,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
     }
     unit_sync<NT>();
     if constexpr (!kOne) b = int64_t(uint32_t(S.misc[1])) | (int64_t(S.misc[2]) << 32);
-    const uint64_t hi = lats ? uint64_t(uint32_t(rec[int64_t(rprim[s]) * kRec + 15])) << kPatchShift : 0ull;
+    const uint64_t hi =
+        lats && live ? uint64_t(uint32_t(rec[int64_t(rprim[s]) * kRec + 15])) << kPatchShift : 0ull;
     if (b + nv <= st.cap) {
       for (int32_t v = tid; v < nv; v += NT) {
         // its pairs: [start, next start), or (stably placed: the starts have run to the ends) [last

@@ -431,3 +431,45 @@ def test_small_units_alike(vx, kind, n, size, log2_res):
     q = mk(max_records=max(r, u), max_units=max(u, max(r, u) // 8 + 1), out_cap=p.out.cap).run()
     one = q.check().numpy()
     assert all(np.array_equal(wide[k], a[k]) and np.array_equal(wide[k], one[k]) for k in a)
+
+
+def _boxes_of_candidates(sizes, log2_res, seed):
+    """Two-point fibers whose candidate boxes have the extents of ``sizes``, a list of boxes for every tile
+    of 16^3: (points, offsets, tiles)."""
+    rng = np.random.default_rng(seed)
+    per = 1 << (log2_res - 4)
+    tiles = rng.permutation(per ** 3)[:len(sizes)]
+    pts = []
+    for t, boxes in zip(tiles, sizes):
+        for box in boxes:
+            a = 16 * np.array([t % per, t // per % per, t // per ** 2]) + np.array([rng.integers(0, 17 - e) for e in box])
+            pts += [a + 0.3, a + np.array(box) - 1 + 0.6]
+    off = np.arange(0, len(pts) + 1, 2)
+    return np.array(pts, np.float32), off
+
+
+@pytest.mark.parametrize("n", [1, 4, 7, 18, 61])
+def test_units_about_the_small_limit(vx, n):
+    """Units of 383, 384 and 385 candidates among ones of a few, in groups of four waves with a last one
+    that is not full: single waves take those of up to 384, blocks the others."""
+    kinds = [[(6, 7, 9), (5, 1, 1)], [(8, 8, 6)], [(5, 7, 11)], [(2, 3, 1)], [(16, 16, 11)], [(1, 1, 1)]]
+    sizes = [kinds[i % len(kinds)] for i in range(n)]
+    cand = [sum(int(np.prod(b)) for b in boxes) for boxes in sizes]
+    log2_res = 7
+    pts, off = _boxes_of_candidates(sizes, log2_res, n)
+    grid = synth.Grid((0.0, 0.0, 0.0), 128.0, log2_res)
+    print(f"case: {n} units of {sorted(set(cand))} candidates", flush=True)
+    mk = lambda **kw: vx.VoxelizePlan(1, grid, _dev(pts), offsets=_dev(off), radius=0.2, **kw)
+    p = mk().run()
+    a = p.check().numpy()
+    r, u = p.n_records, p.n_units
+    assert u == n and p.n_cand == sum(cand) and u <= r <= 12 * u          # single waves, by the counts
+    wide = mk(max_records=r, max_units=8 * r + u, out_cap=p.out.cap).run().check().numpy()
+    assert all(np.array_equal(wide[k], a[k]) for k in a)
+    b = oracle.voxelize_fibers(grid, pts, off, 0.2)
+    assert np.array_equal(a["keys"].astype(np.uint64), b.keys) and np.array_equal(a["count"], b.count)
+    batch = vx.BatchPlan([vx.Patch(grid, _dev(pts), off, 0.2)] * 3, K=1, levels=1).run()
+    batch.check()
+    for i in range(3):
+        got = batch.patch_level(i, 0)
+        assert all(np.array_equal(got[k].astype(a[k].dtype), a[k]) for k in ("keys", "count", "w", "S"))
