@@ -387,8 +387,8 @@ class VoxelizePlan:
             return r, None, None
         if u > self.FIRST_UNITS:
             return r, u, None
-        if keep and v <= self.FIRST_VOXELS:
-            self._first = (out, h)
+        if keep and v <= self.FIRST_VOXELS and h[STAT_FLAGS] == 0:
+            self._first = (out, h)        # (with any flag set, run().check() reports it)
         return r, u, v
 
     def _take_first(self):

@@ -473,3 +473,23 @@ def test_units_about_the_small_limit(vx, n):
     for i in range(3):
         got = batch.patch_level(i, 0)
         assert all(np.array_equal(got[k].astype(a[k].dtype), a[k]) for k in ("keys", "count", "w", "S"))
+
+
+@pytest.mark.parametrize("kind", ["tris", "fibers"])
+def test_one_call_reports_every_flag(vx, monkeypatch, kind):
+    """A status bit of the pass that a one-call voxelization counts by is raised like any run's."""
+    wl = synth.icosphere(subdiv=2, log2_res=5) if kind == "tris" else synth.random_fibers(4, 12, 5, seed=3)
+    print(f"case: one call with a flag set, {kind}", flush=True)
+    call = vx.VoxelizePlan._call
+
+    def flagged(self, *a):
+        call(self, *a)
+        self.stats[vx.STAT_FLAGS] |= vx.FLAG_UNIT_CAPACITY
+
+    monkeypatch.setattr(vx.VoxelizePlan, "_call", flagged)
+    with pytest.raises(vx.VxError) as e:
+        if kind == "tris":
+            vx.voxelize_triangles(_dev(wl.tris), wl.grid)
+        else:
+            vx.voxelize_fibers(_dev(wl.pts), _dev(wl.offsets), wl.radius, wl.grid)
+    assert e.value.status == 2
