@@ -100,10 +100,12 @@ __device__ __forceinline__ T quad(const T* S, const T m[6]) {
 // forward.  Bound by FP32 arithmetic (0.69 M voxels, 2.7 M children, 128 directions: 0.25 ms;
 // with sixteen lanes per voxel, the sums read from LDS for every direction, 0.58 ms).
 // ---------------------------------------------------------------------------------------------
-// sqrt(x): the reciprocal root's estimate, refined on the residual x - s^2; zeros and numbers so
-// small that the residual underflows take the library's function
+// sqrt(x): the reciprocal root's estimate, refined on the residual x - s^2; zeros, numbers so small
+// that the residual underflows, infinities and NaN take the library's function (whatever lies outside
+// [2^-96, inf), by one comparison of the bits)
 __device__ __forceinline__ float sqrt_nrf(float x) {
-  if (__builtin_amdgcn_ballot_w64(!(x >= 0x1p-96f))) return sqrtf(x);
+  constexpr uint32_t least = 0x0f800000u, inf = 0x7f800000u;
+  if (__builtin_amdgcn_ballot_w64(__float_as_uint(x) - least >= inf - least)) return sqrtf(x);
   const float r = __builtin_amdgcn_rsqf(x), s = x * r;
   return fmaf(fmaf(-s, s, x), 0.5f * r, s);
 }

@@ -176,3 +176,16 @@ def test_direction_rows_and_level_ranges(vx, ndir, lo, hi):
     e_p = np.linalg.norm(dpts.cpu().numpy() - o_dp) / np.linalg.norm(o_dp)
     say("loss", loss, o_loss, "relative gradient errors: lobes %.3g, points %.3g" % (e_L, e_p))
     assert e_L <= 1e-4 and e_p <= 1e-4
+
+
+@pytest.mark.parametrize("ndir", [96, 128])
+def test_overflowing_lobes(vx, ndir):
+    """Lobes whose projected area overflows FP32: the loss is infinite, not a NaN."""
+    import torch
+    wl = synth.plain_weave(n_fibers=4, seed=23)
+    say(f"case: fit with lobes of 1e25, {ndir} directions")
+    pd = torch.as_tensor(_lattice_points(wl.grid, wl.pts)).cuda()
+    plan = vx.FitPlan(wl.grid, pd, torch.as_tensor(wl.offsets).cuda(), wl.radius, 1, 3, ndir=ndir)
+    params = vx.fit_init(plan, seed=4)
+    params[1][:, [0, 2, 5, 6, 8, 11]] = 1e25
+    assert float(plan.forward(pd, params).item()) == float("inf")
