@@ -116,7 +116,12 @@ __global__ void __launch_bounds__(kBlock) k_fit_fwd(FitLevels lv, const float* _
   const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float x[DPL][3], m[DPL][6];
 #pragma unroll
-  for (int i = 0; i < DPL; ++i) dir_products(dirs, ndir, lane + 64 * i, x[i], m[i]);
+  for (int i = 0; i < DPL; ++i) {
+    // past the set the last direction again, its residual dropped: zeros there would send every root of
+    // the wave to the library's function (0.69 M voxels, 100 directions: 0.267 -> 0.255 ms)
+    const int k = lane + 64 * i;
+    dir_products(dirs, ndir, k < ndir ? k : ndir - 1, x[i], m[i]);
+  }
   const float rdir = float(ndir);
   for (int64_t i0 = int64_t(blockIdx.x) * kWaves + wv;; i0 += int64_t(gridDim.x) * kWaves) {
     int64_t u = i0;
@@ -160,7 +165,7 @@ __global__ void __launch_bounds__(kBlock) k_fit_fwd(FitLevels lv, const float* _
         const float y1 = lj[2] * x[i][1] + lj[4] * x[i][2], y2 = lj[5] * x[i][2];
         f += sqrt_nrf(y0 * y0 + y1 * y1 + y2 * y2);
       }
-      const float r = f - tau[i] * invW;
+      const float r = lane + 64 * i < ndir ? f - tau[i] * invW : 0.f;
       acc = fmaf(r, r, acc);
     }
     acc = wave_sum(acc);
