@@ -397,16 +397,19 @@ struct FitDown {
   const int32_t* pidx[kMaxFit];    // index of every voxel's parent
   double* g[kMaxFit];              // [7][gcap]
   int64_t gcap[kMaxFit];
+  uint32_t last[kMaxFit];          // gcap - 1 (indexes are 32-bit)
   int lo, hi;                      // levels lo .. hi - 1 hold gradients
 };
 __global__ void __launch_bounds__(kBlock) k_fit_down(FitDown d, const int64_t* n_p) {
   const int64_t n = *n_p;
   for (int64_t c = int64_t(blockIdx.x) * kBlock + threadIdx.x; c < n; c += int64_t(gridDim.x) * kBlock) {
+    // A level over its capacity (flagged: the gradients are invalid) leaves children without a parent and
+    // their index unset: held inside the buffers, whatever it is
     int32_t at[kMaxFit];
     at[0] = int32_t(c);
 #pragma unroll
     for (int L = 1; L < kMaxFit; ++L)
-      if (L < d.hi) at[L] = d.pidx[L - 1][at[L - 1]];
+      if (L < d.hi) at[L] = int32_t(min(uint32_t(d.pidx[L - 1][at[L - 1]]), d.last[L]));
     double acc[7] = {0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int L = kMaxFit - 1; L >= 0; --L)
@@ -418,13 +421,16 @@ __global__ void __launch_bounds__(kBlock) k_fit_down(FitDown d, const int64_t* n
   }
 }
 
-// leaf lookup table: first and end leaf index of every 16^3 tile (empty tiles: 0, 0)
+// leaf lookup table: first and end leaf index of every 16^3 tile (empty tiles: 0, 0).  A leaf over its
+// capacity (flagged) was not written, so its keys may be anything: those past the grid are left out.
 template <class Key>
 __global__ void __launch_bounds__(kBlock) k_tile_index(const Key* __restrict__ keys, const int64_t* n_p,
-                                                       int64_t* __restrict__ tfirst, int64_t* __restrict__ tend) {
+                                                       int64_t tiles, int64_t* __restrict__ tfirst,
+                                                       int64_t* __restrict__ tend) {
   const int64_t n = *n_p;
   for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += int64_t(gridDim.x) * kBlock) {
     const uint64_t t = uint64_t(keys[i]) >> (3 * kTileBits);
+    if (t >= uint64_t(tiles)) continue;
     if (i == 0 || (uint64_t(keys[i - 1]) >> (3 * kTileBits)) != t) tfirst[t] = i;
     if (i == n - 1 || (uint64_t(keys[i + 1]) >> (3 * kTileBits)) != t) tend[t] = i + 1;
   }
@@ -903,6 +909,7 @@ vx_status fit_backward_run(const vx_grid* g, const float* pts, int64_t n_pts, co
       d.pidx[L] = w.pidx[L];
       d.g[L] = w.g[L];
       d.gcap[L] = caps[L];
+      d.last[L] = uint32_t(caps[L] - 1);
     }
     hipLaunchKernelGGL(k_fit_down, dim3(blocks_for(caps[0], 4 * kGrid)), dim3(kBlock), 0, s, d, n_levels);
   }
@@ -916,10 +923,10 @@ vx_status fit_backward_run(const vx_grid* g, const float* pts, int64_t n_pts, co
     launch_fill_i64(w.tend, tiles, 0, s);
     if (key64)
       hipLaunchKernelGGL(k_tile_index<uint64_t>, dim3(kGrid), dim3(kBlock), 0, s, (const uint64_t*)levels[0].keys,
-                         n_levels, w.tfirst, w.tend);
+                         n_levels, tiles, w.tfirst, w.tend);
     else
       hipLaunchKernelGGL(k_tile_index<uint32_t>, dim3(kGrid), dim3(kBlock), 0, s, (const uint32_t*)levels[0].keys,
-                         n_levels, w.tfirst, w.tend);
+                         n_levels, tiles, w.tfirst, w.tend);
   }
   {
     VX_TIMED("fit_pairs", s);

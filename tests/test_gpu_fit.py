@@ -189,3 +189,45 @@ def test_overflowing_lobes(vx, ndir):
     params = vx.fit_init(plan, seed=4)
     params[1][:, [0, 2, 5, 6, 8, 11]] = 1e25
     assert float(plan.forward(pd, params).item()) == float("inf")
+
+
+@pytest.mark.parametrize("what", ["level", "leaf"])
+def test_over_capacity_stays_in_bounds(vx, what):
+    """Points moved so far that a level, or the leaf, outgrows its buffer: forward and backward run to their
+    end whatever the buffers held before, the checks report it, and the plan goes on from the old points."""
+    import torch
+    n, R = 16, 64
+    yz = np.array([[(8 * (b % 4) + 2 + j % 2, 8 * (b // 4) + 2 + j // 2) for j in range(4)] for b in range(n)])
+    far = yz + 2 * np.array([(j % 2, j // 2) for j in range(4)])        # a bundle's four fibers in four parents
+    line = np.linspace(4.5, 30.5, 14)
+
+    def points(yz, x):
+        p = np.empty((n, 4, 14, 3), np.float32)
+        p[..., 0], p[..., 1], p[..., 2] = x, yz[:, :, None, 0] + 0.5, yz[:, :, None, 1] + 0.5
+        return torch.as_tensor(p.reshape(-1, 3)).cuda()
+
+    grid = synth.Grid((0.0, 0.0, 0.0), float(R), 6)
+    home = points(yz, line)
+    away = points(far, line) if what == "level" else points(yz, 2.0 * line)
+    say(f"case: fit over capacity of the {what}, {4 * n} straight fibers, {R}^3")
+    plan = vx.FitPlan(grid, home, torch.arange(0, 4 * n * 14 + 1, 14), 0.2, 1, 4, ndir=64)
+    params = vx.fit_init(plan, seed=4)
+    one = torch.ones(1, device="cuda")
+
+    def step():
+        loss = plan.forward(home, params).clone()
+        dpts, dparams = plan.backward(one, params)
+        plan.check()
+        return [loss, dpts] + dparams
+
+    before = step()
+    plan.ws.fill_(0x7f)
+    for v in plan.levels:
+        v.keys[v.n:] = -1
+    plan.forward(away, params, check=False)
+    plan.backward(one, params)
+    torch.cuda.synchronize()
+    with pytest.raises(vx.VxError) as e:
+        plan.check_forward()
+    assert e.value.status == 2
+    assert all(torch.equal(a, b) for a, b in zip(before, step()))
