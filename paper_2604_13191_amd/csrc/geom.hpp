@@ -841,9 +841,11 @@ VX_HD inline float tri_area(const int32_t* q, const int64_t v[3], int Sb, float 
 // and the mean of a clamped linear function.  FP64 throughout.  With M the triangle's extent in
 // voxels, every end is off by less than M s 2^-51 and the sum by less than M s^2 2^-48; a piece
 // smaller than 2^-20 M s^2 (where that exceeds 2^-28 of it; exact zeros among them) takes the
-// routine above instead, and so does one that lies within (M + 2) s^2 2^-47 of a boundary between
-// two floats: both routines then round to the same float, whose last bit can decide between the
-// equal lobes of a symmetric voxel (the brushed surface's unit kernel: 5.83 -> 5.99 ms with it).
+// routine above instead, and so does one that lies within (M + 2) s^2 2^-46 of a boundary between
+// two floats.  The routine above is off by less than M s^2 2^-46.4 (seven edges, each a cross product
+// from the first vertex of at most 2 M s^2, good to 2^-50, and their sum), so both then round to the same
+// float, whose last bit can decide between the equal lobes of a symmetric voxel.  (The brushed surface's
+// unit kernel: 5.83 -> 5.97 ms with it; a sphere of 1.0 M voxels 290 -> 307 us.)
 // ---------------------------------------------------------------------------------------------
 
 // integral of clamp(v, 0, s) du along (u0, v0) -> (u1, v1) over u in [0, s].  The mean over the
@@ -904,7 +906,8 @@ VX_HD inline __attribute__((noinline)) float tri_area_small(const int32_t* q, in
   const int u = h == 2 ? 0 : h + 1, w = h == 0 ? 2 : h - 1;
   const double e0u = double(q[3 + u] - q[u]), e0w = double(q[3 + w] - q[w]);
   const double e1u = double(q[6 + u] - q[u]), e1w = double(q[6 + w] - q[w]);
-  return float(a * (scale * fabs(fma(e0u, e1w, -(e0w * e1u)))));
+  // (scale is the doubled area, a float, over the projected one: their product rounds back to that float)
+  return float(a * double(float(scale * fabs(fma(e0u, e1w, -(e0w * e1u))))));
 }
 
 // area of the triangle inside [v, v+1)^3 in voxel^2
@@ -961,7 +964,7 @@ VX_HD inline float tri_area_under(const int32_t* q, const int32_t v[3], int Sb, 
   if (lo[0] || lo[1] || lo[2]) sum += area_under(xu[0], xv[0], yu[0], yv[0], s);
   if (hi[0] || hi[1] || hi[2]) sum += area_under(xu[1], xv[1], yu[1], yv[1], s);
   const double a = fabs(sum);
-  const double least = double(bits_float(how & ~3u)), off = 0x1p-27 * least;
+  const double least = double(bits_float(how & ~3u)), off = 0x1p-26 * least;
   if (!(a >= least) || float((a - off) * scale) != float((a + off) * scale)) {
     // mostly touches without area (a lattice-aligned mesh meets a quarter of its voxels in a face,
     // an edge or a corner only): decided exactly where the projection shows it

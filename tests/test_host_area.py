@@ -123,3 +123,17 @@ def test_both_routines_round_alike(area, sb):
         taken += ref > 0.0
         assert got == ref, (q.tolist(), v.tolist(), got, ref)
     assert taken > 1500
+
+
+@pytest.mark.parametrize("q, v, sb", [
+    ([22788, 26864, 18218, 16626, 22992, 18199, 19711, 28176, 21545], [2, 3, 2], 13),
+    ([5831, 5745, 7748, 4542, 8139, 5147, 4886, 5213, 7853], [2, 2, 3], 11),
+    ([25191, 21514, 30530, 20927, 20759, 30521, 18711, 20549, 27379], [3, 2, 3], 13),
+    ([7172, 4848, 6069, 7144, 4665, 6694, 7843, 4774, 6985], [3, 2, 3], 11),
+    ([7128, 4208, 6212, 6797, 5036, 4460, 4797, 4482, 4774], [2, 2, 2], 11),
+    ([7938, 4880, 7426, 4994, 7124, 8113, 7524, 6080, 7828], [2, 3, 3], 11)])
+def test_scaled_by_the_same_float(area, q, v, sb):
+    """Pieces whose area times the doubled area lies so near a float's boundary that the product with any
+    other double than that float rounds the other way."""
+    q, v = np.array(q, np.int64).reshape(3, 3), np.array(v, np.int64)
+    assert area[0](q, v, sb) == area[1](q, v, sb)
