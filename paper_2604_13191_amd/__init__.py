@@ -280,7 +280,7 @@ class VoxelizePlan:
     # 20,480 triangles takes 0.20 ms counted by one pass and 0.46 ms by three calls at 64^3, 0.28 and
     # 0.63 ms at 256^3.  A pass whose voxels do not fit has still given every total and costs what the
     # third counting call does (512^3, 1.0 M voxels: 0.96 and 1.09 ms), so the limits only bound the
-    # roomy buffers: under 60 MB.
+    # roomy buffers: about 60 MB.
     FIRST_MAX_PRIMS = 1 << 16
     FIRST_UNITS, FIRST_VOXELS = 1 << 17, 1 << 18
 
@@ -373,12 +373,16 @@ class VoxelizePlan:
         """The three totals from one whole pass; those after a capacity it exceeded are None."""
         import torch
         cap = 4 * self.n_prims + (1 << 14)
+        # fibers: more units than records, since the library takes their ratio for that of counts and small
+        # units to single waves by it (33,000 to 64,000 points with 11 to 166 records a unit: 10 to 70 us
+        # more a call; with 7 records a unit 30 us less)
+        units = max(self.FIRST_UNITS, cap + 1) if self.kind == 1 else self.FIRST_UNITS
         try:
             out = alloc_voxels(self.FIRST_VOXELS, self.grid.log2_res, self.device, False)
-            ws = self._ws_for(cap, self.FIRST_UNITS, self.FIRST_VOXELS)
+            ws = self._ws_for(cap, units, self.FIRST_VOXELS)
         except torch.OutOfMemoryError:
             return None, None, None
-        self._call(cap, self.FIRST_UNITS, _ptr(ws), ws.numel(), out.cstruct(), _stream())
+        self._call(cap, units, _ptr(ws), ws.numel(), out.cstruct(), _stream())
         h = self.stats.cpu().numpy()
         if h[STAT_FLAGS] & (FLAG_INPUT | FLAG_OFFSETS):
             raise VxError(4, "voxelize")

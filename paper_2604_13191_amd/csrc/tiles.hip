@@ -1342,7 +1342,8 @@ vx_status tile_voxelize(int kind, const vx_grid* g, const float* data, int64_t n
     const Lat* lats = batch ? batch->lats : nullptr;
     const int ugrid = bounded_grid(tu.grids[kTuneUnit], max_units);
     // Small units go to single waves where the capacities, taken from counts, say that units hold few
-    // records (fewer records than units: long segments, whose units are full, or no counts).  Unit
+    // records (fewer records than units: long segments, whose units are full, or capacities that are no
+    // counts, which give units the more room).  Unit
     // kernels of strands and weaves at 4.5 records a unit 104 us, 65 with single waves; at 7.4 133 and
     // 91; at 11 149 and 120; at 12.4 47 and 49; at 16.5 156 and 178, since the two kernels' rests add up.
     const int small = kind == 1 && max_units <= max_rec && max_rec <= 12 * max_units ? kSmallCand : 0;

@@ -493,3 +493,15 @@ def test_one_call_reports_every_flag(vx, monkeypatch, kind):
         else:
             vx.voxelize_fibers(_dev(wl.pts), _dev(wl.offsets), wl.radius, wl.grid)
     assert e.value.status == 2
+
+
+@pytest.mark.parametrize("points", [400, 30_000, 65_536])
+def test_counting_pass_gives_no_counts(vx, monkeypatch, points):
+    """The roomy capacities of a fiber set's counting pass never look like counts of few records a unit."""
+    wl = synth.random_fibers(points // 16, 16, 8, seed=2)
+    print(f"case: one call on {points} points", flush=True)
+    seen = []
+    call = vx.VoxelizePlan._call
+    monkeypatch.setattr(vx.VoxelizePlan, "_call", lambda self, r, u, *a: (seen.append((r, u)), call(self, r, u, *a)))
+    got = vx.voxelize_fibers(_dev(wl.pts), _dev(wl.offsets), wl.radius, wl.grid)
+    assert got.n > 0 and seen[0][1] > seen[0][0]         # (a run of its own follows where the voxels did not fit)
