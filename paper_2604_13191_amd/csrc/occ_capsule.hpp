@@ -42,7 +42,7 @@ VX_HD inline void put_turned(uint64_t (&word)[8], int turn, const Put& put) {
 // of radius h around its centre and lies in the one of radius h sqrt(3)): along a column of sub-cells,
 // the centres within a radius of the segment are one interval, solved for; those between the two
 // radii take cheap bounds and the exact voxel-level test on the sub-box.
-// Bound by VALU issue: 12.8 M pairs of a weave (radius of four sub-cells) 17.0 -> 10.2 ms, of it 4.8 the
+// Bound by VALU issue: 12.8 M pairs of a weave (radius of four sub-cells) 17.0 -> 10.1 ms, of it 4.8 the
 // columns, 2.5 the cheap bounds and 3 the exact tests; with the exact test inside the loop of the bounds
 // (a few lanes at a time) 14.0; before, every sub-cell was tried by its own distance.
 // ---------------------------------------------------------------------------------------------

@@ -166,7 +166,8 @@ __device__ __attribute__((noinline)) bool tri_occ_plane(double n0, double n1, do
 // The pair's mask, handed to put(word index, word) in Morton order.  Coordinates come rotated by
 // `turn` axes (axis 0 here is axis `turn`, the one the triangle is thinnest along: rows run along it
 // and there are few) and the words are rotated back.  One row of columns at a time in a rolled loop:
-// unrolled, its registers spill and the spills alone write 12 GB per 9 M pairs.
+// unrolled, the spills of its registers alone write 12 GB per 9 M pairs.  Rolled, 27 registers are
+// spilled at the kernel's three waves per SIMD (capsules: 21), 128 (160) bytes a lane.
 template <class Put>
 __device__ __forceinline__ void tri_occ_mask(const TriOcc& T, double sl, int turn, const Put& put) {
   uint64_t px = 0;                                       // row y, bits z

@@ -631,7 +631,7 @@ __device__ __forceinline__ void write_voxel(const Stage& st, int64_t i, uint64_t
 }
 
 // Bound by VALU issue (three quarters of the cycles) and the latencies above.  The whole brushed
-// surface (149 M pairs): 7.95 -> 5.99 ms with the area by integration (2.4 ms of it; 3.7 before), unit
+// surface (149 M pairs): 7.95 -> 5.97 ms with the area by integration (2.4 ms of it; 3.7 before), unit
 // codes spread over 4 bits instead of 21, and half the candidates decided by a vertex in the box.
 // Fibers are weighed from the records in LDS, one reciprocal an axis: 14 patches (64,000 units) 2.46 ->
 // 2.21 ms, a weave (10,000 units) 0.515 -> 0.460 ms against records gathered again from memory after
@@ -1037,7 +1037,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(uni
         for (uint32_t i0 = a; i0 < z; i0 += 8) {
           // the loads of a group do not wait for each other, the sums stay in order.  Cleared first:
           // values that no load sets would be kept over the whole unit, and from one to the next
-          // (28 registers spilled; the brushed surface 6.07 -> 5.83 ms, 64 strands 67 -> 55 us)
+          // (28 registers spilled, 11 that remain at four waves per SIMD, none at three and two; the
+          // brushed surface 6.07 -> 5.83 ms, 64 strands 67 -> 55 us)
           float4 t[8];
           float wv[8];
 #pragma unroll
