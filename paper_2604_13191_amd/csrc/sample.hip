@@ -572,49 +572,64 @@ __global__ void __launch_bounds__(kBlock) k_samp_back(const Key* __restrict__ ki
   }
 }
 
-// A wave sums 64 voxels, one a lane, each voxel's samples in order.  The voxels' records are one stretch
-// of the sorted list: their ids are read and their directions gathered 512 at a time, whoever's they
-// are, into LDS, and each lane takes its own from there, a record's direction as often as it counts.
-// Bound by the gathers (41.7 M samples in 16.7 M records, 3.1 M voxels: 0.10 ms; with each lane reading
-// its own samples from memory 0.54 ms).
+// A wave sums 64 voxels, one a lane, each voxel's samples in order, a record's direction as often as it
+// counts.  Bound by the gathers.  Triangles, where the 64 voxels' records fit one tile: they are one stretch
+// of the sorted list, so their ids are read and their directions gathered together into LDS, and each lane
+// takes its own from there (41.7 M samples in 16.7 M records, 3.1 M voxels: 0.096 ms, 0.117 by the other way).
+// Else each lane gathers its own records, eight at a time: through tiles the lanes of a crowded stretch
+// wait for one another (0.8 M samples in 4,096 voxels: 45 us, 310 by tiles; fibers, 159,920 in 588: 0.38 ms,
+// 2.9), and fibers' records, one a sample, are no faster by tiles (4.1 M in 1.8 M voxels: 36 us, 47).
 constexpr int kReduceTile = 512;
+constexpr int kReduceAtOnce = 8;
 template <int KIND, class Key, bool PACKED>
 __global__ void __launch_bounds__(kBlock) k_samp_reduce(Sorted<Key> sorted, const int64_t* __restrict__ start,
                                                         const float4* __restrict__ dirs,
                                                         const int64_t* __restrict__ ctl, vx_voxels out) {
-  __shared__ float4 stage[kWaves][kReduceTile];
-  __shared__ uint8_t counts[kWaves][kReduceTile];   // 1 to 64
-  float4* st = stage[threadIdx.x >> 6];
-  uint8_t* sc = counts[threadIdx.x >> 6];
+  __shared__ float4 stage[KIND == 0 ? kWaves : 1][KIND == 0 ? kReduceTile : 1];
+  __shared__ uint8_t counts[KIND == 0 ? kWaves : 1][KIND == 0 ? kReduceTile : 1];   // 1 to 64
+  float4* st = stage[KIND == 0 ? threadIdx.x >> 6 : 0];
+  uint8_t* sc = counts[KIND == 0 ? threadIdx.x >> 6 : 0];
   const int64_t nv = ctl[SC_VOX];
   const int64_t waves = int64_t(gridDim.x) * kWaves, wave = int64_t(blockIdx.x) * kWaves + (threadIdx.x >> 6);
   for (int64_t v0 = wave * 64; v0 < nv; v0 += waves * 64) {
     const int64_t v = v0 + lane_id(), vend = v0 + 64 < nv ? v0 + 64 : nv;
     const int64_t a = start[v < vend ? v : vend], b = start[v < vend ? v + 1 : vend];
-    const int64_t last = start[vend];
+    const int64_t first = start[v0], last = start[vend];
     Moment m{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     uint32_t samples = 0;
-    for (int64_t j0 = start[v0]; j0 < last; j0 += kReduceTile) {
+    if (KIND == 0 && last - first <= kReduceTile) {
       float4 d[kReduceTile / 64];
 #pragma unroll
       for (int r = 0; r < kReduceTile / 64; ++r) {
-        const int64_t j = j0 + r * 64 + lane_id();
+        const int64_t j = first + r * 64 + lane_id();
         int c;
         d[r] = dirs[sorted.template id<PACKED>(j < last ? j : last - 1, c)];
         sc[r * 64 + lane_id()] = uint8_t(c);
       }
 #pragma unroll
-      for (int r = 0; r < kReduceTile / 64; ++r)
-        st[r * 64 + lane_id()] = d[r];
+      for (int r = 0; r < kReduceTile / 64; ++r) st[r * 64 + lane_id()] = d[r];
       wave_lds_fence();
-      const int lo = int(a > j0 ? a - j0 : 0), hi = int(b - j0 < kReduceTile ? b - j0 : kReduceTile);
-      for (int q = lo; q < hi; ++q) {
+      for (int q = int(a - first); q < int(b - first); ++q) {
         const float4 t = st[q];
         const int c = sc[q];
         samples += uint32_t(c);
         for (int i = 0; i < c; ++i) accum_pair<KIND>(m, t.w, t);
       }
       wave_lds_fence();
+    } else {
+      for (int64_t j0 = a; j0 < b; j0 += kReduceAtOnce) {
+        float4 d[kReduceAtOnce];
+        int c[kReduceAtOnce];
+#pragma unroll
+        for (int r = 0; r < kReduceAtOnce; ++r)
+          d[r] = dirs[sorted.template id<PACKED>(j0 + r < b ? j0 + r : b - 1, c[r])];
+#pragma unroll
+        for (int r = 0; r < kReduceAtOnce; ++r) {
+          const int n = j0 + r < b ? (KIND == 0 ? c[r] : 1) : 0;
+          samples += uint32_t(n);
+          for (int i = 0; i < n; ++i) accum_pair<KIND>(m, d[r].w, d[r]);
+        }
+      }
     }
     if (v >= vend) continue;
     static_cast<Key*>(out.keys)[v] = sorted.key(a);

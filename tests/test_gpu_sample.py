@@ -204,3 +204,28 @@ def test_samples_sharing_voxels(vx, log2_res, n, N, scale):
     ref = oracle.sample_triangles(wl.grid, wl.tris, N)
     assert p.n_inside == ref.n_pairs and p.n_samples > 2 * len(ref.keys)
     say(compare_samples(g, ref, f"{n} triangles, R = {1 << log2_res}, N = {N}"))
+
+
+@pytest.mark.parametrize("each", [7, 8, 9, 300])
+def test_crowded_triangle_voxels(vx, each):
+    """64 neighbouring voxels with one-sample records, as many as one tile of the sum holds (8 a voxel), one
+    fewer and more, and voxels of very different counts among them."""
+    c = np.stack(np.meshgrid(*[np.arange(4)] * 3, indexing="ij"), -1).reshape(-1, 1, 1, 3)
+    rng = np.random.default_rng(each)
+    t = (c + 0.5 + rng.uniform(-0.4, 0.4, size=(64, each, 3, 3))).reshape(-1, 3, 3)
+    t = rng.permutation(np.concatenate([t, 3.5 + rng.uniform(-0.4, 0.4, size=(each // 9 * 40, 3, 3))]))
+    grid = synth.Grid((0.0, 0.0, 0.0), 4.0, 2)
+    tris = t.astype(np.float32)
+    say(f"case: sampled triangles, {len(tris)} in 64 voxels")
+    p, g = _tris(vx, grid, tris, 1)
+    assert p.n_samples == len(tris)
+    say(compare_samples(g, oracle.sample_triangles(grid, tris, 1), f"{each} a voxel"))
+
+
+@pytest.mark.parametrize("fibers,points,step", [(1, 2, 0.1), (3, 5000, 0.02), (20, 2000, 0.05), (300, 40, 0.4)])
+def test_crowded_fiber_voxels(vx, fibers, points, step):
+    """Fibers that stay in a few voxels, thousands of samples in some."""
+    wl = synth.random_fibers(fibers, points, 6, seed=points, step=step)
+    say(f"case: sampled fibers {fibers} x {points}, steps of {step} voxels")
+    _, g = _fibers(vx, wl, 2, 2)
+    say(compare_samples(g, oracle.sample_fibers(wl.grid, wl.pts, wl.offsets, 2, 2), f"{fibers} x {points}"))
