@@ -20,8 +20,7 @@
 namespace vx {
 namespace {
 
-enum { SC_TOTAL = 0, SC_SEGS = 1, SC_VOX = 2, SC_QMAX = 3, SC_SORT = 4, SC_OUTSIDE = 5, SC_WORDS = 6,
-       SC_RECORDS = 7 };
+enum { SC_TOTAL = 0, SC_SEGS = 1, SC_VOX = 2, SC_QMAX = 3, SC_SORT = 4, SC_OUTSIDE = 5, SC_WORDS = 6 };
 
 // A record: the voxel's key, the id of a chord or triangle and how many of its samples lie there, in
 // one word or with the key apart.
@@ -60,12 +59,16 @@ RecordBits record_bits(int kind, int64_t n_prims, int log2R, int sub) {
   return r;
 }
 
-// Blocks of the emission of triangles' samples, whose waves take equal stretches of them: a few rows of
-// 64 at least (the sort's first pass serves its blocks' stretches one by one), one fill of the chip at
-// most: six blocks a CU by their LDS (41.7 M samples: 0.30 ms; 0.33 with four, 0.31 with eight).
+// Blocks of the emission of triangles' samples, whose waves take equal stretches of them, a few rows of 64
+// at least: 512 samples a wave up to 1,024 blocks, 1,024 above (the sort's first pass serves the
+// stretches one by one, so more of them cost it what the emission gains: emission and sort of 1.0 M samples
+// 160 us, at 1,024 a wave 165, at 256 190; of 5 M 187, at 512 a wave 224).  One fill of the chip at most: six
+// blocks a CU by their LDS (41.7 M samples: 0.30 ms; 0.33 with four, 0.31 with eight).
 constexpr int kEmitGrid = 1536;
 int emit_blocks(int64_t max_samples) {
-  const int64_t b = (max_samples + 1024 * kWaves - 1) / (1024 * kWaves);
+  const int64_t few = (max_samples + 512 * kWaves - 1) / (512 * kWaves);
+  const int64_t many = (max_samples + 1024 * kWaves - 1) / (1024 * kWaves);
+  const int64_t b = few < kGrid ? few : (many < kGrid ? kGrid : many);
   return int(b < 1 ? 1 : (b > kEmitGrid ? kEmitGrid : b));
 }
 
@@ -446,10 +449,7 @@ __global__ void __launch_bounds__(kBlock) k_samp_tri_emit(const float* __restric
     }
     wave_lds_fence();
   }
-  if (lane == 0) {
-    filled[wave] = int32_t(o - o0);
-    atomicAdd(reinterpret_cast<unsigned long long*>(ctl + SC_RECORDS), (unsigned long long)(o - o0));
-  }
+  if (lane == 0) filled[wave] = int32_t(o - o0);
   add_outside(outs, ctl);
 }
 
@@ -474,10 +474,20 @@ struct CntIn {
   const int64_t* a;
   __device__ int64_t operator()(int64_t i) const { return a[i]; }
 };
-// the sort's element count: the records (merged) or samples, or none when they did not fit; and its 64s
-__global__ void k_samp_n(int64_t* ctl, int64_t cap, bool merged) {
+// The sort's element count: the samples, or the records (filled: what each of the emission's waves
+// wrote, added here -- counted by the waves, on one address 16 ns apart, they took a third of the emission),
+// or none when they did not fit; and its 64s.
+__global__ void __launch_bounds__(kBlock) k_samp_n(int64_t* ctl, int64_t cap, const int32_t* __restrict__ filled,
+                                                   int waves) {
+  __shared__ int64_t tmp[kWaves + 1];
+  const int64_t total = ctl[SC_TOTAL];
+  int64_t mine = 0, n = total;
+  if (filled) {
+    for (int i = threadIdx.x; i < waves; i += kBlock) mine += filled[i];
+    (void)block_exclusive_scan(mine, tmp, n);
+  }
   if (threadIdx.x != 0) return;
-  const int64_t n = ctl[SC_TOTAL] <= cap ? ctl[merged ? SC_RECORDS : SC_TOTAL] : 0;
+  n = total <= cap ? n : 0;
   ctl[SC_SORT] = n;
   ctl[SC_WORDS] = (n + 63) / 64;
 }
@@ -657,7 +667,8 @@ void samp_back(int kind, const vx_grid* g, int64_t max_samples, const SampWs& w,
   // when there are such samples, and its empty launches take 15 us.
   const int voxel_bits = 3 * g->log2_res;
   const bool own_pass = kind == 1 && voxel_bits % kRadixBits == 0;
-  hipLaunchKernelGGL(k_samp_n, dim3(1), dim3(64), 0, s, w.ctl, max_samples, kind == 0);
+  hipLaunchKernelGGL(k_samp_n, dim3(1), dim3(kBlock), 0, s, w.ctl, max_samples,
+                     kind == 0 ? (const int32_t*)w.filled : nullptr, emit_blocks(max_samples) * kWaves);
   const int low = w.bits.packed ? w.bits.id + w.bits.cnt : 0;
   const PairBufs P = radix_sort_pairs(sizeof(Key) == 8, kind == 0 || own_pass ? voxel_bits : voxel_bits + 1, w.a, w.b, w.a,
                                       w.ctl + SC_SORT, max_samples, w.hist, w.partial, s, low,

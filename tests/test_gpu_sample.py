@@ -229,3 +229,17 @@ def test_crowded_fiber_voxels(vx, fibers, points, step):
     say(f"case: sampled fibers {fibers} x {points}, steps of {step} voxels")
     _, g = _fibers(vx, wl, 2, 2)
     say(compare_samples(g, oracle.sample_fibers(wl.grid, wl.pts, wl.offsets, 2, 2), f"{fibers} x {points}"))
+
+
+@pytest.mark.parametrize("n,N", [(1, 512), (1, 513), (3, 2048), (1023, 2048), (1024, 2048), (2048, 2048), (2049, 2048)])
+def test_emission_stretches(vx, n, N):
+    """Equal triangles, so n N samples: around a wave's 512, and where the blocks stop growing and go on."""
+    rng = np.random.default_rng(n)
+    one = np.array([[0.0, 0.0, 0.0], [3.1, 0.2, 0.4], [0.3, 2.7, 1.9]])
+    tris = (one + np.round(rng.uniform(1.0, 50.0, size=(n, 1, 3)) * 64) / 64).astype(np.float32)
+    grid = synth.Grid((0.0, 0.0, 0.0), 64.0, 6)
+    say(f"case: sampled triangles, {n} equal ones of {N} samples")
+    p, g = _tris(vx, grid, tris, N)
+    ref = oracle.sample_triangles(grid, tris, N)
+    assert p.n_inside == ref.n_pairs
+    say(compare_samples(g, ref, f"{n} x {N}"))
