@@ -491,30 +491,6 @@ __global__ void __launch_bounds__(kBlock) k_samp_n(int64_t* ctl, int64_t cap, co
   ctl[SC_SORT] = n;
   ctl[SC_WORDS] = (n + 63) / 64;
 }
-// voxel starts from the head masks: a word's offset is the voxels that start before it
-struct MaskIn {
-  const uint64_t* mask;
-  __device__ int64_t operator()(int64_t i) const { return __popcll(mask[i]); }
-};
-struct MaskOut {
-  const uint64_t* mask;
-  int64_t* start;
-  int64_t cap;   // entries of start: the voxels' cap + 2
-  __device__ void operator()(int64_t i, int64_t ex, int64_t) const {
-    for (uint64_t m = mask[i]; m; m &= m - 1, ++ex)
-      if (ex < cap) start[ex] = 64 * i + __ffsll((unsigned long long)m) - 1;
-  }
-};
-struct SegTotal {
-  int64_t* start;
-  int64_t* ctl;
-  int64_t cap;
-  __device__ void operator()(int64_t total, int64_t) const {
-    if (total < cap) start[total] = ctl[SC_SORT];
-    ctl[SC_SEGS] = total;
-  }
-};
-
 // voxels = key segments, less the trailing one of samples outside the grid (fibers)
 __global__ void k_samp_finish(int kind, int64_t* ctl, int64_t* stats, int64_t cap, int64_t vcap) {
   if (threadIdx.x != 0) return;
@@ -544,28 +520,84 @@ struct Sorted {
   }
 };
 
-// one bit a sample: does its voxel start here?  One read of the samples instead of the two that a scan
-// over them takes (16.7 M records: 0.06 ms with the scan over the masks).
+// One bit a record: does its voxel start here?  One read of the records instead of the two that a scan over
+// them takes (16.7 M records, 3.1 M voxels: 0.061 ms with the starts).  A block serves a stretch of words
+// and leaves its number of starts: of 32 words at least, and eight waves, whose loads in flight a large
+// set needs (with four 0.077 ms).
+constexpr int kHeadRows = 8;
+constexpr int kHeadBlock = 512, kHeadWaves = kHeadBlock / 64;
+__device__ __forceinline__ int64_t head_chunk(int64_t words) {
+  const int64_t c = (words + gridDim.x - 1) / gridDim.x;
+  return (c + kHeadRows - 1) / kHeadRows * kHeadRows;
+}
+int head_blocks(int64_t max_samples) {
+  const int64_t b = ((max_samples + 63) / 64 + 31) / 32;
+  return int(b < 1 ? 1 : (b > kGrid ? kGrid : b));
+}
 template <class Key>
-__global__ void __launch_bounds__(kBlock) k_samp_heads(Sorted<Key> s, const int64_t* __restrict__ ctl,
-                                                       uint64_t* __restrict__ mask) {
-  constexpr int kRows = 8;
-  const int64_t n = ctl[SC_SORT], words = ctl[SC_WORDS];
-  const int64_t waves = int64_t(gridDim.x) * kWaves, wave = int64_t(blockIdx.x) * kWaves + (threadIdx.x >> 6);
-  for (int64_t w0 = wave * kRows; w0 < words; w0 += waves * kRows) {
-    Key k[kRows], p[kRows];
+__global__ void __launch_bounds__(kHeadBlock) k_samp_heads(Sorted<Key> s, const int64_t* __restrict__ ctl,
+                                                       uint64_t* __restrict__ mask, int64_t* __restrict__ partial) {
+  __shared__ int64_t tmp[kHeadWaves + 1];
+  const int64_t n = ctl[SC_SORT], words = ctl[SC_WORDS], chunk = head_chunk(words);
+  const int64_t b0 = int64_t(blockIdx.x) * chunk, b1 = b0 + chunk < words ? b0 + chunk : words;
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  int64_t count = 0;
+  for (int64_t w0 = b0 + wave * kHeadRows; w0 < b1; w0 += kHeadWaves * kHeadRows) {
+    Key k[kHeadRows], p[kHeadRows];
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      const int64_t i = (w0 + r) * 64 + lane_id();
+    for (int r = 0; r < kHeadRows; ++r) {
+      const int64_t i = (w0 + r) * 64 + lane;
       k[r] = i < n ? s.key(i) : Key(0);
       p[r] = i < n && i > 0 ? s.key(i - 1) : Key(0);
     }
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      const int64_t i = (w0 + r) * 64 + lane_id();
+    for (int r = 0; r < kHeadRows; ++r) {
+      const int64_t i = (w0 + r) * 64 + lane;
       const uint64_t m = __ballot(i < n && (i == 0 || k[r] != p[r]));
-      if (lane_id() == 0 && w0 + r < words) mask[w0 + r] = m;
+      if (lane == 0 && w0 + r < b1) mask[w0 + r] = m;
+      count += w0 + r < b1 ? __popcll(m) : 0;
     }
+  }
+  int64_t all;
+  (void)block_exclusive_scan_n<kHeadWaves>(lane == 0 ? count : int64_t(0), tmp, all);
+  if (threadIdx.x == 0) partial[blockIdx.x] = all;
+}
+
+// Voxel starts from the masks: a word's offset is the voxels that start before it.  A block scans its
+// words' counts, one a thread, and its waves write the starts, a lane per bit and four words at a time
+// (a thread writing all the starts of a word took 20 us of 20,000 samples in as many voxels).  start has cap
+// entries, the voxels' capacity + 2.
+__global__ void __launch_bounds__(kBlock) k_samp_starts(const uint64_t* __restrict__ mask, int64_t* __restrict__ ctl,
+                                                        const int64_t* __restrict__ partial,
+                                                        int64_t* __restrict__ start, int64_t cap) {
+  __shared__ int64_t tmp[kWaves + 1];
+  __shared__ uint64_t word[kBlock];
+  __shared__ int32_t at[kBlock];
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+  const uint64_t lt = (uint64_t(1) << lane) - 1;
+  const int64_t words = ctl[SC_WORDS], chunk = head_chunk(words);
+  const int64_t b0 = int64_t(blockIdx.x) * chunk, b1 = b0 + chunk < words ? b0 + chunk : words;
+  int64_t all, base = block_scan_base(partial, tmp, all);
+  if (blockIdx.x == 0 && tid == 0) {
+    if (all < cap) start[all] = ctl[SC_SORT];
+    ctl[SC_SEGS] = all;
+  }
+  for (int64_t t0 = b0; t0 < b1; t0 += kBlock) {
+    const uint64_t m = t0 + tid < b1 ? mask[t0 + tid] : 0;
+    int64_t tot;
+    at[tid] = int32_t(block_exclusive_scan(int64_t(__popcll(m)), tmp, tot));
+    word[tid] = m;
+    __syncthreads();
+    for (int q0 = wave * 4; q0 < kBlock && t0 + q0 < b1; q0 += kWaves * 4) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {                  // (words past b1 are empty)
+        const uint64_t x = word[q0 + r];
+        const int64_t v = base + at[q0 + r] + __popcll(x & lt);
+        if (((x >> lane) & 1) && v < cap) start[v] = 64 * (t0 + q0 + r) + lane;
+      }
+    }
+    base += tot;
+    __syncthreads();
   }
 }
 
@@ -684,9 +716,10 @@ void samp_back(int kind, const vx_grid* g, int64_t max_samples, const SampWs& w,
   const Sorted<Key> sorted{(const Key*)P.keys, P.prim, w.bits};
   {
     VX_TIMED("sample_heads", s);
-    hipLaunchKernelGGL(k_samp_heads<Key>, dim3(blocks_for(max_samples)), dim3(kBlock), 0, s, sorted, w.ctl, w.mask);
-    device_scan(MaskIn{w.mask}, MaskOut{w.mask, w.start, out->cap + 2}, SegTotal{w.start, w.ctl, out->cap + 2},
-                w.ctl + SC_WORDS, (max_samples + 63) / 64, w.partial, s);
+    const int blocks = head_blocks(max_samples);
+    hipLaunchKernelGGL(k_samp_heads<Key>, dim3(blocks), dim3(kHeadBlock), 0, s, sorted, w.ctl, w.mask, w.partial);
+    hipLaunchKernelGGL(k_samp_starts, dim3(blocks), dim3(kBlock), 0, s, w.mask, w.ctl, w.partial, w.start,
+                       out->cap + 2);
     hipLaunchKernelGGL(k_samp_finish, dim3(1), dim3(64), 0, s, kind, w.ctl, stats, max_samples, out->cap);
   }
   VX_TIMED("sample_reduce", s);

@@ -243,3 +243,19 @@ def test_emission_stretches(vx, n, N):
     ref = oracle.sample_triangles(grid, tris, N)
     assert p.n_inside == ref.n_pairs
     say(compare_samples(g, ref, f"{n} x {N}"))
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 2047, 2048, 2049, 16384, 16449, 70001])
+@pytest.mark.parametrize("alike", [1, 3, 100])
+def test_voxel_starts(vx, n, alike):
+    """Records around the 64s of a mask word and the words of a block, every one in a voxel of its own, a
+    few to a voxel, many."""
+    cells = np.arange(n) // alike
+    at = np.stack([cells % 64, cells // 64 % 64, cells // 4096], -1)[:, None, :]
+    tri = np.array([[0.3, 0.3, 0.3], [0.6, 0.3, 0.4], [0.3, 0.6, 0.5]])
+    tris = np.random.default_rng(n).permutation((at + tri).astype(np.float32))
+    grid = synth.Grid((0.0, 0.0, 0.0), 64.0, 6)
+    say(f"case: sampled triangles, {n} records, {alike} a voxel")
+    p, g = _tris(vx, grid, tris, 1)
+    assert p.n_samples == n and len(g["keys"]) == (n + alike - 1) // alike
+    say(compare_samples(g, oracle.sample_triangles(grid, tris, 1), f"{n} records"))
